@@ -26,13 +26,19 @@ constexpr size_t kAlign = 256;
 constexpr int64_t kLatticeMinCells = 16384;
 // Double-buffered states up to this size are stored with plain stores.
 constexpr size_t kCachedStateBytes = size_t(1) << 30;
+// Smallest z-plane and state of a lattice stored in blocks (blocked_layout).
+constexpr int64_t kBlockedMinPlane = 1024;
+constexpr uint64_t kBlockedMinState = uint64_t(128) << 20;
 // Pad after each population plane (see make_layout).
 constexpr int64_t kPlanePadBytes = 1280;
+// Pad after each distribution's region of a blocked lattice.
+constexpr int64_t kRegionPadBytes = 1280;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
   int64_t ncells = 0, cs = 0;
+  rlb::StateLayout lay{};  // D3Q19 populations
   size_t esz = 0;
   size_t off_descs = 0, off_small = 0, off_bad = 0, off_partials = 0, off_xparts = 0,
          off_buf0 = 0, off_buf1 = 0;
@@ -89,6 +95,22 @@ bool lattice_path(int32_t n_members, int64_t ncells) {
 
 // Velocities per distribution of a lattice kind.
 int nvel(int32_t lattice) { return lattice == RLB_D2Q9 ? 9 : 19; }
+
+// Is a D3Q19 lattice stored in blocks of 32 cells (StateLayout)? Its z-planes
+// must be large enough that rounding them up to whole blocks costs at most 3 %
+// of the memory, and small enough for 32-bit byte offsets within a plane. The
+// adjoint reads its tape in planes. Blocks pay once a step is bound by memory
+// (one-step kernels, planes against blocks: 96^3 FP32 47.6 and 43.1 us, 128^3
+// FP64 237 and 218 us, 256^3 FP32 908 and 877 us); below about 128 MiB of
+// double-buffered state the steps are bound by latency and the block
+// arithmetic shows (40^3 FP64 9.4 and 9.9 us).
+bool blocked_layout(const rlb_params& p, int32_t n, const rlb_options& o, int64_t ncells,
+                    size_t esz) {
+  const int64_t nxy = (int64_t)p.nx * p.ny;
+  return o.lattice == RLB_D3Q19 && o.ckpt_every == 0 && lattice_path(n, ncells) &&
+         nxy >= kBlockedMinPlane && 2 * 38 * (uint64_t)ncells * esz >= kBlockedMinState &&
+         (uint64_t)(nxy + rlb::kBlock) * 19 * esz < (uint64_t(1) << 32);
+}
 
 // Tile geometry of a D2Q9 tile variant on an nx x ny lattice: halo cells a
 // side (y doubled with the correction term), owned cells per tile and the
@@ -175,7 +197,18 @@ rlb_status make_layout(const rlb_params* m, int32_t n, const rlb_options* opt, L
   L.export_parts = (int)std::min<int64_t>(std::max<int64_t>((L.ncells + 255) / 256, 1), 65536);
   L.off_xparts = o;
   o = align_up(o + sizeof(double) * 5 * (size_t)L.export_parts);
-  const size_t buf = 2 * (size_t)nvel(opt->lattice) * (size_t)L.cs * L.esz;
+  size_t buf = 2 * (size_t)nvel(opt->lattice) * (size_t)L.cs * L.esz;
+  const int64_t nxy = (int64_t)m[0].nx * m[0].ny;
+  L.lay = rlb::plane_layout(L.cs, n == 1 ? (uint32_t)nxy : 1u);
+  if (blocked_layout(m[0], n, *opt, L.ncells, L.esz)) {
+    L.lay.shift = rlb::kBlockShift;
+    L.lay.nxy = (uint32_t)nxy;
+    L.lay.zcells = (uint32_t)((nxy + rlb::kBlock - 1) / rlb::kBlock * rlb::kBlock);
+    L.lay.pstr = rlb::kBlock;
+    L.lay.bextra = 18 * rlb::kBlock;
+    L.lay.greg = (int64_t)L.lay.zcells * m[0].nz * 19 + kRegionPadBytes / (int64_t)L.esz;
+    buf = 2 * (size_t)L.lay.greg * L.esz;
+  }
   L.off_buf0 = o;
   o = align_up(o + buf);
   L.off_buf1 = o;
@@ -242,6 +275,7 @@ struct rlb_sim {
   int q = 19;
   bool lattice = false;
   LatticeGeom geom{};
+  rlb::MarchGrid march{};  // blocked D3Q19 lattices
   int variant = 0;
   int64_t steps = 0;
   int64_t diag_step = -1;
@@ -303,6 +337,32 @@ rlb_status launch_lattice_step(rlb_sim* h, int variant, bool diag, const void* s
                                           h->d_partials, h->d_bad, h->stream));
 }
 
+// D3Q19 marching variants: two steps per launch; steps that cannot be paired
+// (the odd one of a call, diagnostics steps) run the one-step kernel kMarchStep.
+constexpr int kMarchStep = 2;
+
+// A marching launch is the default from this share of used cells on (MarchGrid::use).
+// At full use it updates 29 G cells/s in FP32 against 18-19 of the one-step
+// kernels (FP64: 13 against 9). Both sides per step, by use: 40x40x400 FP32
+// (0.42) 40.5 against 32.7 us, 80^3 FP32 (0.59) 25.2 and 27.4, 64^3 FP64 (0.65)
+// 22.1 and 25.2, 96^3 FP32 (0.74) 34.8 and 43.1. With the extended model, whose
+// arithmetic weighs more: 96^3 FP32 (0.74) 48.5 against 45.3, 128^3 FP32 (0.85)
+// 104 and 114.
+constexpr double kMarchUse = 0.6, kMarchUseExt = 0.8;
+
+bool is_march_variant(const rlb_sim* h, int v) {
+  return h->lattice && !h->d2 && v >= rlb::num_lattice_variants();
+}
+
+// A lattice stored in planes runs a marching variant's steps one by one.
+bool can_march(const rlb_sim* h) { return h->L.lay.shift == rlb::kBlockShift; }
+
+rlb_status launch_march(rlb_sim* h, int variant, const void* src, void* dst) {
+  return dev_err(rlb::launch_step_march(h->precision, variant - rlb::num_lattice_variants(),
+                                        h->ext, src, dst, h->geom, h->march, h->d_bad,
+                                        h->stream));
+}
+
 bool is_tile_variant(const rlb_sim* h, int v) {
   return h->lattice && h->d2 && v >= rlb::d2q9_num_lattice_variants();
 }
@@ -317,8 +377,8 @@ int lattice_parts(const rlb_sim* h, int variant) {
                   a, grid);
     return (int)(grid.x * grid.y);
   }
-  return h->d2 ? rlb::d2q9_lattice_partials(variant, h->geom)
-               : rlb::lattice_partials(variant, h->geom);
+  if (h->d2) return rlb::d2q9_lattice_partials(variant, h->geom);
+  return rlb::lattice_partials(is_march_variant(h, variant) ? kMarchStep : variant, h->geom);
 }
 
 // D2Q9 tile rounds: ceil(n / H) launches, each advancing up to H steps of the
@@ -688,14 +748,27 @@ rlb_status advance(rlb_sim* h, int32_t n) {
     return RLB_OK;
   }
   if (h->lattice) {
+    const bool march = is_march_variant(h, h->variant);
+    const int one = march ? kMarchStep : h->variant;
     for (int32_t i = 0; i < n; ++i) {
       const int64_t s = h->steps + 1;
-      const bool diag = D > 0 && (s % D == 0 || i == n - 1);
-      rlb_status st = launch_lattice_step(h, h->variant, diag, state_buf(h), spare_buf(h));
+      const auto is_diag = [&](int64_t step, int32_t at) {
+        return D > 0 && (step % D == 0 || at == n - 1);
+      };
+      const bool diag = is_diag(s, i);
+      if (march && can_march(h) && i + 1 < n && !diag && !is_diag(s + 1, i + 1)) {
+        rlb_status st = launch_march(h, h->variant, state_buf(h), spare_buf(h));
+        if (st != RLB_OK) return st;
+        h->cur = 1 - h->cur;
+        h->steps = s + 1;
+        ++i;
+        continue;
+      }
+      rlb_status st = launch_lattice_step(h, one, diag, state_buf(h), spare_buf(h));
       if (st != RLB_OK) return st;
       if (diag) {
         h->diag_step = s;
-        h->diag_parts = lattice_parts(h, h->variant);
+        h->diag_parts = lattice_parts(h, one);
       }
       h->cur = 1 - h->cur;
       h->steps = s;
@@ -768,6 +841,8 @@ const char* kernel_name_of(const rlb_sim* h, int v) {
     if (is_strip_variant(h, v)) return rlb::d2q9_strip_kernel_name(h->precision, strip_index(v));
     return rlb::d2q9_member_kernel_name(h->precision, v);
   }
+  if (is_march_variant(h, v))
+    return rlb::march_kernel_name(h->precision, v - rlb::num_lattice_variants());
   if (h->lattice) return rlb::lattice_kernel_name(h->precision, v);
   if (v < rlb::num_member_variants()) return rlb::member_kernel_name(h->precision, v);
   if (is_segment_variant(h, v))
@@ -947,7 +1022,7 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   const hipError_t ie =
       planar ? rlb::d2q9_launch_init(h->precision, h->buf[0], L.cs, h->d_descs, n_members, dn,
                                      de, du, L.ncells, h->stream)
-             : rlb::launch_init(h->precision, h->buf[0], L.cs, h->d_descs, n_members, dn, de, du,
+             : rlb::launch_init(h->precision, h->buf[0], L.lay, h->d_descs, n_members, dn, de, du,
                                 L.ncells, h->stream);
   if (ie != hipSuccess) return fail(RLB_E_DEVICE);
   if (hipMemcpyAsync(h->descs.data(), h->d_descs, sizeof(MemberDesc) * n_members,
@@ -963,6 +1038,7 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     h->geom.bcy = d.bcy;
     h->geom.bcz = d.bcz;
     h->geom.cs = L.cs;
+    h->geom.lay = L.lay;
     h->geom.rt = d.rt;
     h->geom.ref = d.ref;
     h->geom.ext = d.ext;
@@ -971,6 +1047,11 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     // at 80-160 MB, even at 320 MB, 10 % faster at 640 MB; nontemporal stores
     // 4-5 % faster from 1.3 GB up, e.g. the 5.1 GB of 256^3).
     h->geom.cached_store = 2 * (L.off_buf1 - L.off_buf0) <= kCachedStateBytes ? 1 : 0;
+  }
+  if (can_march(h)) {
+    h->march = rlb::march_grid(h->precision, h->geom, h->num_cu);
+    if (h->march.use >= (h->ext ? kMarchUseExt : kMarchUse))
+      h->variant = rlb::num_lattice_variants();
   }
   h->cur = 0;
   if (opt->ckpt_every > 0) {
@@ -1033,7 +1114,7 @@ rlb_status rlb_moments(rlb_handle h, double* n, double* eps, double* P, double* 
                                     h->n_members, nc, dn, de, dP, dg, du, h->d_xparts, nparts,
                                     h->stream));
   else
-    RLB_HIP(rlb::launch_export(h->precision, state_buf(h), h->L.cs, h->d_descs, h->n_members,
+    RLB_HIP(rlb::launch_export(h->precision, state_buf(h), h->L.lay, h->d_descs, h->n_members,
                                nc, dn, de, dP, dg, du, h->d_xparts, nparts, h->stream));
   RLB_HIP(rlb::launch_reduce(h->d_xparts, nparts, h->d_small, h->stream));
   double hs[5];
@@ -1086,7 +1167,7 @@ rlb_status rlb_populations(rlb_handle h, double* f, double* g, int32_t out_on_de
     return h->d2 ? rlb::d2q9_launch_population_planes(h->precision, state_buf(h), h->L.cs,
                                                       h->d_descs, h->n_members, nc, p0, np, out,
                                                       h->stream)
-                 : rlb::launch_population_planes(h->precision, state_buf(h), h->L.cs,
+                 : rlb::launch_population_planes(h->precision, state_buf(h), h->L.lay,
                                                  h->d_descs, h->n_members, nc, p0, np, out,
                                                  h->stream);
   };
@@ -1139,7 +1220,7 @@ rlb_status rlb_num_variants(rlb_handle h, int32_t* count) {
     *count = h->lattice ? rlb::d2q9_num_lattice_variants() + rlb::d2q9_num_tile_variants()
                         : rlb::d2q9_num_member_variants() + rlb::d2q9_num_strip_variants();
   else
-    *count = h->lattice ? rlb::num_lattice_variants()
+    *count = h->lattice ? rlb::num_lattice_variants() + rlb::num_march_variants()
                         : rlb::num_member_variants() + rlb::num_segment_variants() +
                               rlb::num_tube_variants();
   return RLB_OK;
@@ -1197,8 +1278,15 @@ rlb_status rlb_tune(rlb_handle h, int32_t trial_steps, int32_t* best_variant,
           st = RLB_OK;
         }
       } else if (h->lattice) {
-        for (int i = 0; i < trial_steps && st == RLB_OK; ++i)
-          st = launch_lattice_step(h, v, false, state_buf(h), spare_buf(h));
+        const bool march = is_march_variant(h, v);
+        for (int i = 0; i < trial_steps && st == RLB_OK; ++i) {
+          if (march && can_march(h) && i + 1 < trial_steps) {
+            st = launch_march(h, v, state_buf(h), spare_buf(h));
+            ++i;
+          } else {
+            st = launch_lattice_step(h, march ? kMarchStep : v, false, state_buf(h), spare_buf(h));
+          }
+        }
       } else if (st == RLB_OK) {
         bool flip = false;
         st = launch_persistent(h, v, trial_steps, 0, state_buf(h), spare_buf(h), 0, 0, &flip);

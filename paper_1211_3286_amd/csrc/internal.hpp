@@ -21,11 +21,43 @@ struct MemberDesc {
   Ext ext;  // eta/s relaxation times and equation of state (EXT kernels, init, export)
 };
 
+// Where the D3Q19 populations of a buffer lie. Cell (x, y, z) of a lattice has
+// the index t = x + nx y + zcells z, and population a of a distribution the
+// element  t + (t >> shift) * bextra + a * pstr  of that distribution's region;
+// the g region starts greg elements after the f region.
+//   planes (shift 31): pstr = cs, the plane stride, bextra = 0;
+//   blocks (shift 5): the 19 populations of 32 cells in a row lie together,
+//     pstr = 32, bextra = 18 * 32, and zcells is nx ny rounded up to 32.
+// Batches, tapes and the D2Q9 buffers are planes; a lattice whose z-planes
+// are large enough is blocked (blocked_layout in api.cpp).
+struct StateLayout {
+  int32_t shift;
+  uint32_t nxy, zcells;  // cells of a z-plane, and the index distance of two
+  int64_t pstr, bextra, greg;
+};
+
+constexpr int kBlockShift = 5;
+constexpr int kBlock = 1 << kBlockShift;
+
+inline StateLayout plane_layout(int64_t cs, uint32_t nxy = 1u) {
+  return StateLayout{31, nxy, nxy, cs, 0, 19 * cs};
+}
+
+// Index t of cell i of a packed lattice (or batch: zcells = nxy there).
+__device__ __forceinline__ uint32_t cell_index(const StateLayout& l, uint32_t i) {
+  return l.zcells == l.nxy ? i : i + (i / l.nxy) * (l.zcells - l.nxy);
+}
+
+__device__ __forceinline__ int64_t cell_element(const StateLayout& l, uint32_t t) {
+  return (int64_t)t + (int64_t)(t >> l.shift) * l.bextra;
+}
+
 // Geometry of a single-lattice launch (the per-step fused kernel).
 struct LatticeGeom {
   int32_t nx, ny, nz;
   int32_t bcx, bcy, bcz;
-  int64_t cs;  // plane stride in elements
+  int64_t cs;  // plane stride in elements (D2Q9)
+  StateLayout lay;  // D3Q19
   Rates rt;
   Ref ref;
   Ext ext;  // eta/s relaxation times and equation of state (EXT kernels, init, export)
@@ -72,14 +104,29 @@ hipError_t launch_member_refs(const MemberDesc* descs, int n_members, const doub
 hipError_t launch_validate(const double* n0, const double* eps0, const double* u0,
                            int64_t ncells, int planar, const MemberDesc* descs, int n_members,
                            unsigned long long* count, hipStream_t s);
-hipError_t launch_init(int precision, void* state, int64_t cs, const MemberDesc* descs,
+hipError_t launch_init(int precision, void* state, const StateLayout& l, const MemberDesc* descs,
                        int n_members, const double* n0, const double* eps0, const double* u0,
                        int64_t ncells, hipStream_t s);
 // ext: the extended model (relaxation times from eta/s, general equation of state).
 hipError_t launch_step_lattice(int precision, int variant, bool diag, bool ext, const void* src,
                                void* dst, const LatticeGeom& g, double* partials,
                                unsigned long long* bad, hipStream_t s);
+hipError_t launch_step_blocks(int precision, int variant, bool diag, bool ext, const void* src,
+                              void* dst, const LatticeGeom& g, double* partials,
+                              unsigned long long* bad, hipStream_t s);  // blocked lattices
 int lattice_partials(int variant, const LatticeGeom& g);  // number of blocks
+// Two steps per launch on one D3Q19 lattice stored in blocks (march.hip): the
+// state after two steps into dst.
+struct MarchGrid {
+  int ntx, ntiles, nchunks;  // tiles along x, tiles, z ranges
+  double use;  // share of the launch's cell slots that are cells of the lattice
+};
+int num_march_variants();
+MarchGrid march_grid(int precision, const LatticeGeom& g, int cus);  // cus: of the device
+const char* march_kernel_name(int precision, int variant);
+hipError_t launch_step_march(int precision, int variant, bool ext, const void* src, void* dst,
+                             const LatticeGeom& g, const MarchGrid& m, unsigned long long* bad,
+                             hipStream_t s);
 // Kernel function pointer and launch shape of the persistent member kernel
 // (for graph nodes). args must outlive the launch.
 struct MemberLaunch {
@@ -163,10 +210,10 @@ hipError_t segment_kernel(int precision, int variant, const void** func, dim3* b
 const char* segment_kernel_name(int precision, int variant);
 hipError_t launch_step_members(int precision, int variant, int n_members, const MemberLaunch& a,
                                hipStream_t s);
-hipError_t launch_export(int precision, const void* state, int64_t cs, const MemberDesc* descs,
-                         int n_members, int64_t ncells, double* n, double* eps, double* P,
+hipError_t launch_export(int precision, const void* state, const StateLayout& l,
+                         const MemberDesc* descs, int n_members, int64_t ncells, double* n, double* eps, double* P,
                          double* gamma, double* u, double* partials, int nparts, hipStream_t s);
-hipError_t launch_population_planes(int precision, const void* state, int64_t cs,
+hipError_t launch_population_planes(int precision, const void* state, const StateLayout& l,
                                     const MemberDesc* descs, int n_members, int64_t ncells,
                                     int p0, int np, double* out, hipStream_t s);
 hipError_t launch_reduce(const double* partials, int nparts, double* out5, hipStream_t s);

@@ -15,125 +15,11 @@
 
 #include "device_util.hpp"
 #include "internal.hpp"
+#include "step_lattice.hpp"
 
 namespace rlb {
 
 namespace {
-
-// -------------------------------------------------------------------------
-// Fused step on one lattice: grid (ceil(nx/BX), ceil(ny/BY), ceil(nz/CZ)),
-// block (BX, BY); each thread updates CZ cells along z. EXT: relaxation times
-// of each cell from eta/s. Tiles are taken in the row-per-XCD order of
-// block_tile. NTS: nontemporal stores; without, plain stores, which the host
-// picks when the double-buffered state fits the memory-side cache, so that the
-// next step reads it back from there. (The store kind is a template argument:
-// two store loops that differ only in the hint behind a run-time branch get
-// merged by the compiler, which keeps the plain form.)
-// -------------------------------------------------------------------------
-template <typename T, int BX, int BY, int CZ, bool DIAG, bool EXT, bool NTS>
-__global__ __launch_bounds__(BX* BY) void k_step_lattice(const T* __restrict__ src,
-                                                        T* __restrict__ dst, LatticeGeom geo,
-                                                        double* __restrict__ partials,
-                                                        unsigned long long* __restrict__ bad) {
-  int bx, by, bz;
-  block_tile(bx, by, bz);
-  const int x = bx * BX + threadIdx.x;
-  const int y = by * BY + threadIdx.y;
-  const int tid = threadIdx.y * BX + threadIdx.x;
-  const bool act = (x < geo.nx) && (y < geo.ny);
-  double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  int nbad = 0;
-  const uint32_t esz = sizeof(T);
-#pragma unroll 1
-  for (int k = 0; k < CZ; ++k) {
-    const int z = bz * CZ + k;
-    if (act && z < geo.nz) {
-      uint32_t off[19], self;
-      pull_offsets(x, y, z, geo.nx, geo.ny, geo.nz, geo.bcx, geo.bcy, geo.bcz, 0u, esz, off,
-                   self);
-      if constexpr (!EXT && (sizeof(T) == 8 || CZ == 1)) {
-        // g first (its recovery needs no f), then f with the recovered
-        // velocity: one distribution's 19 values in flight at a time. FP64:
-        // 142 instead of 154 VGPRs, 1.5 % faster; FP32 with one cell per
-        // thread: 0.3-0.5 % faster (with several cells per thread FP32 lost
-        // 2-9 %, and loads both at once). The arithmetic is that of collide(),
-        // bit for bit. (The relaxation times from eta/s and the general
-        // equation of state need N before the recovery, so the EXT kernels
-        // load both at once.)
-        T g[19];
-#pragma unroll
-        for (int a = 0; a < 19; ++a) g[a] = ld(src + (int64_t)(19 + a) * geo.cs, off[a]);
-        double E, Mx, My, Mz, gs;
-        g_sums(g, geo.ref, E, Mx, My, Mz, gs);
-        Macro mac;
-        const bool ok = recover(E, Mx, My, Mz, mac);
-        if (ok) collide_g(g, Mx, My, Mz, gs, mac, geo.rt, geo.ref);
-#pragma unroll
-        for (int a = 0; a < 19; ++a) {
-          if constexpr (NTS)
-            st_nt(dst + (int64_t)(19 + a) * geo.cs, self, g[a]);
-          else
-            st(dst + (int64_t)(19 + a) * geo.cs, self, g[a]);
-        }
-        T f[19];
-#pragma unroll
-        for (int a = 0; a < 19; ++a) f[a] = ld(src + (int64_t)a * geo.cs, off[a]);
-        double fs = 0.0;
-#pragma unroll
-        for (int a = 0; a < 19; ++a) fs += (double)f[a];
-        const double N = geo.ref.n + fs;
-        if (ok) collide_f(f, N, fs, mac, geo.rt, geo.ref);
-#pragma unroll
-        for (int a = 0; a < 19; ++a) {
-          if constexpr (NTS)
-            st_nt(dst + (int64_t)a * geo.cs, self, f[a]);
-          else
-            st(dst + (int64_t)a * geo.cs, self, f[a]);
-        }
-        nbad += ok ? 0 : 1;
-        if (DIAG) {
-          acc[0] += N;
-          acc[1] += E;
-          acc[2] += Mx;
-          acc[3] += My;
-          acc[4] += Mz;
-        }
-      } else {
-        T f[19], g[19];
-#pragma unroll
-        for (int a = 0; a < 19; ++a) {
-          f[a] = ld(src + (int64_t)a * geo.cs, off[a]);
-          g[a] = ld(src + (int64_t)(19 + a) * geo.cs, off[a]);
-        }
-        Sums s;
-        const bool ok = collide<T, EXT>(f, g, geo.rt, geo.ref, s, &geo.ext);
-        nbad += ok ? 0 : 1;
-        if (DIAG)
-#pragma unroll
-          for (int i = 0; i < 5; ++i) acc[i] += s.v[i];
-#pragma unroll
-        for (int a = 0; a < 19; ++a) {
-          if constexpr (NTS) {
-            st_nt(dst + (int64_t)a * geo.cs, self, f[a]);
-            st_nt(dst + (int64_t)(19 + a) * geo.cs, self, g[a]);
-          } else {
-            st(dst + (int64_t)a * geo.cs, self, f[a]);
-            st(dst + (int64_t)(19 + a) * geo.cs, self, g[a]);
-          }
-        }
-      }
-    }
-  }
-  if (nbad) count_bad(bad, nbad);
-  if (DIAG) {
-    block_sum5<BX * BY>(acc, tid);
-    if (tid == 0) {
-      const int64_t b = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-#pragma unroll
-      for (int i = 0; i < 5; ++i) partials[b * 5 + i] = acc[i];
-    }
-  }
-}
 
 // -------------------------------------------------------------------------
 // Persistent step over a batch: one block per member, all nsteps inside the
@@ -445,7 +331,7 @@ __global__ __launch_bounds__(256) void k_validate(const double* n0, const double
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_init(T* state, int64_t cs, const MemberDesc* descs,
+__global__ __launch_bounds__(256) void k_init(T* state, StateLayout l, const MemberDesc* descs,
                                               int n_members, const double* n0,
                                               const double* eps0, const double* u0,
                                               int64_t ncells) {
@@ -455,16 +341,17 @@ __global__ __launch_bounds__(256) void k_init(T* state, int64_t cs, const Member
     double f[19], g[19];
     const double P = pressure_of(eps0[i], n0[i], d.ext);
     equilibrium_dev(n0[i], eps0[i], P, u0[i], u0[ncells + i], u0[2 * ncells + i], d.ref, f, g);
+    T* const c = state + cell_element(l, cell_index(l, (uint32_t)i));
 #pragma unroll
     for (int a = 0; a < 19; ++a) {
-      state[a * cs + i] = (T)f[a];
-      state[(19 + a) * cs + i] = (T)g[a];
+      c[a * l.pstr] = (T)f[a];
+      c[l.greg + a * l.pstr] = (T)g[a];
     }
   }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_export(const T* state, int64_t cs,
+__global__ __launch_bounds__(256) void k_export(const T* state, StateLayout l,
                                                 const MemberDesc* descs, int n_members,
                                                 int64_t ncells, double* n, double* eps,
                                                 double* P, double* gamma, double* u,
@@ -474,10 +361,11 @@ __global__ __launch_bounds__(256) void k_export(const T* state, int64_t cs,
        i += (int64_t)gridDim.x * 256) {
     const MemberDesc& d = descs[find_member(descs, n_members, i)];
     T f[19], g[19];
+    const T* const c = state + cell_element(l, cell_index(l, (uint32_t)i));
 #pragma unroll
     for (int a = 0; a < 19; ++a) {
-      f[a] = state[a * cs + i];
-      g[a] = state[(19 + a) * cs + i];
+      f[a] = c[a * l.pstr];
+      g[a] = c[l.greg + a * l.pstr];
     }
     double N, E, Mx, My, Mz, fs, gs;
     cell_sums(f, g, d.ref, N, E, Mx, My, Mz, fs, gs);
@@ -512,16 +400,18 @@ __global__ __launch_bounds__(256) void k_export(const T* state, int64_t cs,
 // Planes [p0, p0 + np) of the state as FP64 populations (reference added back);
 // plane p < 19 is f_p, plane p >= 19 is g_(p-19). out[(p - p0) * ncells + cell].
 template <typename T>
-__global__ __launch_bounds__(256) void k_population_planes(const T* state, int64_t cs,
+__global__ __launch_bounds__(256) void k_population_planes(const T* state, StateLayout l,
                                                            const MemberDesc* descs, int n_members,
                                                            int64_t ncells, int p0, int np,
                                                            double* out) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ncells;
        i += (int64_t)gridDim.x * 256) {
     const Ref ref = descs[find_member(descs, n_members, i)].ref;
+    const T* const c = state + cell_element(l, cell_index(l, (uint32_t)i));
     for (int p = p0; p < p0 + np; ++p) {
       const double r = p < 19 ? weight(p) * ref.n : gref_unit(p - 19) * ref.P;
-      out[(int64_t)(p - p0) * ncells + i] = (double)state[p * cs + i] + r;
+      const int64_t e = p < 19 ? p * l.pstr : l.greg + (p - 19) * l.pstr;
+      out[(int64_t)(p - p0) * ncells + i] = (double)c[e] + r;
     }
   }
 }
@@ -538,16 +428,6 @@ __global__ __launch_bounds__(256) void k_reduce(const double* partials, int npar
 }
 
 // ------------------------------ variants ---------------------------------
-// The /w3 forms reserve 44 KiB of LDS per 256-thread block that the kernel
-// never touches: 3 blocks fit in a CU's 160 KiB where 4 would by registers, so
-// they run 3 waves per SIMD instead of 4. On 512^3 FP32 lattices the 256 x 1
-// block ran 2 % faster so (fewer streams in flight per channel); on 256^3
-// the blocks were within 1 %.
-constexpr unsigned kOcc3Lds = 44 * 1024;
-constexpr LatticeVariant kLat[] = {{64, 1, 1},  {64, 4, 1},  {128, 2, 1}, {256, 1, 1},
-                                   {64, 4, 2},  {256, 1, 2}, {128, 2, 4}, {256, 1, 4},
-                                   {128, 2, 1}, {256, 1, 1}};
-constexpr int kNumLat = sizeof(kLat) / sizeof(kLat[0]);
 // At most 512 threads: with 1024 (4 waves per SIMD, at most 128 VGPRs) every
 // member build spills to scratch, which the build refuses for every kernel.
 constexpr MemberVariant kMem[] = {{256, 1}, {512, 1}, {256, 2}, {512, 2}};
@@ -588,51 +468,6 @@ int grid_for(int64_t n) {
   if (b > 65536) b = 65536;
   if (b < 1) b = 1;
   return (int)b;
-}
-
-template <typename T, int BX, int BY, int CZ, bool EXT, bool NTS>
-void lat_launch_stores(bool diag, dim3 grid, dim3 block, unsigned lds, const void* src, void* dst,
-                       const LatticeGeom& g, double* partials, unsigned long long* bad,
-                       hipStream_t s) {
-  if (diag)
-    hipLaunchKernelGGL((k_step_lattice<T, BX, BY, CZ, true, EXT, NTS>), grid, block, lds, s,
-                       (const T*)src, (T*)dst, g, partials, bad);
-  else
-    hipLaunchKernelGGL((k_step_lattice<T, BX, BY, CZ, false, EXT, NTS>), grid, block, lds, s,
-                       (const T*)src, (T*)dst, g, partials, bad);
-}
-
-template <typename T, int BX, int BY, int CZ, bool EXT>
-hipError_t lat_launch(bool diag, const void* src, void* dst, const LatticeGeom& g,
-                      double* partials, unsigned long long* bad, hipStream_t s,
-                      unsigned lds = 0) {
-  dim3 block(BX, BY, 1);
-  dim3 grid((g.nx + BX - 1) / BX, (g.ny + BY - 1) / BY, (g.nz + CZ - 1) / CZ);
-  if (g.cached_store)
-    lat_launch_stores<T, BX, BY, CZ, EXT, false>(diag, grid, block, lds, src, dst, g, partials,
-                                                 bad, s);
-  else
-    lat_launch_stores<T, BX, BY, CZ, EXT, true>(diag, grid, block, lds, src, dst, g, partials,
-                                                bad, s);
-  return hipGetLastError();
-}
-
-template <typename T, bool EXT>
-hipError_t lat_dispatch(int v, bool diag, const void* src, void* dst, const LatticeGeom& g,
-                        double* partials, unsigned long long* bad, hipStream_t s) {
-  switch (v) {
-    case 0: return lat_launch<T, 64, 1, 1, EXT>(diag, src, dst, g, partials, bad, s);
-    case 1: return lat_launch<T, 64, 4, 1, EXT>(diag, src, dst, g, partials, bad, s);
-    case 2: return lat_launch<T, 128, 2, 1, EXT>(diag, src, dst, g, partials, bad, s);
-    case 3: return lat_launch<T, 256, 1, 1, EXT>(diag, src, dst, g, partials, bad, s);
-    case 4: return lat_launch<T, 64, 4, 2, EXT>(diag, src, dst, g, partials, bad, s);
-    case 5: return lat_launch<T, 256, 1, 2, EXT>(diag, src, dst, g, partials, bad, s);
-    case 6: return lat_launch<T, 128, 2, 4, EXT>(diag, src, dst, g, partials, bad, s);
-    case 7: return lat_launch<T, 256, 1, 4, EXT>(diag, src, dst, g, partials, bad, s);
-    case 8: return lat_launch<T, 128, 2, 1, EXT>(diag, src, dst, g, partials, bad, s, kOcc3Lds);
-    case 9: return lat_launch<T, 256, 1, 1, EXT>(diag, src, dst, g, partials, bad, s, kOcc3Lds);
-  }
-  return hipErrorInvalidValue;
 }
 
 template <typename T, bool EXT>
@@ -760,15 +595,15 @@ hipError_t launch_validate(const double* n0, const double* eps0, const double* u
   return hipGetLastError();
 }
 
-hipError_t launch_init(int precision, void* state, int64_t cs, const MemberDesc* descs,
+hipError_t launch_init(int precision, void* state, const StateLayout& l, const MemberDesc* descs,
                        int n_members, const double* n0, const double* eps0, const double* u0,
                        int64_t ncells, hipStream_t s) {
   dim3 grid(grid_for(ncells));
   if (precision)
-    hipLaunchKernelGGL(k_init<float>, grid, dim3(256), 0, s, (float*)state, cs, descs,
+    hipLaunchKernelGGL(k_init<float>, grid, dim3(256), 0, s, (float*)state, l, descs,
                        n_members, n0, eps0, u0, ncells);
   else
-    hipLaunchKernelGGL(k_init<double>, grid, dim3(256), 0, s, (double*)state, cs, descs,
+    hipLaunchKernelGGL(k_init<double>, grid, dim3(256), 0, s, (double*)state, l, descs,
                        n_members, n0, eps0, u0, ncells);
   return hipGetLastError();
 }
@@ -776,11 +611,9 @@ hipError_t launch_init(int precision, void* state, int64_t cs, const MemberDesc*
 hipError_t launch_step_lattice(int precision, int v, bool diag, bool ext, const void* src,
                                void* dst, const LatticeGeom& g, double* partials,
                                unsigned long long* bad, hipStream_t s) {
-  if (precision)
-    return ext ? lat_dispatch<float, true>(v, diag, src, dst, g, partials, bad, s)
-              : lat_dispatch<float, false>(v, diag, src, dst, g, partials, bad, s);
-  return ext ? lat_dispatch<double, true>(v, diag, src, dst, g, partials, bad, s)
-            : lat_dispatch<double, false>(v, diag, src, dst, g, partials, bad, s);
+  return g.lay.shift == kBlockShift
+             ? launch_step_blocks(precision, v, diag, ext, src, dst, g, partials, bad, s)
+             : lat_step<false>(precision, v, diag, ext, src, dst, g, partials, bad, s);
 }
 
 hipError_t member_kernel(int precision, int v, bool ext, const void** func, dim3* block) {
@@ -803,29 +636,29 @@ hipError_t launch_step_members(int precision, int v, int n_members, const Member
   return hipLaunchKernel(f, dim3(n_members), block, args, 0, s);
 }
 
-hipError_t launch_export(int precision, const void* state, int64_t cs, const MemberDesc* descs,
-                         int n_members, int64_t ncells, double* n, double* eps, double* P,
+hipError_t launch_export(int precision, const void* state, const StateLayout& l,
+                         const MemberDesc* descs, int n_members, int64_t ncells, double* n, double* eps, double* P,
                          double* gamma, double* u, double* partials, int nparts,
                          hipStream_t s) {
   if (precision)
-    hipLaunchKernelGGL(k_export<float>, dim3(nparts), dim3(256), 0, s, (const float*)state, cs,
+    hipLaunchKernelGGL(k_export<float>, dim3(nparts), dim3(256), 0, s, (const float*)state, l,
                        descs, n_members, ncells, n, eps, P, gamma, u, partials);
   else
     hipLaunchKernelGGL(k_export<double>, dim3(nparts), dim3(256), 0, s, (const double*)state,
-                       cs, descs, n_members, ncells, n, eps, P, gamma, u, partials);
+                       l, descs, n_members, ncells, n, eps, P, gamma, u, partials);
   return hipGetLastError();
 }
 
-hipError_t launch_population_planes(int precision, const void* state, int64_t cs,
+hipError_t launch_population_planes(int precision, const void* state, const StateLayout& l,
                                     const MemberDesc* descs, int n_members, int64_t ncells,
                                     int p0, int np, double* out, hipStream_t s) {
   dim3 grid(grid_for(ncells));
   if (precision)
     hipLaunchKernelGGL(k_population_planes<float>, grid, dim3(256), 0, s, (const float*)state,
-                       cs, descs, n_members, ncells, p0, np, out);
+                       l, descs, n_members, ncells, p0, np, out);
   else
     hipLaunchKernelGGL(k_population_planes<double>, grid, dim3(256), 0, s,
-                       (const double*)state, cs, descs, n_members, ncells, p0, np, out);
+                       (const double*)state, l, descs, n_members, ncells, p0, np, out);
   return hipGetLastError();
 }
 

@@ -122,6 +122,7 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
   double* d_parts = (double*)(ws + c.parts);
   double* d_xparts = (double*)(ws + c.xparts);
   void* buf[2] = {ws + c.buf0, ws + c.buf1};
+  const rlb::StateLayout lay = rlb::plane_layout(c.cs, (uint32_t)p.nx * (uint32_t)p.ny);
 
   // the array keeps the previous call's contents: clear the counters
   const size_t nzero = (c.parts - c.small) / sizeof(unsigned long long);
@@ -168,7 +169,7 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
   // t = 0: reference state and equilibria (rlb_init)
   NA_HIP(rlb::launch_member_refs(d_desc, 1, n0, eps0, u0, nc, d_parts, st));
   NA_HIP(d2 ? rlb::d2q9_launch_init(o.precision, buf[0], c.cs, d_desc, 1, n0, eps0, u0, nc, st)
-            : rlb::launch_init(o.precision, buf[0], c.cs, d_desc, 1, n0, eps0, u0, nc, st));
+            : rlb::launch_init(o.precision, buf[0], lay, d_desc, 1, n0, eps0, u0, nc, st));
   NA_HIP(hipMemcpyAsync(&desc, d_desc, sizeof(desc), hipMemcpyDeviceToHost, st));
   NA_HIP(hipStreamSynchronize(st));
 
@@ -181,6 +182,7 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
   g.bcy = desc.bcy;
   g.bcz = desc.bcz;
   g.cs = c.cs;
+  g.lay = lay;
   g.rt = desc.rt;
   g.ref = desc.ref;
   g.ext = desc.ext;
@@ -202,7 +204,7 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
     NA_HIP(rlb::d2q9_launch_export(o.precision, buf[cur], c.cs, d_desc, 1, nc, n, eps, P, gamma,
                                    u, d_xparts, c.export_parts, st));
   else
-    NA_HIP(rlb::launch_export(o.precision, buf[cur], c.cs, d_desc, 1, nc, n, eps, P, gamma, u,
+    NA_HIP(rlb::launch_export(o.precision, buf[cur], lay, d_desc, 1, nc, n, eps, P, gamma, u,
                               d_xparts, c.export_parts, st));
   NA_HIP(rlb::launch_reduce(d_xparts, c.export_parts, d_small, st));
   NA_HIP(rlb::launch_sum_bad(d_bad, d_bad_total, st));
