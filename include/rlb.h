@@ -184,12 +184,13 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
  * equilibria of Eqs. (7)-(9) (D2Q9: Eqs. 32-34); the f BGK collision of
  * Eq. (5) and the g MRT collision of Eqs. (30)-(31), m* = m - S(m - m_eq),
  * g* = M^-1 m* (Eq. 35), with the correction of Eq. (37) when selected.
- * Single-member lattices run one fused kernel launch per step (D2Q9: or
- * rounds of H steps on tiles held in LDS); batches (and small single
- * lattices) run in a HIP graph, either all nsteps inside one persistent
- * launch, or as rounds of H steps on segments held in LDS (1 x 1 x L tubes;
- * narrow D2Q9 members cut into rows), by the selected variant (rlb_tune picks
- * the fastest). The variants give identical results, bit for bit. No
+ * Single-member lattices run one fused kernel launch per step or per two
+ * steps (D2Q9: or rounds of H steps on tiles held in LDS); batches (and small
+ * single lattices) run all nsteps inside one persistent launch, one launch per
+ * step over all members, or rounds of H steps on segments held in LDS (1 x 1 x
+ * L tubes; narrow D2Q9 members cut into rows), by the selected variant (a rule
+ * on the sizes picks the first, rlb_tune the fastest). The variants give
+ * identical results, bit for bit. No
  * validation per step: cells that
  * become inadmissible (E <= 0 or |M| >= E) keep their populations uncollided
  * and are counted; the count is reported by rlb_moments/rlb_diagnostics. */

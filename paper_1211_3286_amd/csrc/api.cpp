@@ -45,6 +45,8 @@ struct Layout {
   size_t off_stage = 0, off_segs = 0, off_flags = 0, off_tape = 0, total = 0;
   int max_parts = 0;
   int export_parts = 0;  // blocks of the field export (its own partials region)
+  int blocks[rlb::kNumCells] = {};  // persistent path: blocks of a k_*_cells launch
+  int64_t max_member = 0;           // cells of the largest member
   int64_t max_segs = 0;  // persistent path: one segment per z-plane (D2Q9: per row) at most
   rlb::TapeLayout tape;
 };
@@ -181,6 +183,13 @@ rlb_status make_layout(const rlb_params* m, int32_t n, const rlb_options* opt, L
     // rounds: segments of whole rows (at most ny per member)
     for (int i = 0; i < n; ++i) L.max_segs += d2 ? m[i].ny : m[i].nz;
     parts = std::max<int64_t>(parts, L.max_segs);
+    for (int i = 0; i < n; ++i) {
+      const int64_t c = (int64_t)m[i].nx * m[i].ny * m[i].nz;
+      L.blocks[0] += (int)((c + 63) / 64);
+      L.blocks[1] += (int)((c + 255) / 256);
+      L.max_member = std::max(L.max_member, c);
+    }
+    parts = std::max<int64_t>(parts, L.blocks[0]);
   }
   L.max_parts = std::max(parts, 1);
   size_t o = 0;
@@ -280,11 +289,7 @@ struct rlb_sim {
   int64_t steps = 0;
   int64_t diag_step = -1;
   int diag_parts = 0;
-  // persistent kernels and their graph
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
-  hipGraphNode_t gnode = nullptr;
-  const void* graph_func = nullptr;
+  // persistent kernels
   rlb::MemberLaunch margs{};
   rlb::SegLaunch sargs{};
   rlb::Segment* d_segs = nullptr;
@@ -293,8 +298,7 @@ struct rlb_sim {
   unsigned long long epoch = 0;  // steps every segment flag holds
   int seg_built = -1;             // variant the device segment table describes (segments:
                                   // sv; tube rounds: 1000 + tv; strip rounds: 2000 + sv)
-  hipGraph_t tgraph = nullptr;    // chain of tube (or strip) rounds of the last rlb_step
-  hipGraphExec_t tgexec = nullptr;
+  bool seg_whole = false;         // tube or strip segments: every member is one, whole
   bool all_tubes = false;
   int nseg = 0;
   int num_cu = 0;
@@ -425,15 +429,54 @@ bool is_segment_variant(const rlb_sim* h, int v) {
          v < rlb::num_member_variants() + rlb::num_segment_variants();
 }
 
+// Default of the persistent path. us a step, the choice against the one-block
+// member kernel (512 threads), which keeps members of up to 1024 cells (one or
+// two passes of its block):
+//   1 x 1 x L tubes: rounds of 16 steps; L = 100 FP32 1.9 against 2.9, 800 2.4
+//     and 7.1, 64 ragged ones up to 3200 4.0 and 30 (FP64 1.8 and 2.8, 2.3 and
+//     9.3, 5.0 and 32);
+//   narrow D2Q9 members: strip rounds of 8 steps, if windows of 256 cells leave
+//     an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
+//   the rest: one launch per step; 16^3 FP32 4.1 and 29, 24^3 5.1 and 115, 120^2
+//     D2Q9 3.3 and 41; 64-thread blocks until they fill the chip.
+constexpr int64_t kMemberCells = 1024, kStripCells = 256;
+constexpr int kSmallBlocks = 4096;
+
+int cells_base(const rlb_sim* h);
+
+int default_persistent(const rlb_sim* h) {
+  if (h->all_tubes) return rlb::num_member_variants() + rlb::num_segment_variants() + 1;
+  if (h->d2 && h->L.max_member > kStripCells) {
+    const int v = 3;
+    const rlb::TubeVariant t = rlb::d2q9_strip_variant(v);
+    const int rows = 2 * t.halo * (h->corr ? 2 : 1) + 1;
+    bool fits = true;
+    for (const rlb_params& p : h->params) fits = fits && (int64_t)p.nx * rows <= t.nt;
+    if (fits) return rlb::d2q9_num_member_variants() + v;
+  }
+  if (h->L.max_member <= kMemberCells) return 1;
+  return cells_base(h) + (h->L.blocks[0] <= kSmallBlocks ? 0 : 1);
+}
+
+// First of the one-launch-per-step variants, which follow the others.
+int cells_base(const rlb_sim* h) {
+  return h->d2 ? rlb::d2q9_num_member_variants() + rlb::d2q9_num_strip_variants()
+               : rlb::num_member_variants() + rlb::num_segment_variants() +
+                     rlb::num_tube_variants();
+}
+
+bool is_cells_variant(const rlb_sim* h, int v) { return !h->lattice && v >= cells_base(h); }
+
 bool is_tube_variant(const rlb_sim* h, int v) {
-  return !h->lattice && !h->d2 &&
+  return !h->lattice && !h->d2 && !is_cells_variant(h, v) &&
          v >= rlb::num_member_variants() + rlb::num_segment_variants();
 }
 
 int tube_index(int v) { return v - rlb::num_member_variants() - rlb::num_segment_variants(); }
 
 bool is_strip_variant(const rlb_sim* h, int v) {
-  return !h->lattice && h->d2 && v >= rlb::d2q9_num_member_variants();
+  return !h->lattice && h->d2 && !is_cells_variant(h, v) &&
+         v >= rlb::d2q9_num_member_variants();
 }
 
 int strip_index(int v) { return v - rlb::d2q9_num_member_variants(); }
@@ -479,6 +522,7 @@ rlb_status build_tube_segments(rlb_sim* h, int tv) {
                          hipMemcpyHostToDevice, h->stream));
   RLB_HIP(hipStreamSynchronize(h->stream));
   h->nseg = (int)segs.size();
+  h->seg_whole = h->nseg == h->n_members;  // a cut member has two or more
   h->seg_built = 1000 + tv;
   return RLB_OK;
 }
@@ -530,13 +574,18 @@ rlb_status build_strip_segments(rlb_sim* h, int sv) {
                          hipMemcpyHostToDevice, h->stream));
   RLB_HIP(hipStreamSynchronize(h->stream));
   h->nseg = (int)segs.size();
+  h->seg_whole = h->nseg == h->n_members;  // a cut member has two or more
   h->seg_built = 2000 + sv;
   return RLB_OK;
 }
 
-// Tube rounds: ceil(n / H) launches chained in a HIP graph, each round
-// reading one buffer and writing the other (pingpong) or always A -> B
-// (trials). *flip tells whether the state changed buffers.
+// Tube rounds: ceil(n / H) launches (one when every member fits its block
+// whole), each reading one buffer and writing the other (pingpong) or always
+// A -> B (trials). *flip tells whether the state changed buffers. The rounds
+// are launched one by one: a round runs for 10 us and more, which covers the
+// launch of the next, while a graph of them is built and instantiated anew for
+// every step count (1 x 1 x 800 FP64, 400 steps: 762 us,
+// and 924 as a graph).
 // (The D2Q9 strip rounds take the same path with their own segments and
 // kernel.)
 rlb_status launch_tubes(rlb_sim* h, int variant, int nsteps, int pingpong, void* a, void* b,
@@ -562,44 +611,25 @@ rlb_status launch_tubes(rlb_sim* h, int variant, int nsteps, int pingpong, void*
     v = rlb::tube_variant(tv);
     RLB_HIP(rlb::tube_kernel(h->precision, tv, h->ext, &func, &block));
   }
-  const int rounds = (nsteps + v.halo - 1) / v.halo;
-  if (h->tgexec) {  // the previous chain may still run: let it finish first
-    RLB_HIP(hipStreamSynchronize(h->stream));
-    (void)hipGraphExecDestroy(h->tgexec);
-    (void)hipGraphDestroy(h->tgraph);
-    h->tgexec = nullptr;
-    h->tgraph = nullptr;
-  }
-  RLB_HIP(hipGraphCreate(&h->tgraph, 0));
-  hipGraphNode_t prev = nullptr;
+  const int per = h->seg_whole ? nsteps : v.halo;
+  const int rounds = (nsteps + per - 1) / per;
+  rlb::TubeRound arg{};
+  arg.descs = h->d_descs;
+  arg.segs = (const rlb::TubeSeg*)h->d_segs;
+  arg.cs = h->L.cs;
+  arg.diag_every = diag_every;
+  arg.last_step = step0 + nsteps;
+  arg.partials = h->d_partials;
+  arg.bad = h->d_bad;
   for (int r = 0; r < rounds; ++r) {
-    rlb::TubeRound arg{};
     const bool odd = pingpong && (r & 1);
-    arg.descs = h->d_descs;
-    arg.segs = (const rlb::TubeSeg*)h->d_segs;
     arg.src = odd ? b : a;
     arg.dst = odd ? a : b;
-    arg.cs = h->L.cs;
-    arg.nsteps = std::min(v.halo, nsteps - r * v.halo);
-    arg.diag_every = diag_every;
-    arg.step0 = step0 + (int64_t)r * v.halo;
-    arg.last_step = step0 + nsteps;
-    arg.partials = h->d_partials;
-    arg.bad = h->d_bad;
+    arg.nsteps = std::min(per, nsteps - r * per);
+    arg.step0 = step0 + (int64_t)r * per;
     void* args[] = {&arg};
-    hipKernelNodeParams kp{};
-    kp.func = const_cast<void*>(func);
-    kp.gridDim = dim3(h->nseg, 1, 1);
-    kp.blockDim = block;
-    kp.sharedMemBytes = 0;
-    kp.kernelParams = args;
-    kp.extra = nullptr;
-    hipGraphNode_t node;
-    RLB_HIP(hipGraphAddKernelNode(&node, h->tgraph, prev ? &prev : nullptr, prev ? 1 : 0, &kp));
-    prev = node;
+    RLB_HIP(hipLaunchKernel(func, dim3(h->nseg, 1, 1), block, args, 0, h->stream));
   }
-  RLB_HIP(hipGraphInstantiate(&h->tgexec, h->tgraph, nullptr, nullptr, 0));
-  RLB_HIP(hipGraphLaunch(h->tgexec, h->stream));
   *flip = pingpong && (rounds & 1);
   return RLB_OK;
 }
@@ -650,13 +680,30 @@ rlb_status segments_fit(rlb_sim* h, int sv, const void* func, int nt) {
   return RLB_OK;
 }
 
-// Persistent kernels run from a one-node HIP graph (built on first use, and
-// again when the kernel changes; later calls only update the arguments).
+// The persistent path: nsteps steps by the variant's kernels.
 rlb_status launch_persistent(rlb_sim* h, int variant, int nsteps, int pingpong, void* a, void* b,
                              int diag_every, int64_t step0, bool* flip) {
   if (is_tube_variant(h, variant) || is_strip_variant(h, variant))
     return launch_tubes(h, variant, nsteps, pingpong, a, b, diag_every, step0, flip);
   *flip = pingpong && (nsteps & 1);
+  if (is_cells_variant(h, variant)) {
+    const int cv = variant - cells_base(h);
+    rlb::MemberLaunch m{};
+    m.descs = h->d_descs;
+    m.cs = h->L.cs;
+    m.partials = h->d_partials;
+    m.bad = h->d_bad;
+    for (int t = 0; t < nsteps; ++t) {
+      const bool odd = pingpong && (t & 1);
+      m.bufA = odd ? b : a;
+      m.bufB = odd ? a : b;
+      const bool diag =
+          diag_every > 0 && ((step0 + t + 1) % diag_every == 0 || t == nsteps - 1);
+      RLB_HIP(rlb::launch_step_cells(h->precision, h->d2, cv, h->corr, h->ext, diag, m,
+                                     h->n_members, h->L.blocks[cv], h->stream));
+    }
+    return RLB_OK;
+  }
   const void* func;
   dim3 block, grid;
   void* args[1];
@@ -703,29 +750,7 @@ rlb_status launch_persistent(rlb_sim* h, int variant, int nsteps, int pingpong, 
     args[0] = &h->margs;
     grid = dim3(h->n_members, 1, 1);
   }
-  hipKernelNodeParams kp{};
-  kp.func = const_cast<void*>(func);
-  kp.gridDim = grid;
-  kp.blockDim = block;
-  kp.sharedMemBytes = 0;
-  kp.kernelParams = args;
-  kp.extra = nullptr;
-  if (h->gexec && h->graph_func != func) {
-    RLB_HIP(hipStreamSynchronize(h->stream));
-    (void)hipGraphExecDestroy(h->gexec);
-    (void)hipGraphDestroy(h->graph);
-    h->gexec = nullptr;
-    h->graph = nullptr;
-  }
-  if (!h->gexec) {
-    RLB_HIP(hipGraphCreate(&h->graph, 0));
-    RLB_HIP(hipGraphAddKernelNode(&h->gnode, h->graph, nullptr, 0, &kp));
-    RLB_HIP(hipGraphInstantiate(&h->gexec, h->graph, nullptr, nullptr, 0));
-    h->graph_func = func;
-  } else {
-    RLB_HIP(hipGraphExecKernelNodeSetParams(h->gexec, h->gnode, &kp));
-  }
-  RLB_HIP(hipGraphLaunch(h->gexec, h->stream));
+  RLB_HIP(hipLaunchKernel(func, grid, block, args, 0, h->stream));
   if (is_segment_variant(h, variant)) h->epoch += (unsigned long long)nsteps;
   return RLB_OK;
 }
@@ -783,7 +808,9 @@ rlb_status advance(rlb_sim* h, int32_t n) {
     h->diag_step = h->steps + n;
     const bool by_seg = is_segment_variant(h, h->variant) || is_tube_variant(h, h->variant) ||
                         is_strip_variant(h, h->variant);
-    h->diag_parts = by_seg ? h->nseg : h->n_members;
+    h->diag_parts = is_cells_variant(h, h->variant) ? h->L.blocks[h->variant - cells_base(h)]
+                    : by_seg                        ? h->nseg
+                                                    : h->n_members;
   }
   h->steps += n;
   if (flip) h->cur = 1 - h->cur;
@@ -835,6 +862,7 @@ bool host_fields_ok(const double* n0, const double* eps0, const double* u0, int6
 namespace {
 
 const char* kernel_name_of(const rlb_sim* h, int v) {
+  if (is_cells_variant(h, v)) return rlb::cells_kernel_name(h->precision, h->d2, v - cells_base(h));
   if (h->d2) {
     if (is_tile_variant(h, v)) return rlb::d2q9_tile_kernel_name(h->precision, tile_index(v));
     if (h->lattice) return rlb::d2q9_lattice_kernel_name(h->precision, v);
@@ -943,12 +971,11 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   h->corr = opt->correction != 0;
   h->q = nvel(opt->lattice);
   h->lattice = lattice_path(n_members, L.ncells);
-  // defaults: the lattice path's 256 x 1 block; the persistent path's 512
-  // threads with one cell each
-  h->variant = h->d2 ? (h->lattice ? 2 : 1) : (h->lattice ? 3 : 1);
   h->all_tubes = !h->d2;
   for (int i = 0; i < n_members; ++i)
     if (members[i].nx != 1 || members[i].ny != 1) h->all_tubes = false;
+  // default of the lattice path: the 256 x 1 block
+  h->variant = h->lattice ? (h->d2 ? 2 : 3) : default_persistent(h);
 
   auto fail = [&](rlb_status s) {
     delete h;
@@ -957,15 +984,20 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   // member descriptors (refs are filled on the device)
   h->descs.resize(n_members);
   int64_t off = 0;
+  int first64 = 0, first256 = 0;
   for (int i = 0; i < n_members; ++i) {
     const rlb_params& p = members[i];
     MemberDesc& d = h->descs[i];
     std::memset(&d, 0, sizeof(d));
     d.offset = off;
+    d.first64 = first64;
+    d.first256 = first256;
     d.nx = p.nx;
     d.ny = p.ny;
     d.nz = p.nz;
     d.ncells = p.nx * p.ny * p.nz;
+    first64 += (int)(((int64_t)d.ncells + 63) / 64);
+    first256 += (int)(((int64_t)d.ncells + 255) / 256);
     d.bcx = p.bc[0];
     d.bcy = p.bc[1];
     d.bcz = p.bc[2];
@@ -1218,11 +1250,10 @@ rlb_status rlb_num_variants(rlb_handle h, int32_t* count) {
   if (!h || !count) return RLB_E_ARG;
   if (h->d2)
     *count = h->lattice ? rlb::d2q9_num_lattice_variants() + rlb::d2q9_num_tile_variants()
-                        : rlb::d2q9_num_member_variants() + rlb::d2q9_num_strip_variants();
+                        : cells_base(h) + rlb::kNumCells;
   else
     *count = h->lattice ? rlb::num_lattice_variants() + rlb::num_march_variants()
-                        : rlb::num_member_variants() + rlb::num_segment_variants() +
-                              rlb::num_tube_variants();
+                        : cells_base(h) + rlb::kNumCells;
   return RLB_OK;
 }
 
@@ -1333,10 +1364,6 @@ void rlb_free(rlb_handle h) {
   {
     DeviceGuard g(h->device);
     (void)hipStreamSynchronize(h->stream);
-    if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
-    if (h->graph) (void)hipGraphDestroy(h->graph);
-    if (h->tgexec) (void)hipGraphExecDestroy(h->tgexec);
-    if (h->tgraph) (void)hipGraphDestroy(h->tgraph);
     rlb::tape_release(h->tape);
   }
   delete h;

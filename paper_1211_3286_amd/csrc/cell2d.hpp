@@ -412,5 +412,19 @@ __device__ __forceinline__ void pull_offsets(int x, int y, int nx, int ny, int b
   self = off[0];
 }
 
+// Fields of the y - 1 and y + 1 neighbours of cell (x, y) for the correction
+// term (their pulled g, recovered), neighbours picked by the y-streaming rule.
+template <typename T>
+__device__ __forceinline__ void c7_neighbours(const T* __restrict__ src, int64_t cs, int x,
+                                              int y, int nx, int ny, int bcx, int bcy,
+                                              uint32_t base, const Ref& ref,
+                                              C7Fields& fm, C7Fields& fp) {
+  uint32_t off[9], self;
+  pull_offsets(x, nbr(y, -1, ny, bcy), nx, ny, bcx, bcy, base, sizeof(T), off, self);
+  fm = c7_fields_at(src, cs, off, ref);
+  pull_offsets(x, nbr(y, 1, ny, bcy), nx, ny, bcx, bcy, base, sizeof(T), off, self);
+  fp = c7_fields_at(src, cs, off, ref);
+}
+
 }  // namespace d2q9
 }  // namespace rlb

@@ -15,7 +15,7 @@ struct MemberDesc {
   int32_t nx, ny, nz;
   int32_t ncells;  // nx*ny*nz (members of the persistent path are < 2^31 cells)
   int32_t bcx, bcy, bcz;
-  int32_t pad;
+  int32_t first64, first256;  // first block of the member in k_*_cells launches
   Rates rt;
   Ref ref;
   Ext ext;  // eta/s relaxation times and equation of state (EXT kernels, init, export)
@@ -143,6 +143,13 @@ struct MemberLaunch {
   unsigned long long* bad;
 };
 hipError_t member_kernel(int precision, int variant, bool ext, const void** func, dim3* block);
+
+// One launch per step over all members, one cell per thread (cells.hip);
+// variants: 64 or 256 threads a block. Reads a.bufA, writes a.bufB.
+constexpr int kNumCells = 2;
+hipError_t launch_step_cells(int precision, bool d2, int variant, bool corr, bool ext, bool diag,
+                             const MemberLaunch& a, int n_members, int nblocks, hipStream_t s);
+const char* cells_kernel_name(int precision, bool d2, int variant);
 
 // Segmented persistent step: every member is cut into segments of whole
 // z-planes, one block per segment; a segment waits (per step) for the two

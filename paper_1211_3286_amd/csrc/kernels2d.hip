@@ -16,20 +16,6 @@ namespace rlb {
 
 namespace {
 
-// Fields of the y - 1 and y + 1 neighbours of cell (x, y) for the correction
-// term (their pulled g, recovered), neighbours picked by the y-streaming rule.
-template <typename T>
-__device__ __forceinline__ void c7_neighbours(const T* __restrict__ src, int64_t cs, int x,
-                                              int y, int nx, int ny, int bcx, int bcy,
-                                              uint32_t base, const Ref& ref,
-                                              d2q9::C7Fields& fm, d2q9::C7Fields& fp) {
-  uint32_t off[9], self;
-  d2q9::pull_offsets(x, nbr(y, -1, ny, bcy), nx, ny, bcx, bcy, base, sizeof(T), off, self);
-  fm = d2q9::c7_fields_at(src, cs, off, ref);
-  d2q9::pull_offsets(x, nbr(y, 1, ny, bcy), nx, ny, bcx, bcy, base, sizeof(T), off, self);
-  fp = d2q9::c7_fields_at(src, cs, off, ref);
-}
-
 // -------------------------------------------------------------------------
 // Fused step on one nx x ny lattice: grid (ceil(nx/BX), ceil(ny/(BY*CY))),
 // block (BX, BY); each thread updates CY cells along y. Tiles are taken in
@@ -60,7 +46,7 @@ __global__ __launch_bounds__(BX* BY) void k_d2q9_lattice(const T* __restrict__ s
     if (x < geo.nx && y < geo.ny) {
       d2q9::C7Fields fm, fp;
       if constexpr (CORR)
-        c7_neighbours(src, geo.cs, x, y, geo.nx, geo.ny, geo.bcx, geo.bcy, 0u, geo.ref, fm,
+        d2q9::c7_neighbours(src, geo.cs, x, y, geo.nx, geo.ny, geo.bcx, geo.bcy, 0u, geo.ref, fm,
                       fp);
       uint32_t off[9], self;
       d2q9::pull_offsets(x, y, geo.nx, geo.ny, geo.bcx, geo.bcy, 0u, esz, off, self);
@@ -231,7 +217,7 @@ __global__ __launch_bounds__(NT) void k_d2q9_members(MemberLaunch a) {
           const int x = c - y * d.nx;
           d2q9::C7Fields fm, fp;
           if constexpr (CORR)
-            c7_neighbours(src, a.cs, x, y, d.nx, d.ny, d.bcx, d.bcy, base, d.ref, fm, fp);
+            d2q9::c7_neighbours(src, a.cs, x, y, d.nx, d.ny, d.bcx, d.bcy, base, d.ref, fm, fp);
           uint32_t off[9], self;
           d2q9::pull_offsets(x, y, d.nx, d.ny, d.bcx, d.bcy, base, esz, off, self);
           T f[9], g[9];
