@@ -154,7 +154,7 @@ def options(precision: int = FP32, ckpt_every: int = 0, tape_steps: int = 0,
 
 def workspace_size(members: Sequence, opt: COptions) -> int:
     n = ctypes.c_size_t(0)
-    arr = cparams(members)
+    arr = members if isinstance(members, ctypes.Array) else cparams(members)
     _check(lib().rlb_workspace_size(arr, len(members), ctypes.byref(opt), ctypes.byref(n)),
            "rlb_workspace_size")
     return int(n.value)
@@ -191,7 +191,7 @@ class Simulation:
         self.opt = options(precision, ckpt_every, tape_steps, diag_every, self.lattice,
                            correction)
         self._arr = cparams(self.members)
-        self.ws_bytes = workspace_size(self.members, self.opt)
+        self.ws_bytes = workspace_size(self._arr, self.opt)
         self.workspace = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=dev)
         base = _dptr(self.workspace)
         self._ws_ptr = (base + 255) // 256 * 256

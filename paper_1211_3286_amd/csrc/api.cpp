@@ -47,6 +47,7 @@ struct Layout {
   int export_parts = 0;  // blocks of the field export (its own partials region)
   int blocks[rlb::kNumCells] = {};  // persistent path: blocks of a k_*_cells launch
   int64_t max_member = 0;           // cells of the largest member
+  int ref_blocks = 0;               // blocks per member of the input pass
   int64_t max_segs = 0;  // persistent path: one segment per z-plane (D2Q9: per row) at most
   rlb::TapeLayout tape;
 };
@@ -177,7 +178,10 @@ rlb_status make_layout(const rlb_params* m, int32_t n, const rlb_options* opt, L
       for (int v = 0; v < rlb::num_lattice_variants(); ++v)
         parts = std::max(parts, rlb::lattice_partials(v, g));
   }
-  parts = std::max<int64_t>(parts, (int64_t)n * rlb::kRefBlocks);
+  for (int i = 0; i < n; ++i)
+    L.max_member = std::max(L.max_member, (int64_t)m[i].nx * m[i].ny * m[i].nz);
+  L.ref_blocks = rlb::ref_blocks(L.max_member);
+  parts = std::max<int64_t>(parts, (int64_t)n * L.ref_blocks);
   if (!lattice_path(n, L.ncells)) {  // segment tables of the persistent path
     // D3Q19: segments of whole z-planes (at most nz per member); D2Q9 strip
     // rounds: segments of whole rows (at most ny per member)
@@ -187,7 +191,6 @@ rlb_status make_layout(const rlb_params* m, int32_t n, const rlb_options* opt, L
       const int64_t c = (int64_t)m[i].nx * m[i].ny * m[i].nz;
       L.blocks[0] += (int)((c + 63) / 64);
       L.blocks[1] += (int)((c + 255) / 256);
-      L.max_member = std::max(L.max_member, c);
     }
     parts = std::max<int64_t>(parts, L.blocks[0]);
   }
@@ -203,7 +206,7 @@ rlb_status make_layout(const rlb_params* m, int32_t n, const rlb_options* opt, L
   o = align_up(o + sizeof(double) * 5 * (size_t)L.max_parts);
   // The field export keeps its partial sums apart, so that rlb_moments never
   // overwrites the diagnostics partials of the latest step.
-  L.export_parts = (int)std::min<int64_t>(std::max<int64_t>((L.ncells + 255) / 256, 1), 65536);
+  L.export_parts = rlb::export_blocks(L.ncells);
   L.off_xparts = o;
   o = align_up(o + sizeof(double) * 5 * (size_t)L.export_parts);
   size_t buf = 2 * (size_t)nvel(opt->lattice) * (size_t)L.cs * L.esz;
@@ -267,10 +270,9 @@ struct rlb_sim {
   Layout L;
   char* ws = nullptr;
   MemberDesc* d_descs = nullptr;
-  double* d_small = nullptr;  // [0..4] sums out, [8..] scratch
+  double* d_small = nullptr;  // the host's view, then the gradient's sums
   unsigned long long* d_bad = nullptr;
-  unsigned long long* d_count = nullptr;
-  unsigned long long* d_bad_total = nullptr;  // the slots' total for the host
+  rlb::HostView* d_view = nullptr;  // what the host reads back, in one copy
   unsigned long long* d_bad_save = nullptr;
   double* d_partials = nullptr;
   double* d_xparts = nullptr;  // export partials (rlb_moments)
@@ -294,7 +296,6 @@ struct rlb_sim {
   rlb::SegLaunch sargs{};
   rlb::Segment* d_segs = nullptr;
   unsigned long long* d_flags = nullptr;
-  int* d_error = nullptr;
   unsigned long long epoch = 0;  // steps every segment flag holds
   int seg_built = -1;             // variant the device segment table describes (segments:
                                   // sv; tube rounds: 1000 + tv; strip rounds: 2000 + sv)
@@ -320,17 +321,12 @@ rlb_status dev_err(hipError_t e) { return e == hipSuccess ? RLB_OK : RLB_E_DEVIC
 void* state_buf(rlb_sim* h) { return h->buf[h->cur]; }
 void* spare_buf(rlb_sim* h) { return h->buf[1 - h->cur]; }
 
-// Total of the inadmissible-cell slots (count_bad), summed on the device and
-// copied back; total() is valid once the stream has reached the copy.
-struct BadSlots {
-  unsigned long long v = 0;
-  hipError_t fetch(const rlb_sim* h) {
-    hipError_t e = rlb::launch_sum_bad(h->d_bad, h->d_bad_total, h->stream);
-    if (e != hipSuccess) return e;
-    return hipMemcpyAsync(&v, h->d_bad_total, sizeof(v), hipMemcpyDeviceToHost, h->stream);
-  }
-  unsigned long long total() const { return v; }
-};
+// The host's view, once the stream has reached it.
+rlb_status read_view(rlb_sim* h, rlb::HostView* v) {
+  RLB_HIP(hipMemcpyAsync(v, h->d_view, sizeof(*v), hipMemcpyDeviceToHost, h->stream));
+  RLB_HIP(hipStreamSynchronize(h->stream));
+  return RLB_OK;
+}
 
 rlb_status launch_lattice_step(rlb_sim* h, int variant, bool diag, const void* src, void* dst) {
   if (h->d2)
@@ -726,7 +722,7 @@ rlb_status launch_persistent(rlb_sim* h, int variant, int nsteps, int pingpong, 
     g.step0 = step0;
     g.epoch = h->epoch;
     g.flags = h->d_flags;
-    g.error = h->d_error;
+    g.error = (int*)&h->d_view->error;
     g.partials = h->d_partials;
     g.bad = h->d_bad;
     args[0] = &h->sargs;
@@ -881,10 +877,9 @@ const char* kernel_name_of(const rlb_sim* h, int v) {
 // A persistent segment launch whose neighbour wait timed out leaves a sticky
 // error word; it is reported at the next synchronising call.
 rlb_status persistent_error(rlb_sim* h) {
-  int e = 0;
-  RLB_HIP(hipMemcpyAsync(&e, h->d_error, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-  RLB_HIP(hipStreamSynchronize(h->stream));
-  return e ? RLB_E_DEVICE : RLB_OK;
+  rlb::HostView v;
+  rlb_status st = read_view(h, &v);
+  return st != RLB_OK ? st : v.error ? RLB_E_DEVICE : RLB_OK;
 }
 
 }  // namespace
@@ -955,8 +950,7 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   h->ws = (char*)workspace;
   h->d_descs = (MemberDesc*)(h->ws + L.off_descs);
   h->d_small = (double*)(h->ws + L.off_small);
-  h->d_count = (unsigned long long*)(h->d_small + 16);
-  h->d_bad_total = (unsigned long long*)(h->d_small + 20);
+  h->d_view = (rlb::HostView*)h->d_small;
   h->d_bad = (unsigned long long*)(h->ws + L.off_bad);
   h->d_bad_save = h->d_bad + rlb::kBadBytes / sizeof(unsigned long long);
   h->d_partials = (double*)(h->ws + L.off_partials);
@@ -966,7 +960,6 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   h->d_stage = (double*)(h->ws + L.off_stage);
   h->d_segs = (rlb::Segment*)(h->ws + L.off_segs);
   h->d_flags = (unsigned long long*)(h->ws + L.off_flags);
-  h->d_error = (int*)(h->d_small + 24);
   h->d2 = planar;
   h->corr = opt->correction != 0;
   h->q = nvel(opt->lattice);
@@ -1021,35 +1014,26 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     if (p.eta_over_s > 0.0 || d.ext.general_eos) h->ext = true;
     off += d.ncells;
   }
-  const double *dn, *de, *du;
-  if (hipMemsetAsync(h->d_small, 0, 1024, h->stream) != hipSuccess ||
-      hipMemsetAsync(h->d_bad, 0, rlb::kBadBytes, h->stream) != hipSuccess)
-    return fail(RLB_E_DEVICE);
-  if (L.max_segs > 0 &&
-      hipMemsetAsync(h->d_flags, 0, sizeof(unsigned long long) * L.max_segs, h->stream) !=
-          hipSuccess)
-    return fail(RLB_E_DEVICE);
   if (hipDeviceGetAttribute(&h->num_cu, hipDeviceAttributeMultiprocessorCount, h->device) !=
       hipSuccess)
     return fail(RLB_E_DEVICE);
-  if (copy_fields_in(h, n0, eps0, u0, fields_on_device, &dn, &de, &du) != RLB_OK)
+  // The whole start is enqueued and its one answer read back at the end: the
+  // refused cells and the reference the lattice kernels take as an argument.
+  const double *dn, *de, *du;
+  static_assert(sizeof(rlb::HostView) <= 256, "the small area holds the view and more");
+  if (rlb::launch_begin((unsigned long long*)h->d_small,
+                        (L.off_bad + rlb::kBadBytes - L.off_small) / sizeof(unsigned long long),
+                        h->d_flags, (size_t)L.max_segs, n_members == 1 ? &h->descs[0] : nullptr,
+                        h->d_descs, h->stream) != hipSuccess)
     return fail(RLB_E_DEVICE);
-  if (hipMemcpyAsync(h->d_descs, h->descs.data(), sizeof(MemberDesc) * n_members,
+  if (n_members > 1 &&
+      hipMemcpyAsync(h->d_descs, h->descs.data(), sizeof(MemberDesc) * n_members,
                      hipMemcpyHostToDevice, h->stream) != hipSuccess)
     return fail(RLB_E_DEVICE);
-  if (fields_on_device) {
-    if (rlb::launch_validate(dn, de, du, L.ncells, planar ? 1 : 0, h->d_descs, n_members,
-                             h->d_count, h->stream) != hipSuccess)
-      return fail(RLB_E_DEVICE);
-    unsigned long long cnt = 0;
-    if (hipMemcpyAsync(&cnt, h->d_count, sizeof(cnt), hipMemcpyDeviceToHost, h->stream) !=
-            hipSuccess ||
-        hipStreamSynchronize(h->stream) != hipSuccess)
-      return fail(RLB_E_DEVICE);
-    if (cnt) return fail(RLB_E_UNPHYSICAL);
-  }
-  if (rlb::launch_member_refs(h->d_descs, n_members, dn, de, du, L.ncells, h->d_partials,
-                              h->stream) != hipSuccess)
+  if (copy_fields_in(h, n0, eps0, u0, fields_on_device, &dn, &de, &du) != RLB_OK)
+    return fail(RLB_E_DEVICE);
+  if (rlb::launch_prepare(h->d_descs, n_members, L.ref_blocks, dn, de, du, L.ncells,
+                          planar ? 1 : 0, h->d_partials, h->d_view, h->stream) != hipSuccess)
     return fail(RLB_E_DEVICE);
   const hipError_t ie =
       planar ? rlb::d2q9_launch_init(h->precision, h->buf[0], L.cs, h->d_descs, n_members, dn,
@@ -1057,10 +1041,10 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
              : rlb::launch_init(h->precision, h->buf[0], L.lay, h->d_descs, n_members, dn, de, du,
                                 L.ncells, h->stream);
   if (ie != hipSuccess) return fail(RLB_E_DEVICE);
-  if (hipMemcpyAsync(h->descs.data(), h->d_descs, sizeof(MemberDesc) * n_members,
-                     hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
-      hipStreamSynchronize(h->stream) != hipSuccess)
-    return fail(RLB_E_DEVICE);
+  rlb::HostView view;
+  if (read_view(h, &view) != RLB_OK) return fail(RLB_E_DEVICE);
+  if (view.refused) return fail(RLB_E_UNPHYSICAL);
+  h->descs[0].ref = view.ref0;
   if (h->lattice) {
     const MemberDesc& d = h->descs[0];
     h->geom.nx = d.nx;
@@ -1144,15 +1128,11 @@ rlb_status rlb_moments(rlb_handle h, double* n, double* eps, double* P, double* 
   if (h->d2)
     RLB_HIP(rlb::d2q9_launch_export(h->precision, state_buf(h), h->L.cs, h->d_descs,
                                     h->n_members, nc, dn, de, dP, dg, du, h->d_xparts, nparts,
-                                    h->stream));
+                                    nullptr, h->stream));
   else
     RLB_HIP(rlb::launch_export(h->precision, state_buf(h), h->L.lay, h->d_descs, h->n_members,
-                               nc, dn, de, dP, dg, du, h->d_xparts, nparts, h->stream));
-  RLB_HIP(rlb::launch_reduce(h->d_xparts, nparts, h->d_small, h->stream));
-  double hs[5];
-  BadSlots slots;
-  RLB_HIP(hipMemcpyAsync(hs, h->d_small, sizeof(hs), hipMemcpyDeviceToHost, h->stream));
-  RLB_HIP(slots.fetch(h));
+                               nc, dn, de, dP, dg, du, h->d_xparts, nparts, nullptr, h->stream));
+  RLB_HIP(rlb::launch_finish(h->d_xparts, nparts, h->d_bad, h->d_view, h->stream));
   if (!out_on_device) {
     if (n) RLB_HIP(hipMemcpyAsync(n, dn, sizeof(double) * nc, hipMemcpyDeviceToHost, h->stream));
     if (eps)
@@ -1163,12 +1143,13 @@ rlb_status rlb_moments(rlb_handle h, double* n, double* eps, double* P, double* 
     if (u)
       RLB_HIP(hipMemcpyAsync(u, du, sizeof(double) * 3 * nc, hipMemcpyDeviceToHost, h->stream));
   }
-  RLB_HIP(hipStreamSynchronize(h->stream));
-  const unsigned long long bad = slots.total();
-  if (sums) std::memcpy(sums, hs, sizeof(hs));
-  if (n_unphysical) *n_unphysical = (int64_t)bad;
-  if (persistent_error(h) != RLB_OK) return RLB_E_DEVICE;
-  return bad ? RLB_E_UNPHYSICAL : RLB_OK;
+  rlb::HostView view;
+  rlb_status st = read_view(h, &view);
+  if (st != RLB_OK) return st;
+  if (sums) std::memcpy(sums, view.sums, sizeof(view.sums));
+  if (n_unphysical) *n_unphysical = (int64_t)view.bad;
+  if (view.error) return RLB_E_DEVICE;
+  return view.bad ? RLB_E_UNPHYSICAL : RLB_OK;
 }
 
 rlb_status rlb_diagnostics(rlb_handle h, double sums[5], int64_t* step, int64_t* n_unphysical) {
@@ -1176,16 +1157,14 @@ rlb_status rlb_diagnostics(rlb_handle h, double sums[5], int64_t* step, int64_t*
   if (h->diag_step < 0) return RLB_E_STATE;
   DeviceGuard g(h->device);
   if (!g.ok) return RLB_E_DEVICE;
-  RLB_HIP(rlb::launch_reduce(h->d_partials, h->diag_parts, h->d_small, h->stream));
-  double hs[5];
-  BadSlots slots;
-  RLB_HIP(hipMemcpyAsync(hs, h->d_small, sizeof(hs), hipMemcpyDeviceToHost, h->stream));
-  RLB_HIP(slots.fetch(h));
-  RLB_HIP(hipStreamSynchronize(h->stream));
-  if (sums) std::memcpy(sums, hs, sizeof(hs));
+  RLB_HIP(rlb::launch_finish(h->d_partials, h->diag_parts, h->d_bad, h->d_view, h->stream));
+  rlb::HostView view;
+  rlb_status st = read_view(h, &view);
+  if (st != RLB_OK) return st;
+  if (sums) std::memcpy(sums, view.sums, sizeof(view.sums));
   if (step) *step = h->diag_step;
-  if (n_unphysical) *n_unphysical = (int64_t)slots.total();
-  return persistent_error(h);
+  if (n_unphysical) *n_unphysical = (int64_t)view.bad;
+  return view.error ? RLB_E_DEVICE : RLB_OK;
 }
 
 rlb_status rlb_populations(rlb_handle h, double* f, double* g, int32_t out_on_device) {
@@ -1221,7 +1200,6 @@ rlb_status rlb_populations(rlb_handle h, double* f, double* g, int32_t out_on_de
       }
     }
   }
-  RLB_HIP(hipStreamSynchronize(h->stream));
   return persistent_error(h);
 }
 
@@ -1241,7 +1219,7 @@ rlb_status rlb_grad(rlb_handle h, const double* dL_du, const double* dL_deps,
   c.tau_q_tied = !(h->params[0].tau_q > 0.0);
   c.state = state_buf(h);
   c.stage = h->d_stage;
-  c.sums_out = h->d_small;
+  c.sums_out = h->d_small + 32;
   c.stream = h->stream;
   return rlb::tape_grad(h->tape, c, dL_du, dL_deps, dL_dtau, dL_deps0, dL_du0, io_on_device);
 }

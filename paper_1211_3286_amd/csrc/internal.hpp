@@ -92,18 +92,41 @@ __device__ __forceinline__ void count_bad(unsigned long long* bad, int n) {
   atomicAdd(bad + (size_t)kBadStride * (b & (kBadSlots - 1)), (unsigned long long)n);
 }
 
+// What the host reads back of a handle, at the start of its small area (one
+// copy): the lattice sums and the inadmissible-cell total (launch_finish), the
+// error word of the segmented launches, the number of refused input cells and
+// the reference of member 0 (launch_begin, launch_prepare).
+struct HostView {
+  double sums[5];
+  unsigned long long bad;
+  unsigned long long error;
+  unsigned long long refused;
+  Ref ref0;
+};
+
 // precision: 0 = FP64, 1 = FP32 (rlb.h).
-// Partial-sum blocks per member of the reference-state pass; the partials
-// buffer must hold n_members * kRefBlocks * 5 doubles.
+// Blocks per member of the input pass (launch_prepare), whose partials buffer
+// must hold n_members * ref_blocks() * 5 doubles. At most 64, whatever the size:
+// the blocks set the order of the reference's sum, and the reference every
+// rounding of FP32 populations.
 constexpr int kRefBlocks = 64;
-hipError_t launch_member_refs(const MemberDesc* descs, int n_members, const double* n0,
-                              const double* eps0, const double* u0, int64_t ncells,
-                              double* parts, hipStream_t s);
-// planar: also count cells with u_z != 0 (D2Q9 lattices carry no z velocity);
-// cells of members with a general equation of state also need eps > m n.
-hipError_t launch_validate(const double* n0, const double* eps0, const double* u0,
-                           int64_t ncells, int planar, const MemberDesc* descs, int n_members,
-                           unsigned long long* count, hipStream_t s);
+inline int ref_blocks(int64_t max_member) {
+  const int64_t want = (max_member + 255) / 256;
+  return (int)(want < 1 ? 1 : want > kRefBlocks ? kRefBlocks : want);
+}
+// Clears the small area, the inadmissible-cell slots and the segment flags; a
+// single member's descriptor travels as an argument (one = null: the caller
+// copies the descriptors).
+hipError_t launch_begin(unsigned long long* small, size_t n_small, unsigned long long* flags,
+                        size_t n_flags, const MemberDesc* one, MemberDesc* descs, hipStream_t s);
+// One pass over the input fields: counts the cells rlb_init refuses into
+// view->refused, and sets every member's reference state (its mean n gamma and
+// eps/3; view->ref0 that of member 0). planar: also refuse u_z != 0 (D2Q9
+// lattices carry no z velocity); cells of members with a general equation of
+// state also need eps > m n.
+hipError_t launch_prepare(MemberDesc* descs, int n_members, int nblocks, const double* n0,
+                          const double* eps0, const double* u0, int64_t ncells, int planar,
+                          double* parts, HostView* view, hipStream_t s);
 hipError_t launch_init(int precision, void* state, const StateLayout& l, const MemberDesc* descs,
                        int n_members, const double* n0, const double* eps0, const double* u0,
                        int64_t ncells, hipStream_t s);
@@ -217,16 +240,23 @@ hipError_t segment_kernel(int precision, int variant, const void** func, dim3* b
 const char* segment_kernel_name(int precision, int variant);
 hipError_t launch_step_members(int precision, int variant, int n_members, const MemberLaunch& a,
                                hipStream_t s);
+// The fields of the state; nothing is written while *refused is not 0 (null: always).
 hipError_t launch_export(int precision, const void* state, const StateLayout& l,
                          const MemberDesc* descs, int n_members, int64_t ncells, double* n, double* eps, double* P,
-                         double* gamma, double* u, double* partials, int nparts, hipStream_t s);
+                         double* gamma, double* u, double* partials, int nparts, const unsigned long long* refused,
+                         hipStream_t s);
 hipError_t launch_population_planes(int precision, const void* state, const StateLayout& l,
                                     const MemberDesc* descs, int n_members, int64_t ncells,
                                     int p0, int np, double* out, hipStream_t s);
-hipError_t launch_reduce(const double* partials, int nparts, double* out5, hipStream_t s);
-// The total of the inadmissible-cell slots into *out (device).
-hipError_t launch_sum_bad(const unsigned long long* slots, unsigned long long* out,
-                          hipStream_t s);
+// view->sums from nparts partial 5-vectors and view->bad from the slots.
+hipError_t launch_finish(const double* partials, int nparts, const unsigned long long* slots,
+                         HostView* view, hipStream_t s);
+// Blocks of the field export, whose partials one block of launch_finish adds.
+constexpr int64_t kExportBlocks = 2048;
+inline int export_blocks(int64_t ncells) {
+  const int64_t b = (ncells + 255) / 256;
+  return (int)(b < 1 ? 1 : b > kExportBlocks ? kExportBlocks : b);
+}
 const char* lattice_kernel_name(int precision, int variant);
 const char* member_kernel_name(int precision, int variant);
 
@@ -285,7 +315,8 @@ hipError_t d2q9_launch_init(int precision, void* state, int64_t cs, const Member
 hipError_t d2q9_launch_export(int precision, const void* state, int64_t cs,
                               const MemberDesc* descs, int n_members, int64_t ncells, double* n,
                               double* eps, double* P, double* gamma, double* u,
-                              double* partials, int nparts, hipStream_t s);
+                              double* partials, int nparts, const unsigned long long* refused,
+                         hipStream_t s);
 hipError_t d2q9_launch_population_planes(int precision, const void* state, int64_t cs,
                                          const MemberDesc* descs, int n_members, int64_t ncells,
                                          int p0, int np, double* out, hipStream_t s);

@@ -13,6 +13,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device_util.hpp"
 #include "internal.hpp"
 #include "step_lattice.hpp"
@@ -278,56 +280,84 @@ __device__ __forceinline__ int find_member(const MemberDesc* __restrict__ d, int
   return lo;
 }
 
-// Mean n gamma and eps/3 of each member's initial fields (its reference
-// state), in two deterministic passes: kRefBlocks partial sums per member,
-// then one block per member adds them in order.
-__global__ __launch_bounds__(256) void k_member_ref_parts(const MemberDesc* descs,
-                                                          const double* n0, const double* eps0,
-                                                          const double* u0, int64_t ncells,
-                                                          double* parts) {
+__global__ __launch_bounds__(256) void k_begin(unsigned long long* small, size_t n_small,
+                                               unsigned long long* flags, size_t n_flags,
+                                               MemberDesc one, MemberDesc* descs) {
+  const size_t i = blockIdx.x * (size_t)256 + threadIdx.x, step = gridDim.x * (size_t)256;
+  for (size_t k = i; k < n_small; k += step) small[k] = 0ull;
+  for (size_t k = i; k < n_flags; k += step) flags[k] = 0ull;
+  if (descs && i == 0) *descs = one;
+}
+
+// Input pass, grid (blocks, members): a block's share of a member's cells is
+// validated and summed (n gamma and eps, for the member's reference state). A
+// thread adds its cells c, c + 256 kRefBlocks, ... in that order; with kAhead of
+// them loaded at once the 64 blocks stream a large lattice (512^3: 2.7 ms,
+// one cell at a time in two kernels 5.6 ms).
+__global__ __launch_bounds__(256) void k_prepare(const MemberDesc* descs,
+                                                 const double* __restrict__ n0,
+                                                 const double* __restrict__ eps0,
+                                                 const double* __restrict__ u0, int64_t ncells,
+                                                 int planar, double* parts, HostView* view) {
+  constexpr int kAhead = 8;
   const MemberDesc& d = descs[blockIdx.y];
+  const Ext& x = d.ext;
   double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int c = blockIdx.x * 256 + threadIdx.x; c < d.ncells; c += kRefBlocks * 256) {
-    const int64_t i = d.offset + c;
-    const double ux = u0[i], uy = u0[ncells + i], uz = u0[2 * ncells + i];
-    v[0] += n0[i] / sqrt(1.0 - (ux * ux + uy * uy + uz * uz));
-    v[1] += eps0[i];
+  int nb = 0;
+  for (int64_t c0 = blockIdx.x * 256 + threadIdx.x; c0 < d.ncells;
+       c0 += (int64_t)kAhead * kRefBlocks * 256) {
+    double n[kAhead], e[kAhead], ux[kAhead], uy[kAhead], uz[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const int64_t c = c0 + (int64_t)k * kRefBlocks * 256;
+      const int64_t i = d.offset + (c < d.ncells ? c : c0);
+      n[k] = n0[i];
+      e[k] = eps0[i];
+      ux[k] = u0[i];
+      uy[k] = u0[ncells + i];
+      uz[k] = u0[2 * ncells + i];
+    }
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      if (c0 + (int64_t)k * kRefBlocks * 256 >= d.ncells) break;
+      const double uu = ux[k] * ux[k] + uy[k] * uy[k] + uz[k] * uz[k];
+      const bool ok = (e[k] > 0.0) && (n[k] >= 0.0) && (uu < 1.0) && (n[k] < INFINITY) &&
+                      (e[k] < INFINITY) && (!planar || uz[k] == 0.0) &&
+                      (!x.general_eos || e[k] - x.mass * n[k] > 0.0);
+      nb += ok ? 0 : 1;
+      v[0] += n[k] / sqrt(1.0 - uu);
+      v[1] += e[k];
+    }
   }
+  if (nb) atomicAdd(&view->refused, (unsigned long long)nb);
   block_sum5<256>(v, threadIdx.x);
   if (threadIdx.x == 0) {
-    const int64_t b = (int64_t)blockIdx.y * kRefBlocks + blockIdx.x;
+    const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     for (int k = 0; k < 5; ++k) parts[b * 5 + k] = v[k];
   }
 }
 
-__global__ __launch_bounds__(64) void k_member_ref_final(MemberDesc* descs, const double* parts) {
-  if (threadIdx.x != 0) return;
+// The members' references from their partial sums (added block by block), one
+// wave per member.
+__global__ __launch_bounds__(kRefBlocks) void k_member_ref(MemberDesc* descs, const double* parts,
+                                                           int nblocks, HostView* view) {
+  __shared__ double sh[kRefBlocks][2];
   MemberDesc& d = descs[blockIdx.x];
+  const int b = threadIdx.x;
+  const double* p = parts + ((int64_t)blockIdx.x * nblocks + b) * 5;
+  sh[b][0] = b < nblocks ? p[0] : 0.0;
+  sh[b][1] = b < nblocks ? p[1] : 0.0;
+  __syncthreads();
+  if (b != 0) return;
   double sn = 0.0, se = 0.0;
-  for (int b = 0; b < kRefBlocks; ++b) {
-    sn += parts[((int64_t)blockIdx.x * kRefBlocks + b) * 5 + 0];
-    se += parts[((int64_t)blockIdx.x * kRefBlocks + b) * 5 + 1];
+#pragma unroll 8
+  for (int k = 0; k < kRefBlocks; ++k) {
+    sn += sh[k][0];
+    se += sh[k][1];
   }
   d.ref.n = sn / d.ncells;
   d.ref.P = se / (3.0 * d.ncells);
-}
-
-__global__ __launch_bounds__(256) void k_validate(const double* n0, const double* eps0,
-                                                  const double* u0, int64_t ncells, int planar,
-                                                  const MemberDesc* descs, int n_members,
-                                                  unsigned long long* count) {
-  int nb = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ncells;
-       i += (int64_t)gridDim.x * 256) {
-    const double ux = u0[i], uy = u0[ncells + i], uz = u0[2 * ncells + i];
-    const double uu = ux * ux + uy * uy + uz * uz;
-    const Ext& x = descs[find_member(descs, n_members, i)].ext;
-    const bool ok = (eps0[i] > 0.0) && (n0[i] >= 0.0) && (uu < 1.0) && (n0[i] < INFINITY) &&
-                    (eps0[i] < INFINITY) && (!planar || uz == 0.0) &&
-                    (!x.general_eos || eps0[i] - x.mass * n0[i] > 0.0);
-    nb += ok ? 0 : 1;
-  }
-  if (nb) atomicAdd(count, (unsigned long long)nb);
+  if (blockIdx.x == 0) view->ref0 = d.ref;
 }
 
 template <typename T>
@@ -355,7 +385,9 @@ __global__ __launch_bounds__(256) void k_export(const T* state, StateLayout l,
                                                 const MemberDesc* descs, int n_members,
                                                 int64_t ncells, double* n, double* eps,
                                                 double* P, double* gamma, double* u,
-                                                double* partials) {
+                                                double* partials,
+                                                const unsigned long long* refused) {
+  if (refused && *refused) return;
   double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ncells;
        i += (int64_t)gridDim.x * 256) {
@@ -416,15 +448,26 @@ __global__ __launch_bounds__(256) void k_population_planes(const T* state, State
   }
 }
 
-// Deterministic sum of nparts partial 5-vectors (single block).
-__global__ __launch_bounds__(256) void k_reduce(const double* partials, int nparts, double* out) {
+// What the host reads back (single block): the deterministic sum of nparts
+// partial 5-vectors and the total of the inadmissible-cell slots.
+__global__ __launch_bounds__(256) void k_finish(const double* partials, int nparts,
+                                                const unsigned long long* __restrict__ slots,
+                                                HostView* view) {
+  static_assert(kBadSlots == 256, "one slot per thread");
+  __shared__ unsigned long long bad[4];
   double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  unsigned long long t = slots[(size_t)threadIdx.x * kBadStride];
   for (int j = threadIdx.x; j < nparts; j += 256)
 #pragma unroll
     for (int k = 0; k < 5; ++k) v[k] += partials[(int64_t)j * 5 + k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+  if ((threadIdx.x & 63) == 0) bad[threadIdx.x >> 6] = t;
   block_sum5<256>(v, threadIdx.x);
-  if (threadIdx.x == 0)
-    for (int k = 0; k < 5; ++k) out[k] = v[k];
+  if (threadIdx.x == 0) {
+    for (int k = 0; k < 5; ++k) view->sums[k] = v[k];
+    view->bad = (bad[0] + bad[1]) + (bad[2] + bad[3]);
+  }
 }
 
 // ------------------------------ variants ---------------------------------
@@ -479,20 +522,6 @@ const void* mem_func(int v) {
     case 3: return (const void*)&k_step_members<T, 512, 2, EXT>;
   }
   return nullptr;
-}
-
-// Total of the inadmissible-cell slots (count_bad) into *out: one block of
-// kBadSlots threads.
-__global__ __launch_bounds__(kBadSlots) void k_sum_bad(const unsigned long long* __restrict__ slots,
-                                                        unsigned long long* __restrict__ out) {
-  __shared__ unsigned long long sh[kBadSlots];
-  sh[threadIdx.x] = slots[(size_t)threadIdx.x * kBadStride];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long t = 0;
-    for (int k = 0; k < kBadSlots; ++k) t += sh[k];
-    *out = t;
-  }
 }
 
 }  // namespace
@@ -577,21 +606,22 @@ const char* member_kernel_name(int precision, int v) {
   return precision ? n32[v] : n64[v];
 }
 
-hipError_t launch_member_refs(const MemberDesc* descs, int n_members, const double* n0,
-                              const double* eps0, const double* u0, int64_t ncells,
-                              double* parts, hipStream_t s) {
-  hipLaunchKernelGGL(k_member_ref_parts, dim3(kRefBlocks, n_members), dim3(256), 0, s, descs, n0,
-                     eps0, u0, ncells, parts);
-  hipLaunchKernelGGL(k_member_ref_final, dim3(n_members), dim3(64), 0, s,
-                     const_cast<MemberDesc*>(descs), (const double*)parts);
+hipError_t launch_begin(unsigned long long* small, size_t n_small, unsigned long long* flags,
+                        size_t n_flags, const MemberDesc* one, MemberDesc* descs, hipStream_t s) {
+  const int64_t most = (int64_t)std::max(n_small, n_flags);
+  const int blocks = (int)std::min<int64_t>((most + 255) / 256, 1024);
+  hipLaunchKernelGGL(k_begin, dim3(blocks), dim3(256), 0, s, small, n_small, flags, n_flags,
+                     one ? *one : MemberDesc{}, one ? descs : nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_validate(const double* n0, const double* eps0, const double* u0,
-                           int64_t ncells, int planar, const MemberDesc* descs, int n_members,
-                           unsigned long long* count, hipStream_t s) {
-  hipLaunchKernelGGL(k_validate, dim3(grid_for(ncells)), dim3(256), 0, s, n0, eps0, u0, ncells,
-                     planar, descs, n_members, count);
+hipError_t launch_prepare(MemberDesc* descs, int n_members, int nblocks, const double* n0,
+                          const double* eps0, const double* u0, int64_t ncells, int planar,
+                          double* parts, HostView* view, hipStream_t s) {
+  hipLaunchKernelGGL(k_prepare, dim3(nblocks, n_members), dim3(256), 0, s,
+                     (const MemberDesc*)descs, n0, eps0, u0, ncells, planar, parts, view);
+  hipLaunchKernelGGL(k_member_ref, dim3(n_members), dim3(kRefBlocks), 0, s, descs,
+                     (const double*)parts, nblocks, view);
   return hipGetLastError();
 }
 
@@ -639,13 +669,13 @@ hipError_t launch_step_members(int precision, int v, int n_members, const Member
 hipError_t launch_export(int precision, const void* state, const StateLayout& l,
                          const MemberDesc* descs, int n_members, int64_t ncells, double* n, double* eps, double* P,
                          double* gamma, double* u, double* partials, int nparts,
-                         hipStream_t s) {
+                         const unsigned long long* refused, hipStream_t s) {
   if (precision)
     hipLaunchKernelGGL(k_export<float>, dim3(nparts), dim3(256), 0, s, (const float*)state, l,
-                       descs, n_members, ncells, n, eps, P, gamma, u, partials);
+                       descs, n_members, ncells, n, eps, P, gamma, u, partials, refused);
   else
     hipLaunchKernelGGL(k_export<double>, dim3(nparts), dim3(256), 0, s, (const double*)state,
-                       l, descs, n_members, ncells, n, eps, P, gamma, u, partials);
+                       l, descs, n_members, ncells, n, eps, P, gamma, u, partials, refused);
   return hipGetLastError();
 }
 
@@ -662,14 +692,9 @@ hipError_t launch_population_planes(int precision, const void* state, const Stat
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double* partials, int nparts, double* out5, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, partials, nparts, out5);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum_bad(const unsigned long long* slots, unsigned long long* out,
-                          hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_bad, dim3(1), dim3(kBadSlots), 0, s, slots, out);
+hipError_t launch_finish(const double* partials, int nparts, const unsigned long long* slots,
+                         HostView* view, hipStream_t s) {
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, partials, nparts, slots, view);
   return hipGetLastError();
 }
 

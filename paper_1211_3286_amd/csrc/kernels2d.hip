@@ -623,7 +623,9 @@ __global__ __launch_bounds__(256) void k_d2q9_export(const T* state, int64_t cs,
                                                      const MemberDesc* descs, int n_members,
                                                      int64_t ncells, double* n, double* eps,
                                                      double* P, double* gamma, double* u,
-                                                     double* partials) {
+                                                     double* partials,
+                                                     const unsigned long long* refused) {
+  if (refused && *refused) return;
   double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < ncells;
        i += (int64_t)gridDim.x * 256) {
@@ -969,14 +971,14 @@ hipError_t d2q9_launch_init(int precision, void* state, int64_t cs, const Member
 hipError_t d2q9_launch_export(int precision, const void* state, int64_t cs,
                               const MemberDesc* descs, int n_members, int64_t ncells, double* n,
                               double* eps, double* P, double* gamma, double* u,
-                              double* partials, int nparts, hipStream_t s) {
+                              double* partials, int nparts, const unsigned long long* refused, hipStream_t s) {
   if (precision)
     hipLaunchKernelGGL(k_d2q9_export<float>, dim3(nparts), dim3(256), 0, s, (const float*)state,
-                       cs, descs, n_members, ncells, n, eps, P, gamma, u, partials);
+                       cs, descs, n_members, ncells, n, eps, P, gamma, u, partials, refused);
   else
     hipLaunchKernelGGL(k_d2q9_export<double>, dim3(nparts), dim3(256), 0, s,
                        (const double*)state, cs, descs, n_members, ncells, n, eps, P, gamma, u,
-                       partials);
+                       partials, refused);
   return hipGetLastError();
 }
 

@@ -22,6 +22,8 @@ static __device__ __align__(256) unsigned char scratch[RLB_NOALLOC_SCRATCH_BYTES
 
 constexpr int kMaxDevices = 64;
 constexpr size_t kAlign = 256;
+// Lattices up to this size take 64-thread blocks (they leave CUs idle otherwise).
+constexpr int64_t kSmallCells = 64 * 4096;
 
 struct DeviceSlot {
   std::mutex mu;           // one call at a time per device: the array is shared
@@ -31,27 +33,22 @@ DeviceSlot g_slots[kMaxDevices];
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-__global__ void k_zero(unsigned long long* p, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0ull;
-}
-
 // Carving of the scratch array for one lattice of ncells cells.
 struct Carve {
   size_t desc, small, bad, parts, xparts, buf0, buf1, total;
   int64_t cs;
-  int export_parts;
+  int ref_blocks, export_parts;
 };
 
 Carve carve(int64_t ncells, int q, size_t esz) {
   Carve c{};
   c.cs = (ncells + 63) / 64 * 64 + 64;
-  c.export_parts = (int)std::min<int64_t>(std::max<int64_t>((ncells + 255) / 256, 1), 65536);
+  c.ref_blocks = rlb::ref_blocks(ncells);
+  c.export_parts = rlb::export_blocks(ncells);
   size_t o = 0;
   c.desc = o;
   o = align_up(o + sizeof(rlb::MemberDesc));
-  c.small = o;  // [0..4] sums, [16] validation count, [20] inadmissible total
+  c.small = o;  // the host's view
   o = align_up(o + 1024);
   c.bad = o;
   o = align_up(o + rlb::kBadBytes);
@@ -115,19 +112,12 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
   const int64_t nc = (int64_t)p.nx * p.ny * p.nz;
   const Carve c = carve(nc, d2 ? 9 : 19, o.precision == RLB_FP32 ? 4 : 8);
   rlb::MemberDesc* d_desc = (rlb::MemberDesc*)(ws + c.desc);
-  double* d_small = (double*)(ws + c.small);
-  unsigned long long* d_count = (unsigned long long*)(d_small + 16);
-  unsigned long long* d_bad_total = (unsigned long long*)(d_small + 20);
+  rlb::HostView* d_view = (rlb::HostView*)(ws + c.small);
   unsigned long long* d_bad = (unsigned long long*)(ws + c.bad);
   double* d_parts = (double*)(ws + c.parts);
   double* d_xparts = (double*)(ws + c.xparts);
   void* buf[2] = {ws + c.buf0, ws + c.buf1};
   const rlb::StateLayout lay = rlb::plane_layout(c.cs, (uint32_t)p.nx * (uint32_t)p.ny);
-
-  // the array keeps the previous call's contents: clear the counters
-  const size_t nzero = (c.parts - c.small) / sizeof(unsigned long long);
-  hipLaunchKernelGGL(k_zero, dim3(64), dim3(256), 0, st, (unsigned long long*)d_small, nzero);
-  NA_HIP(hipGetLastError());
 
   rlb::MemberDesc desc;
   std::memset(&desc, 0, sizeof(desc));
@@ -157,65 +147,52 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
   desc.ext.mass = p.mass;
   desc.ext.general_eos = paper_eos(p) ? 0 : 1;
   const bool ext = p.eta_over_s > 0.0 || desc.ext.general_eos;
-  NA_HIP(hipMemcpyAsync(d_desc, &desc, sizeof(desc), hipMemcpyHostToDevice, st));
 
-  // validation of the input fields (rlb_init's checks), before any state
-  NA_HIP(rlb::launch_validate(n0, eps0, u0, nc, d2 ? 1 : 0, d_desc, 1, d_count, st));
-  unsigned long long cnt = 0;
-  NA_HIP(hipMemcpyAsync(&cnt, d_count, sizeof(cnt), hipMemcpyDeviceToHost, st));
-  NA_HIP(hipStreamSynchronize(st));
-  if (cnt) return RLB_E_UNPHYSICAL;
-
-  // t = 0: reference state and equilibria (rlb_init)
-  NA_HIP(rlb::launch_member_refs(d_desc, 1, n0, eps0, u0, nc, d_parts, st));
+  // The whole run is enqueued and its one answer read back at the end (each
+  // wait for the device costs what several of these kernels take): the
+  // reference state stays on the device, where the step kernels read it, and
+  // the export writes nothing when the input pass refused a cell. The array
+  // keeps the previous call's contents: the counters are cleared first.
+  NA_HIP(rlb::launch_begin((unsigned long long*)d_view,
+                           (c.parts - c.small) / sizeof(unsigned long long), nullptr, 0, &desc,
+                           d_desc, st));
+  NA_HIP(rlb::launch_prepare(d_desc, 1, c.ref_blocks, n0, eps0, u0, nc, d2 ? 1 : 0, d_parts,
+                             d_view, st));
   NA_HIP(d2 ? rlb::d2q9_launch_init(o.precision, buf[0], c.cs, d_desc, 1, n0, eps0, u0, nc, st)
             : rlb::launch_init(o.precision, buf[0], lay, d_desc, 1, n0, eps0, u0, nc, st));
-  NA_HIP(hipMemcpyAsync(&desc, d_desc, sizeof(desc), hipMemcpyDeviceToHost, st));
-  NA_HIP(hipStreamSynchronize(st));
 
-  // steps (rlb_step): one fused launch per step, the default lattice variant
-  rlb::LatticeGeom g{};
-  g.nx = desc.nx;
-  g.ny = desc.ny;
-  g.nz = desc.nz;
-  g.bcx = desc.bcx;
-  g.bcy = desc.bcy;
-  g.bcz = desc.bcz;
-  g.cs = c.cs;
-  g.lay = lay;
-  g.rt = desc.rt;
-  g.ref = desc.ref;
-  g.ext = desc.ext;
-  g.cached_store = 1;  // at most RLB_NOALLOC_SCRATCH_BYTES of state
-  const int variant = d2 ? 2 : 3;
+  // steps (rlb_step): one launch per step
+  const int variant = nc <= kSmallCells ? 0 : 1;
+  const int blocks = (int)(variant ? (nc + 255) / 256 : (nc + 63) / 64);
+  rlb::MemberLaunch m{};
+  m.descs = d_desc;
+  m.cs = c.cs;
+  m.partials = d_parts;
+  m.bad = d_bad;
   int cur = 0;
   for (int32_t i = 0; i < nsteps; ++i) {
-    if (d2)
-      NA_HIP(rlb::d2q9_launch_step_lattice(o.precision, variant, false, o.correction != 0, ext,
-                                           buf[cur], buf[1 - cur], g, d_parts, d_bad, st));
-    else
-      NA_HIP(rlb::launch_step_lattice(o.precision, variant, false, ext, buf[cur], buf[1 - cur],
-                                      g, d_parts, d_bad, st));
+    m.bufA = buf[cur];
+    m.bufB = buf[1 - cur];
+    NA_HIP(rlb::launch_step_cells(o.precision, d2, variant, o.correction != 0, ext, false, m, 1,
+                                  blocks, st));
     cur = 1 - cur;
   }
 
   // fields and lattice sums of the final state (rlb_moments)
   if (d2)
     NA_HIP(rlb::d2q9_launch_export(o.precision, buf[cur], c.cs, d_desc, 1, nc, n, eps, P, gamma,
-                                   u, d_xparts, c.export_parts, st));
+                                   u, d_xparts, c.export_parts, &d_view->refused, st));
   else
     NA_HIP(rlb::launch_export(o.precision, buf[cur], lay, d_desc, 1, nc, n, eps, P, gamma, u,
-                              d_xparts, c.export_parts, st));
-  NA_HIP(rlb::launch_reduce(d_xparts, c.export_parts, d_small, st));
-  NA_HIP(rlb::launch_sum_bad(d_bad, d_bad_total, st));
-  double hs[5];
-  unsigned long long bad = 0;
-  NA_HIP(hipMemcpyAsync(hs, d_small, sizeof(hs), hipMemcpyDeviceToHost, st));
-  NA_HIP(hipMemcpyAsync(&bad, d_bad_total, sizeof(bad), hipMemcpyDeviceToHost, st));
+                              d_xparts, c.export_parts, &d_view->refused, st));
+  NA_HIP(rlb::launch_finish(d_xparts, c.export_parts, d_bad, d_view, st));
+  rlb::HostView view;
+  NA_HIP(hipMemcpyAsync(&view, d_view, sizeof(view), hipMemcpyDeviceToHost, st));
   NA_HIP(hipStreamSynchronize(st));
-  if (sums) std::memcpy(sums, hs, sizeof(hs));
-  if (n_unphysical) *n_unphysical = (int64_t)bad;
-  return bad ? RLB_E_UNPHYSICAL : RLB_OK;
+  if (view.refused) return RLB_E_UNPHYSICAL;
+  if (sums) std::memcpy(sums, view.sums, sizeof(view.sums));
+  if (n_unphysical) *n_unphysical = (int64_t)view.bad;
+  return view.bad ? RLB_E_UNPHYSICAL : RLB_OK;
 }
 
 }  // namespace
