@@ -337,9 +337,29 @@ rlb_status launch_lattice_step(rlb_sim* h, int variant, bool diag, const void* s
                                           h->d_partials, h->d_bad, h->stream));
 }
 
-// D3Q19 marching variants: two steps per launch; steps that cannot be paired
-// (the odd one of a call, diagnostics steps) run the one-step kernel kMarchStep.
-constexpr int kMarchStep = 2;
+// Marching variants (D3Q19: two steps per launch, D2Q9: H); steps that do not
+// fill a launch (the last of a call, diagnostics steps) run a one-step kernel.
+int march_step(const rlb_sim* h) { return h->d2 ? 3 : 2; }
+
+int march_base(const rlb_sim* h) {
+  return h->d2 ? rlb::d2q9_num_lattice_variants() + rlb::d2q9_num_tile_variants()
+               : rlb::num_lattice_variants();
+}
+
+bool is_march_variant(const rlb_sim* h, int v) { return h->lattice && v >= march_base(h); }
+
+// Where a marching variant cannot launch (D3Q19 lattices stored in planes;
+// D2Q9: the correction, or fewer columns between faces than a wave has) it runs
+// its steps one by one.
+bool can_march(const rlb_sim* h) {
+  if (h->d2) return !h->corr && rlb::d2q9_march_fits(h->geom);
+  return h->L.lay.shift == rlb::kBlockShift;
+}
+
+int march_steps(const rlb_sim* h, int v) {
+  if (!can_march(h)) return 1;
+  return h->d2 ? rlb::d2q9_march_steps(v - march_base(h)) : 2;
+}
 
 // A marching launch is the default from this share of used cells on (MarchGrid::use).
 // At full use it updates 29 G cells/s in FP32 against 18-19 of the one-step
@@ -348,23 +368,23 @@ constexpr int kMarchStep = 2;
 // 22.1 and 25.2, 96^3 FP32 (0.74) 34.8 and 43.1. With the extended model, whose
 // arithmetic weighs more: 96^3 FP32 (0.74) 48.5 against 45.3, 128^3 FP32 (0.85)
 // 104 and 114.
+// D2Q9, us a step against the one-step default: 700 x 500 FP32 (0.33) 10.1 and
+// 10.3, 300^2 FP32 (0.08) 7.3 and 5.9, 1000 x 800 FP32 (0.52) 15 and 20; extended:
+// 1000 x 800 FP32 (0.52) 29 and 22, FP64 (0.64) 32 and 37.
 constexpr double kMarchUse = 0.6, kMarchUseExt = 0.8;
-
-bool is_march_variant(const rlb_sim* h, int v) {
-  return h->lattice && !h->d2 && v >= rlb::num_lattice_variants();
-}
-
-// A lattice stored in planes runs a marching variant's steps one by one.
-bool can_march(const rlb_sim* h) { return h->L.lay.shift == rlb::kBlockShift; }
+constexpr double kMarchUse2 = 0.35, kMarchUseExt2 = 0.6;
 
 rlb_status launch_march(rlb_sim* h, int variant, const void* src, void* dst) {
-  return dev_err(rlb::launch_step_march(h->precision, variant - rlb::num_lattice_variants(),
-                                        h->ext, src, dst, h->geom, h->march, h->d_bad,
-                                        h->stream));
+  const int v = variant - march_base(h);
+  if (h->d2)
+    return dev_err(rlb::d2q9_launch_march(h->precision, v, h->ext, src, dst, h->geom, h->num_cu,
+                                          h->d_bad, h->stream));
+  return dev_err(rlb::launch_step_march(h->precision, v, h->ext, src, dst, h->geom, h->march,
+                                        h->d_bad, h->stream));
 }
 
 bool is_tile_variant(const rlb_sim* h, int v) {
-  return h->lattice && h->d2 && v >= rlb::d2q9_num_lattice_variants();
+  return h->lattice && h->d2 && v >= rlb::d2q9_num_lattice_variants() && !is_march_variant(h, v);
 }
 
 int tile_index(int v) { return v - rlb::d2q9_num_lattice_variants(); }
@@ -377,8 +397,9 @@ int lattice_parts(const rlb_sim* h, int variant) {
                   a, grid);
     return (int)(grid.x * grid.y);
   }
-  if (h->d2) return rlb::d2q9_lattice_partials(variant, h->geom);
-  return rlb::lattice_partials(is_march_variant(h, variant) ? kMarchStep : variant, h->geom);
+  if (is_march_variant(h, variant)) variant = march_step(h);
+  return h->d2 ? rlb::d2q9_lattice_partials(variant, h->geom)
+               : rlb::lattice_partials(variant, h->geom);
 }
 
 // D2Q9 tile rounds: ceil(n / H) launches, each advancing up to H steps of the
@@ -770,19 +791,22 @@ rlb_status advance(rlb_sim* h, int32_t n) {
   }
   if (h->lattice) {
     const bool march = is_march_variant(h, h->variant);
-    const int one = march ? kMarchStep : h->variant;
+    const int one = march ? march_step(h) : h->variant;
+    const int per = march ? march_steps(h, h->variant) : 1;
     for (int32_t i = 0; i < n; ++i) {
       const int64_t s = h->steps + 1;
       const auto is_diag = [&](int64_t step, int32_t at) {
         return D > 0 && (step % D == 0 || at == n - 1);
       };
       const bool diag = is_diag(s, i);
-      if (march && can_march(h) && i + 1 < n && !diag && !is_diag(s + 1, i + 1)) {
+      int k = 0;  // steps from here on that may share a launch
+      while (k < per && i + k < n && !is_diag(s + k, i + k)) ++k;
+      if (per > 1 && k == per) {
         rlb_status st = launch_march(h, h->variant, state_buf(h), spare_buf(h));
         if (st != RLB_OK) return st;
         h->cur = 1 - h->cur;
-        h->steps = s + 1;
-        ++i;
+        h->steps += per;
+        i += per - 1;
         continue;
       }
       rlb_status st = launch_lattice_step(h, one, diag, state_buf(h), spare_buf(h));
@@ -858,6 +882,9 @@ bool host_fields_ok(const double* n0, const double* eps0, const double* u0, int6
 namespace {
 
 const char* kernel_name_of(const rlb_sim* h, int v) {
+  if (is_march_variant(h, v))
+    return h->d2 ? rlb::d2q9_march_kernel_name(h->precision, v - march_base(h))
+                 : rlb::march_kernel_name(h->precision, v - march_base(h));
   if (is_cells_variant(h, v)) return rlb::cells_kernel_name(h->precision, h->d2, v - cells_base(h));
   if (h->d2) {
     if (is_tile_variant(h, v)) return rlb::d2q9_tile_kernel_name(h->precision, tile_index(v));
@@ -865,8 +892,6 @@ const char* kernel_name_of(const rlb_sim* h, int v) {
     if (is_strip_variant(h, v)) return rlb::d2q9_strip_kernel_name(h->precision, strip_index(v));
     return rlb::d2q9_member_kernel_name(h->precision, v);
   }
-  if (is_march_variant(h, v))
-    return rlb::march_kernel_name(h->precision, v - rlb::num_lattice_variants());
   if (h->lattice) return rlb::lattice_kernel_name(h->precision, v);
   if (v < rlb::num_member_variants()) return rlb::member_kernel_name(h->precision, v);
   if (is_segment_variant(h, v))
@@ -967,8 +992,10 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   h->all_tubes = !h->d2;
   for (int i = 0; i < n_members; ++i)
     if (members[i].nx != 1 || members[i].ny != 1) h->all_tubes = false;
-  // default of the lattice path: the 256 x 1 block
-  h->variant = h->lattice ? (h->d2 ? 2 : 3) : default_persistent(h);
+  // default of the lattice path where nothing marches: the 256 x 1 block, or
+  // with the correction the 64 x 4 one, which shares the neighbours' fields
+  // (1531 x 1203 FP64 128 us a step against 135, FP32 50 against 70)
+  h->variant = h->lattice ? (h->d2 ? (h->corr ? 3 : 2) : 3) : default_persistent(h);
 
   auto fail = [&](rlb_status s) {
     delete h;
@@ -1064,10 +1091,17 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     // 4-5 % faster from 1.3 GB up, e.g. the 5.1 GB of 256^3).
     h->geom.cached_store = 2 * (L.off_buf1 - L.off_buf0) <= kCachedStateBytes ? 1 : 0;
   }
-  if (can_march(h)) {
-    h->march = rlb::march_grid(h->precision, h->geom, h->num_cu);
-    if (h->march.use >= (h->ext ? kMarchUseExt : kMarchUse))
-      h->variant = rlb::num_lattice_variants();
+  if (h->lattice && can_march(h)) {
+    double use, least;
+    if (h->d2) {
+      use = rlb::d2q9_march_use(h->precision, h->ext, h->geom, h->num_cu);
+      least = h->ext ? kMarchUseExt2 : kMarchUse2;
+    } else {
+      h->march = rlb::march_grid(h->precision, h->geom, h->num_cu);
+      use = h->march.use;
+      least = h->ext ? kMarchUseExt : kMarchUse;
+    }
+    if (use >= least) h->variant = march_base(h);
   }
   h->cur = 0;
   if (opt->ckpt_every > 0) {
@@ -1227,10 +1261,10 @@ rlb_status rlb_grad(rlb_handle h, const double* dL_du, const double* dL_deps,
 rlb_status rlb_num_variants(rlb_handle h, int32_t* count) {
   if (!h || !count) return RLB_E_ARG;
   if (h->d2)
-    *count = h->lattice ? rlb::d2q9_num_lattice_variants() + rlb::d2q9_num_tile_variants()
+    *count = h->lattice ? march_base(h) + rlb::d2q9_num_march_variants()
                         : cells_base(h) + rlb::kNumCells;
   else
-    *count = h->lattice ? rlb::num_lattice_variants() + rlb::num_march_variants()
+    *count = h->lattice ? march_base(h) + rlb::num_march_variants()
                         : cells_base(h) + rlb::kNumCells;
   return RLB_OK;
 }
@@ -1288,13 +1322,14 @@ rlb_status rlb_tune(rlb_handle h, int32_t trial_steps, int32_t* best_variant,
         }
       } else if (h->lattice) {
         const bool march = is_march_variant(h, v);
-        for (int i = 0; i < trial_steps && st == RLB_OK; ++i) {
-          if (march && can_march(h) && i + 1 < trial_steps) {
+        const int per = march ? march_steps(h, v) : 1;
+        for (int i = 0; i < trial_steps && st == RLB_OK; i += per) {
+          if (per > 1 && i + per <= trial_steps)
             st = launch_march(h, v, state_buf(h), spare_buf(h));
-            ++i;
-          } else {
-            st = launch_lattice_step(h, march ? kMarchStep : v, false, state_buf(h), spare_buf(h));
-          }
+          else
+            for (int k = i; k < std::min(i + per, trial_steps) && st == RLB_OK; ++k)
+              st = launch_lattice_step(h, march ? march_step(h) : v, false, state_buf(h),
+                                       spare_buf(h));
         }
       } else if (st == RLB_OK) {
         bool flip = false;

@@ -77,6 +77,52 @@ __device__ __forceinline__ void st(T* plane, uint32_t byteoff, T v) {
   *reinterpret_cast<T*>(reinterpret_cast<char*>(plane) + byteoff) = v;
 }
 
+// Pointers known to be global (a lane's element: scalar base, vector offset).
+template <typename T>
+using GPtr = __attribute__((address_space(1))) T*;
+
+template <typename T>
+__device__ __forceinline__ GPtr<T> to_global(T* p) {
+  return (GPtr<T>)p;
+}
+
+// A scalar pointer moved on in an opaque chain: the many plane bases of a loop
+// would spill scalar registers if the compiler held them all across it.
+template <typename T>
+__device__ __forceinline__ void advance(GPtr<T>& p, int64_t n) {
+  p += n;
+  asm volatile("" : "+s"(p));
+}
+
+// The element at a 32-bit byte offset of a plane: scalar base, vector offset.
+// (The offset is opaque too: widened to 64 bits outside the loop it would cost
+// a vector addition per access.)
+template <typename T>
+__device__ __forceinline__ T at_off(GPtr<const T> p, uint32_t off) {
+  asm volatile("" : "+v"(off));
+  return *(GPtr<const T>)((GPtr<const char>)p + off);
+}
+
+template <bool NTS, typename T>
+__device__ __forceinline__ void put_off(GPtr<T> p, uint32_t off, T v) {
+  asm volatile("" : "+v"(off));
+  GPtr<T> q = (GPtr<T>)((GPtr<char>)p + off);
+  if constexpr (NTS)
+    __builtin_nontemporal_store(v, q);
+  else
+    *q = v;
+}
+
+// Waits for the values (loads in flight land) and keeps the compiler from
+// waiting for them again later, when stores are in flight behind them.
+template <typename T, int N>
+__device__ __forceinline__ void landed(T (&v)[N]) {
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int a = 0; a < N; ++a) asm volatile("" : "+v"(v[a]));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Byte offsets of the 19 pull sources of cell (x, y, z) (source = cell - e_a).
 __device__ __forceinline__ void pull_offsets(int x, int y, int z, int nx, int ny, int nz, int bcx,
                                              int bcy, int bcz, uint32_t base, uint32_t esz,

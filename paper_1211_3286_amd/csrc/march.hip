@@ -45,34 +45,6 @@ __device__ __forceinline__ int on_axis(int c, int N, int bc) {
   return c < 0 ? c + N : c;
 }
 
-// Pointers known to be global (a lane's element: scalar base, vector offset).
-template <typename T>
-using GPtr = __attribute__((address_space(1))) T*;
-
-template <typename T>
-__device__ __forceinline__ GPtr<T> to_global(T* p) {
-  return (GPtr<T>)p;
-}
-
-// The element at a 32-bit byte offset of a plane: scalar base, vector offset.
-// (The offset is opaque too: widened to 64 bits outside the loop it would cost
-// a vector addition per access.)
-template <typename T>
-__device__ __forceinline__ T at_off(GPtr<const T> p, uint32_t off) {
-  asm volatile("" : "+v"(off));
-  return *(GPtr<const T>)((GPtr<const char>)p + off);
-}
-
-template <bool NTS, typename T>
-__device__ __forceinline__ void put_off(GPtr<T> p, uint32_t off, T v) {
-  asm volatile("" : "+v"(off));
-  GPtr<T> q = (GPtr<T>)((GPtr<char>)p + off);
-  if constexpr (NTS)
-    __builtin_nontemporal_store(v, q);
-  else
-    *q = v;
-}
-
 // Byte offset of cell (x, y) within a z-plane of a blocked region (a plane is
 // whole blocks).
 template <typename T>
@@ -132,16 +104,6 @@ __device__ __forceinline__ void f_half(T (&f)[19], const LatticeGeom& geo, const
     for (int a = 0; a < 19; ++a) fs += (double)f[a];
     if (h.ok) collide_f(f, geo.ref.n + fs, fs, h.mac, geo.rt, geo.ref);
   }
-}
-
-// Waits for the values (loads in flight land) and keeps the compiler from
-// waiting for them again later, when stores are in flight behind them.
-template <typename T>
-__device__ __forceinline__ void landed(T (&v)[19]) {
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int a = 0; a < 19; ++a) asm volatile("" : "+v"(v[a]));
-  __builtin_amdgcn_sched_barrier(0);
 }
 
 template <typename T, int WX, int WY, int NT, bool EXT, bool NTS>

@@ -41,11 +41,17 @@ def _problem(shape, bc, eta=0.0):
     return prob
 
 
+def _plane(nx, ny, bc, eta=0.0):
+    prob = _problem((nx, ny, 1), bc + (0,), eta)
+    prob.params.lattice, prob.params.kappa = "d2q9", 4 / 3
+    return prob
+
+
 def _run(prob, prec, variant, calls, **kw):
     import paper_1211_3286_amd as rlb
     sim = rlb.from_problems(prob, precision=prec, **kw)
     sim.variant = variant
-    assert ("march" in sim.kernel_name) == (variant == MARCH)
+    assert ("march" in sim.kernel_name) == (variant >= (17 if sim.q == 9 else MARCH))
     for n in calls:
         sim.step(n)
     return sim
@@ -92,6 +98,51 @@ def test_march_keeps_the_diagnostics_steps():
     prob = _problem((96, 80, 64), (0, 0, 0))
     a, b = (_run(prob, FP32, v, (), diag_every=5) for v in (MARCH, ONE))
     for n in (9, 1, 14):
+        a.step(n)
+        b.step(n)
+        (sa, ta, _), (sb, tb, _) = a.diagnostics(), b.diagnostics()
+        assert ta == tb == a.steps and np.array_equal(sa, sb)
+    for x, y in zip(a.populations(), b.populations()):
+        assert bool((x == y).all())
+
+
+# D2Q9: strips own 58 (H = 4) or 60 columns of 64; ranges of a few rows
+PLANES = [
+    ((58, 300), (0, 0)), ((59, 290), (0, 1)), ((64, 257), (1, 1)), ((65, 260), (1, 0)),
+    ((122, 140), (1, 1)), ((3, 6000), (0, 1)), ((2049, 8), (1, 0)), ((2100, 9), (0, 1)),
+    ((187, 151), (1, 1)), ((63, 300), (1, 1)), ((2400, 7), (0, 0)),
+]
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("eta", [0.0, 0.1], ids=["fixed", "eta_s"])
+@pytest.mark.parametrize("shape,bc", PLANES, ids=["x".join(map(str, s)) for s, _ in PLANES])
+def test_d2q9_march_equals_the_one_step_kernel(shape, bc, eta, prec):
+    """Every marching variant against the first one-step kernel, bit for bit, and
+    that one against the oracle; lattices too small to march run step by step."""
+    prob = _plane(*shape, bc, eta)
+    say("d2q9 march", shape, bc, eta, "prec", prec)
+    ref = _run(prob, prec, 0, (11,))
+    st = oracle.run(prob, 11)
+    gs, _, bad = gpu_state(ref, prob)
+    assert bad == st.bad == 0
+    assert relmax(gs[0]["f"], st.f) < TOL[prec] and relmax(gs[0]["g"], st.g) < TOL[prec]
+    for v in (17, 18):
+        sim = _run(prob, prec, v, (9, 2))
+        for x, y in zip(sim.populations(), ref.populations()):
+            assert bool((x == y).all()), sim.kernel_name
+        sim.close()
+
+
+def test_d2q9_march_counts_and_diagnostics():
+    prob = wl.blast_disk(136)
+    st = oracle.run(prob, 4)
+    for v in (17, 18):
+        sim = _run(prob, FP64, v, (4,))
+        assert sim.moments(allow_unphysical=True)["bad"] == st.bad > 50
+    prob = _plane(200, 150, (0, 0))
+    a, b = (_run(prob, FP32, v, (), diag_every=7) for v in (17, 3))
+    for n in (13, 1, 9):
         a.step(n)
         b.step(n)
         (sa, ta, _), (sb, tb, _) = a.diagnostics(), b.diagnostics()
