@@ -349,16 +349,16 @@ int march_base(const rlb_sim* h) {
 bool is_march_variant(const rlb_sim* h, int v) { return h->lattice && v >= march_base(h); }
 
 // Where a marching variant cannot launch (D3Q19 lattices stored in planes;
-// D2Q9: the correction, or fewer columns between faces than a wave has) it runs
-// its steps one by one.
+// D2Q9: fewer columns between faces than a wave has, or few rows) it runs its
+// steps one by one.
 bool can_march(const rlb_sim* h) {
-  if (h->d2) return !h->corr && rlb::d2q9_march_fits(h->geom);
+  if (h->d2) return rlb::d2q9_march_fits(h->geom);
   return h->L.lay.shift == rlb::kBlockShift;
 }
 
 int march_steps(const rlb_sim* h, int v) {
   if (!can_march(h)) return 1;
-  return h->d2 ? rlb::d2q9_march_steps(v - march_base(h)) : 2;
+  return h->d2 ? rlb::d2q9_march_steps(v - march_base(h), h->corr) : 2;
 }
 
 // A marching launch is the default from this share of used cells on (MarchGrid::use).
@@ -370,14 +370,22 @@ int march_steps(const rlb_sim* h, int v) {
 // 104 and 114.
 // D2Q9, us a step against the one-step default: 700 x 500 FP32 (0.33) 10.1 and
 // 10.3, 300^2 FP32 (0.08) 7.3 and 5.9, 1000 x 800 FP32 (0.52) 15 and 20; extended:
-// 1000 x 800 FP32 (0.52) 29 and 22, FP64 (0.64) 32 and 37.
-constexpr double kMarchUse = 0.6, kMarchUseExt = 0.8;
-constexpr double kMarchUse2 = 0.35, kMarchUseExt2 = 0.6;
+// 1000 x 800 FP32 (0.52) 29 and 22, FP64 (0.64) 32 and 37. With the correction:
+// 1000 x 800 FP32 (0.53) 26 and 25, 1531 x 1203 FP32 (0.69) 45 and 50, 700 x 500
+// FP64 (0.55) 18 and 21, 300^2 FP64 (0.18) 14 and 9; extended and corrected:
+// 2000 x 1800 FP32 145 and 118 (one wave per SIMD: never the default), FP64 (0.82)
+// 156 and 199.
+double least_march_use(const rlb_sim* h) {
+  if (!h->d2) return h->ext ? 0.8 : 0.6;
+  if (!h->corr) return h->ext ? 0.6 : 0.35;
+  if (h->precision == RLB_FP32) return h->ext ? 2.0 : 0.6;
+  return h->ext ? 0.7 : 0.5;
+}
 
 rlb_status launch_march(rlb_sim* h, int variant, const void* src, void* dst) {
   const int v = variant - march_base(h);
   if (h->d2)
-    return dev_err(rlb::d2q9_launch_march(h->precision, v, h->ext, src, dst, h->geom, h->num_cu,
+    return dev_err(rlb::d2q9_launch_march(h->precision, v, h->corr, h->ext, src, dst, h->geom, h->num_cu,
                                           h->d_bad, h->stream));
   return dev_err(rlb::launch_step_march(h->precision, v, h->ext, src, dst, h->geom, h->march,
                                         h->d_bad, h->stream));
@@ -883,7 +891,7 @@ namespace {
 
 const char* kernel_name_of(const rlb_sim* h, int v) {
   if (is_march_variant(h, v))
-    return h->d2 ? rlb::d2q9_march_kernel_name(h->precision, v - march_base(h))
+    return h->d2 ? rlb::d2q9_march_kernel_name(h->precision, v - march_base(h), h->corr)
                  : rlb::march_kernel_name(h->precision, v - march_base(h));
   if (is_cells_variant(h, v)) return rlb::cells_kernel_name(h->precision, h->d2, v - cells_base(h));
   if (h->d2) {
@@ -1092,16 +1100,11 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     h->geom.cached_store = 2 * (L.off_buf1 - L.off_buf0) <= kCachedStateBytes ? 1 : 0;
   }
   if (h->lattice && can_march(h)) {
-    double use, least;
-    if (h->d2) {
-      use = rlb::d2q9_march_use(h->precision, h->ext, h->geom, h->num_cu);
-      least = h->ext ? kMarchUseExt2 : kMarchUse2;
-    } else {
-      h->march = rlb::march_grid(h->precision, h->geom, h->num_cu);
-      use = h->march.use;
-      least = h->ext ? kMarchUseExt : kMarchUse;
-    }
-    if (use >= least) h->variant = march_base(h);
+    if (!h->d2) h->march = rlb::march_grid(h->precision, h->geom, h->num_cu);
+    const double use =
+        h->d2 ? rlb::d2q9_march_use(h->precision, h->corr, h->ext, h->geom, h->num_cu)
+              : h->march.use;
+    if (use >= least_march_use(h)) h->variant = march_base(h);
   }
   h->cur = 0;
   if (opt->ckpt_every > 0) {
@@ -1261,7 +1264,7 @@ rlb_status rlb_grad(rlb_handle h, const double* dL_du, const double* dL_deps,
 rlb_status rlb_num_variants(rlb_handle h, int32_t* count) {
   if (!h || !count) return RLB_E_ARG;
   if (h->d2)
-    *count = h->lattice ? march_base(h) + rlb::d2q9_num_march_variants()
+    *count = h->lattice ? march_base(h) + rlb::d2q9_num_march_variants(h->corr)
                         : cells_base(h) + rlb::kNumCells;
   else
     *count = h->lattice ? march_base(h) + rlb::num_march_variants()

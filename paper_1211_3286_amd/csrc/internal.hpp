@@ -321,16 +321,16 @@ hipError_t d2q9_launch_population_planes(int precision, const void* state, int64
                                          const MemberDesc* descs, int n_members, int64_t ncells,
                                          int p0, int np, double* out, hipStream_t s);
 
-// H steps per launch on one D2Q9 lattice without the correction (march2d.hip).
-// cus: compute units of the device.
-int d2q9_num_march_variants();
-int d2q9_march_steps(int variant);
+// H steps per launch on one D2Q9 lattice (march2d.hip). cus:
+// compute units of the device.
+int d2q9_num_march_variants(bool corr);
+int d2q9_march_steps(int variant, bool corr);
 bool d2q9_march_fits(const LatticeGeom& g);
 // Share of variant 0's cell slots that are cells of the lattice.
-double d2q9_march_use(int precision, bool ext, const LatticeGeom& g, int cus);
-const char* d2q9_march_kernel_name(int precision, int variant);
-hipError_t d2q9_launch_march(int precision, int variant, bool ext, const void* src, void* dst,
-                             const LatticeGeom& g, int cus, unsigned long long* bad,
+double d2q9_march_use(int precision, bool corr, bool ext, const LatticeGeom& g, int cus);
+const char* d2q9_march_kernel_name(int precision, int variant, bool corr);
+hipError_t d2q9_launch_march(int precision, int variant, bool corr, bool ext, const void* src,
+                             void* dst, const LatticeGeom& g, int cus, unsigned long long* bad,
                              hipStream_t s);
 
 }  // namespace rlb

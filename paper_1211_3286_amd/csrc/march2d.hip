@@ -16,6 +16,12 @@
 // take 0.245 and 0.195 ms, FP64 H = 3, 4, 6 0.403, 0.299 and 0.293. us a step,
 // best tile and now (H = 4): 4096^2 FP32 265 and 195, FP64 503 and 299; 2048^2
 // FP64 120 and 72; 1531 x 1203 FP32 31 and 26, FP64 52 and 35.
+//
+// With the correction of Eqs. (37)-(38) a stage recovers a row as it arrives and
+// collides it one row later, between the fields of its neighbours: one recovery
+// per cell, two rows of lag per stage, H = 2 (250 registers in FP32, a wave per
+// SIMD in FP64). us a step, best one-step kernel and now: 4096^2 FP32 420 and
+// 347, FP64 831 and 557; 1531 x 1203 FP64 125 and 68.
 
 #include <hip/hip_runtime.h>
 
@@ -62,12 +68,80 @@ struct Between {
   T up_old[6], up[6], mid[6], down[6];
 };
 
-template <typename T, int H, bool EXT>
+// With the correction a stage collides a row once the fields of the next are
+// known: the row it holds meanwhile, and the fields of that row and the last.
+// (Plain scalars, copied one by one: copies of the structs themselves would keep
+// the array in memory. What a few operations give again is not held: N, u^2, P
+// and three of the own fields come back by the expressions they came from.)
+template <typename T>
+struct Held {
+  T f[9], g[9];
+  double fs, gs, Mx, My, ux, uy, sigma, gam;  // this row
+  double b_x1, b_gam, b_su2, b_su;            // fields of the row below
+  int ok, b_ok;
+
+  __device__ __forceinline__ d2q9::Recovered rec(const Ref& ref) const {
+    d2q9::Recovered r;
+    r.N = ref.n + fs;
+    r.E = 0.0;  // only for the sums, which no marching launch leaves
+    r.Mx = Mx;
+    r.My = My;
+    r.fs = fs;
+    r.gs = gs;
+    r.mac.ux = ux;
+    r.mac.uy = uy;
+    r.mac.uz = 0.0;
+    r.mac.u2 = r.mac.ux * r.mac.ux + r.mac.uy * r.mac.uy;
+    r.mac.sigma = sigma;
+    r.mac.P = 0.25 * r.mac.sigma * (1.0 - r.mac.u2);
+    r.ok = ok != 0;
+    return r;
+  }
+  __device__ __forceinline__ d2q9::C7Fields fields(const d2q9::Recovered& r) const {
+    d2q9::C7Fields F;
+    F.x1 = r.mac.sigma * (1.0 / 3.0) - r.mac.P;
+    F.gam = gam;
+    F.su = r.mac.sigma * r.mac.uy;
+    F.su2 = F.su * r.mac.uy;
+    F.ok = r.ok;
+    return F;
+  }
+  __device__ __forceinline__ d2q9::C7Fields below() const {
+    return d2q9::C7Fields{b_x1, b_gam, b_su2, b_su, b_ok != 0};
+  }
+  __device__ __forceinline__ void set_below(const d2q9::C7Fields& F) {
+    b_x1 = F.x1;
+    b_gam = F.gam;
+    b_su2 = F.su2;
+    b_su = F.su;
+    b_ok = F.ok ? 1 : 0;
+  }
+  __device__ __forceinline__ void set(const T (&nf)[9], const T (&ng)[9],
+                                      const d2q9::Recovered& r, double g_am) {
+    fs = r.fs;
+    gs = r.gs;
+    Mx = r.Mx;
+    My = r.My;
+    ux = r.mac.ux;
+    uy = r.mac.uy;
+    sigma = r.mac.sigma;
+    gam = g_am;
+    ok = r.ok ? 1 : 0;
+#pragma unroll
+    for (int a = 0; a < 9; ++a) {
+      f[a] = nf[a];
+      g[a] = ng[a];
+    }
+  }
+};
+
+template <typename T, int H, bool CORR, bool EXT>
 __global__ __launch_bounds__(64 * kWaves) void k_d2q9_march(const T* __restrict__ src,
                                                             T* __restrict__ dst, LatticeGeom geo,
                                                             int nstrips, int nbx, int nchunks,
                                                             unsigned long long* __restrict__ bad) {
   constexpr int HALO = H - 1, OWN = 64 - 2 * HALO;
+  constexpr int LAG = CORR ? 2 : 1;  // rows a stage is behind the one before
   // XCD j takes one contiguous run of items, x fastest: neighbouring strips
   // share the lines at their edges in its L2.
   const unsigned nb = gridDim.x, b = blockIdx.x;
@@ -93,11 +167,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_d2q9_march(const T* __restrict_
   const uint32_t esz = sizeof(T);
   const uint32_t xs[3] = {(uint32_t)nbr(x, -1, nx, geo.bcx) * esz, (uint32_t)x * esz,
                           (uint32_t)nbr(x, 1, nx, geo.bcx) * esz};
-  // Rows: stage s computes [y0 - (H - s), y1 + (H - s)), cut at faces.
+  // Rows: stage s computes [y0 - LAG (H - s), y1 + LAG (H - s)) (with the
+  // correction it recovers one more a side), cut at faces.
   const int y0 = (int)((int64_t)ny * chunk / nchunks);
   const int y1 = (int)((int64_t)ny * (chunk + 1) / nchunks);
-  const int ylo = geo.bcy ? 0 : -H, yhi = geo.bcy ? ny - 1 : ny - 1 + H;
-  const int first = max(y0 - HALO, ylo), last = min(y1 - 1 + HALO, yhi);
+  const int ylo = geo.bcy ? 0 : -2 * H, yhi = geo.bcy ? ny - 1 : ny - 1 + 2 * H;
+  const int reach = LAG * HALO + (CORR ? 1 : 0);
+  const int first = max(y0 - reach, ylo), last = min(y1 - 1 + reach, yhi);
 
   auto load = [&](int r, T (&f)[9], T (&g)[9]) {
     const int Y = r < 0 ? r + ny : r >= ny ? r - ny : r;  // only beyond a periodic end
@@ -119,11 +195,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_d2q9_march(const T* __restrict_
 
   T nf[9], ng[9];  // the row being loaded
   Between<T> st[H - 1] = {};
+  Held<T> held[CORR ? H : 1] = {};
   int nbad = 0;
   load(first, nf, ng);
 #pragma unroll 1
-  for (int r = first; r <= y1 - 1 + HALO; ++r) {
-    T f[9], g[9];
+  for (int r = first; r <= y1 - 1 + reach; ++r) {
+    T f[9], g[9];  // pulled populations of row r - LAG (s - 1)
 #pragma unroll
     for (int a = 0; a < 9; ++a) {
       f[a] = nf[a];
@@ -132,13 +209,50 @@ __global__ __launch_bounds__(64 * kWaves) void k_d2q9_march(const T* __restrict_
     if (r < last) load(r + 1, nf, ng);
 #pragma unroll
     for (int s = 1; s <= H; ++s) {
-      const int y = r - (s - 1);  // this stage's row
-      const bool on = y >= max(y0 - (H - s), ylo) && y <= min(y1 - 1 + (H - s), yhi);
-      if (on) {
-        Sums sums;
-        const bool ok = d2q9::collide<T, false, EXT>(f, g, geo.rt, geo.ref, sums, nullptr,
-                                                     nullptr, &geo.ext);
-        if (mine && y >= y0 && y < y1) nbad += ok ? 0 : 1;
+      const int side = LAG * (H - s);
+      const int y = r - LAG * s + 1;  // the row this stage collides
+      const bool on = y >= max(y0 - side, ylo) && y <= min(y1 - 1 + side, yhi);
+      T of[9], og[9];  // its result
+      if constexpr (CORR) {
+        Held<T>& h = held[s - 1];
+        const int q = y + 1;
+        const bool fresh = q >= max(y0 - side - 1, ylo) && q <= min(y1 + side, yhi);
+        const d2q9::Recovered hrec = h.rec(geo.ref);
+        const d2q9::C7Fields own = h.fields(hrec);
+        d2q9::Recovered rec;
+        d2q9::C7Fields above = own;  // at the upper face the row stands for the next
+        if (fresh) {
+          rec = d2q9::recovered<T, EXT>(f, g, geo.ref, &geo.ext);
+          above = d2q9::c7_fields(rec.mac, rec.ok);
+        }
+#pragma unroll
+        for (int a = 0; a < 9; ++a) {
+          of[a] = h.f[a];
+          og[a] = h.g[a];
+        }
+        if (on) {
+          Sums sums;
+          const d2q9::C7Fields below = h.below();
+          const bool ok = d2q9::collide_recovered<T, true, EXT>(
+              of, og, hrec, geo.rt, geo.ref, sums, &below, &above, &geo.ext);
+          if (mine && y >= y0 && y < y1) nbad += ok ? 0 : 1;
+        }
+        if (fresh) {
+          h.set_below(geo.bcy && q == 0 ? above : own);
+          h.set(f, g, rec, above.gam);
+        }
+      } else {
+        if (on) {
+          Sums sums;
+          const bool ok = d2q9::collide<T, false, EXT>(f, g, geo.rt, geo.ref, sums, nullptr,
+                                                       nullptr, &geo.ext);
+          if (mine && y >= y0 && y < y1) nbad += ok ? 0 : 1;
+        }
+#pragma unroll
+        for (int a = 0; a < 9; ++a) {
+          of[a] = f[a];
+          og[a] = g[a];
+        }
       }
       if (s < H) {
         // Hand the row on: with its e_y = -1 the next stage completes row y - 1.
@@ -148,7 +262,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_d2q9_march(const T* __restrict_
           int ku = 0, km = 0, kd = 0;
 #pragma unroll
           for (int a = 0; a < 18; ++a) {
-            const T v = shift_in(d2q9::ex(a % 9), a < 9 ? f[a % 9] : g[a % 9]);
+            const T v = shift_in(d2q9::ex(a % 9), a < 9 ? of[a % 9] : og[a % 9]);
             if (d2q9::ey(a % 9) > 0)
               up[ku++] = v;
             else if (d2q9::ey(a % 9) == 0)
@@ -182,7 +296,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_d2q9_march(const T* __restrict_
 #pragma unroll
           for (int a = 0; a < 18; ++a) {
             if (a > 0) advance(p, geo.cs);
-            put_off<false>(p, xs[1], a < 9 ? f[a % 9] : g[a % 9]);
+            put_off<false>(p, xs[1], a < 9 ? of[a % 9] : og[a % 9]);
           }
         }
       }
@@ -192,26 +306,27 @@ __global__ __launch_bounds__(64 * kWaves) void k_d2q9_march(const T* __restrict_
 }
 
 // Blocks of a kernel that a CU holds at a time (a property of the built kernel).
-template <typename T, int H, bool EXT>
+template <typename T, int H, bool CORR, bool EXT>
 int blocks_per_cu() {
   static const int n = [] {
     int v = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &v, (const void*)&k_d2q9_march<T, H, EXT>, 64 * kWaves, 0);
+        &v, (const void*)&k_d2q9_march<T, H, CORR, EXT>, 64 * kWaves, 0);
     return e == hipSuccess && v > 0 ? v : 1;
   }();
   return n;
 }
 
 // Strips, blocks along x and number of y ranges: as many as let the blocks of a
-// launch end together (k rounds of all slots), each range costing H + 1 rows
-// more than it owns (the halo rows of the early stages and the pipeline's start).
+// launch end together (k rounds of all slots), each range costing
+// more rows than it owns (the halo rows of the early stages and the pipeline's
+// start).
 struct Plan {
   int nstrips, nbx, nchunks;
   double use;  // share of the launch's cell slots that are cells of the lattice
 };
 
-Plan plan_of(const LatticeGeom& g, int h, int64_t slots) {
+Plan plan_of(const LatticeGeom& g, int h, int more, int64_t slots) {
   const int own = 64 - 2 * (h - 1);
   Plan p{};
   p.nstrips = (g.nx + own - 1) / own;
@@ -220,7 +335,7 @@ Plan plan_of(const LatticeGeom& g, int h, int64_t slots) {
   for (int k = 1; k <= 6; ++k) {
     const int c = (int)std::max<int64_t>(1, std::min<int64_t>(k * slots / p.nbx, g.ny / 4));
     const int64_t rounds = ((int64_t)p.nbx * c + slots - 1) / slots;
-    const double cost = rounds * ((g.ny + c - 1) / c + h + 1.0);
+    const double cost = rounds * ((g.ny + c - 1) / c + more);
     if (cost < least * 0.999) {
       least = cost;
       p.nchunks = c;
@@ -230,66 +345,90 @@ Plan plan_of(const LatticeGeom& g, int h, int64_t slots) {
   return p;
 }
 
-template <typename T, int H, bool EXT>
+template <typename T, int H, bool CORR, bool EXT>
 Plan plan(const LatticeGeom& g, int cus) {
-  return plan_of(g, H, (int64_t)cus * blocks_per_cu<T, H, EXT>());
+  return plan_of(g, H, CORR ? 2 * H : H + 1, (int64_t)cus * blocks_per_cu<T, H, CORR, EXT>());
 }
 
-template <typename T, int H, bool EXT>
+template <typename T, int H, bool CORR, bool EXT>
 hipError_t launch(const void* src, void* dst, const LatticeGeom& g, int cus,
                   unsigned long long* bad, hipStream_t s) {
-  const Plan p = plan<T, H, EXT>(g, cus);
-  hipLaunchKernelGGL((k_d2q9_march<T, H, EXT>), dim3((unsigned)(p.nbx * p.nchunks)),
+  const Plan p = plan<T, H, CORR, EXT>(g, cus);
+  hipLaunchKernelGGL((k_d2q9_march<T, H, CORR, EXT>), dim3((unsigned)(p.nbx * p.nchunks)),
                      dim3(64 * kWaves), 0, s, (const T*)src, (T*)dst, g, p.nstrips, p.nbx,
                      p.nchunks, bad);
   return hipGetLastError();
 }
 
-template <typename T, int H>
-hipError_t launch_ext(bool ext, const void* src, void* dst, const LatticeGeom& g, int cus,
-                      unsigned long long* bad, hipStream_t s) {
-  return ext ? launch<T, H, true>(src, dst, g, cus, bad, s)
-             : launch<T, H, false>(src, dst, g, cus, bad, s);
+// Steps of the variants. With the correction 3 steps need a wave per SIMD to
+// itself and lose to 2 (4096^2 FP32 0.49 against 0.35 ms).
+constexpr int num_of(bool corr) { return corr ? 1 : 2; }
+constexpr int steps_of(bool corr, int v) { return corr ? 2 : v == 0 ? 4 : 3; }
+
+// fn.run<T, H, CORR, EXT>() of a form.
+template <typename T, bool CORR, bool EXT, typename F>
+auto with_form(int v, F fn) {
+  if (v == 0) return fn.template run<T, steps_of(CORR, 0), CORR, EXT>();
+  return fn.template run<T, steps_of(CORR, num_of(CORR) - 1), CORR, EXT>();
 }
 
-template <typename T>
-hipError_t dispatch(int h, bool ext, const void* src, void* dst, const LatticeGeom& g, int cus,
-                    unsigned long long* bad, hipStream_t s) {
-  switch (h) {
-    case 3: return launch_ext<T, 3>(ext, src, dst, g, cus, bad, s);
-    case 4: return launch_ext<T, 4>(ext, src, dst, g, cus, bad, s);
+template <typename T, bool CORR, typename F>
+auto with_form(int v, bool ext, F fn) {
+  return ext ? with_form<T, CORR, true>(v, fn) : with_form<T, CORR, false>(v, fn);
+}
+
+template <typename F>
+auto with_form(int precision, int v, bool corr, bool ext, F fn) {
+  if (precision)
+    return corr ? with_form<float, true>(v, ext, fn) : with_form<float, false>(v, ext, fn);
+  return corr ? with_form<double, true>(v, ext, fn) : with_form<double, false>(v, ext, fn);
+}
+
+struct Launch {
+  const void* src;
+  void* dst;
+  const LatticeGeom& g;
+  int cus;
+  unsigned long long* bad;
+  hipStream_t s;
+  template <typename T, int H, bool CORR, bool EXT>
+  hipError_t run() const {
+    return launch<T, H, CORR, EXT>(src, dst, g, cus, bad, s);
   }
-  return hipErrorInvalidValue;
-}
+};
 
-constexpr int kSteps[] = {4, 3};
-constexpr int kNum = sizeof(kSteps) / sizeof(kSteps[0]);
+struct Use {
+  const LatticeGeom& g;
+  int cus;
+  template <typename T, int H, bool CORR, bool EXT>
+  double run() const {
+    return plan<T, H, CORR, EXT>(g, cus).use;
+  }
+};
 
 }  // namespace
 
-int d2q9_num_march_variants() { return kNum; }
-int d2q9_march_steps(int v) { return kSteps[v]; }
+int d2q9_num_march_variants(bool corr) { return num_of(corr); }
+int d2q9_march_steps(int v, bool corr) { return steps_of(corr, v); }
 
-double d2q9_march_use(int precision, bool ext, const LatticeGeom& g, int cus) {
-  constexpr int H = kSteps[0];
-  if (precision) return (ext ? plan<float, H, true>(g, cus) : plan<float, H, false>(g, cus)).use;
-  return (ext ? plan<double, H, true>(g, cus) : plan<double, H, false>(g, cus)).use;
+double d2q9_march_use(int precision, bool corr, bool ext, const LatticeGeom& g, int cus) {
+  return with_form(precision, 0, corr, ext, Use{g, cus});
 }
 
 bool d2q9_march_fits(const LatticeGeom& g) { return g.ny >= 8 && (!g.bcx || g.nx >= 64); }
 
-const char* d2q9_march_kernel_name(int precision, int v) {
-  static const char* n[2][kNum] = {{"k_d2q9_march<double>/h4", "k_d2q9_march<double>/h3"},
-                                   {"k_d2q9_march<float>/h4", "k_d2q9_march<float>/h3"}};
-  return v < 0 || v >= kNum ? "?" : n[precision ? 1 : 0][v];
+const char* d2q9_march_kernel_name(int precision, int v, bool corr) {
+  static const char* n[2][3] = {
+      {"k_d2q9_march<double>/h2", "k_d2q9_march<double>/h3", "k_d2q9_march<double>/h4"},
+      {"k_d2q9_march<float>/h2", "k_d2q9_march<float>/h3", "k_d2q9_march<float>/h4"}};
+  return v < 0 || v >= num_of(corr) ? "?" : n[precision ? 1 : 0][steps_of(corr, v) - 2];
 }
 
-hipError_t d2q9_launch_march(int precision, int v, bool ext, const void* src, void* dst,
+hipError_t d2q9_launch_march(int precision, int v, bool corr, bool ext, const void* src, void* dst,
                              const LatticeGeom& g, int cus, unsigned long long* bad,
                              hipStream_t s) {
-  if (v < 0 || v >= kNum || !d2q9_march_fits(g)) return hipErrorInvalidValue;
-  return precision ? dispatch<float>(kSteps[v], ext, src, dst, g, cus, bad, s)
-                   : dispatch<double>(kSteps[v], ext, src, dst, g, cus, bad, s);
+  if (v < 0 || v >= num_of(corr) || !d2q9_march_fits(g)) return hipErrorInvalidValue;
+  return with_form(precision, v, corr, ext, Launch{src, dst, g, cus, bad, s});
 }
 
 }  // namespace rlb

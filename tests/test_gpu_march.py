@@ -149,3 +149,30 @@ def test_d2q9_march_counts_and_diagnostics():
         assert ta == tb == a.steps and np.array_equal(sa, sb)
     for x, y in zip(a.populations(), b.populations()):
         assert bool((x == y).all())
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("eta", [0.0, 0.1], ids=["fixed", "eta_s"])
+@pytest.mark.parametrize("shape,bc", PLANES, ids=["x".join(map(str, s)) for s, _ in PLANES])
+def test_d2q9_march_with_the_correction(shape, bc, eta, prec):
+    """The corrected marching kernel (a stage holds a row until the next one's
+    fields are known) against the one-step kernel that recovers both neighbours,
+    bit for bit, and that one against the oracle."""
+    prob = _plane(*shape, bc, eta)
+    prob.params.correction = 1
+    say("d2q9 march +c7", shape, bc, eta, "prec", prec)
+    ref = _run(prob, prec, 0, (7,))
+    st = oracle.run(prob, 7)
+    gs, _, bad = gpu_state(ref, prob)
+    assert bad == st.bad == 0
+    assert relmax(gs[0]["f"], st.f) < TOL[prec] and relmax(gs[0]["g"], st.g) < TOL[prec]
+    sim = _run(prob, prec, 17, (5, 2))
+    for x, y in zip(sim.populations(), ref.populations()):
+        assert bool((x == y).all())
+
+
+def test_d2q9_corrected_march_counts_inadmissible_cells():
+    prob = wl.blast_disk(136, correction=1)
+    st = oracle.run(prob, 4)
+    sim = _run(prob, FP64, 17, (4,))
+    assert sim.moments(allow_unphysical=True)["bad"] == st.bad > 50
