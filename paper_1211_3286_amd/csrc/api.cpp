@@ -281,6 +281,7 @@ struct rlb_sim {
   int cur = 0;
   bool d2 = false;  // D2Q9 model (9 velocities, 18 planes per buffer)
   bool corr = false;  // D2Q9 with the correction term of Eqs. (37)-(38)
+  bool eos = false;    // some member has a general equation of state
   bool ext = false;    // some member takes its relaxation times from eta/s per cell or
                        // has the general equation of state (the EXT kernels)
   int q = 19;
@@ -361,25 +362,32 @@ int march_steps(const rlb_sim* h, int v) {
   return h->d2 ? rlb::d2q9_march_steps(v - march_base(h), h->corr) : 2;
 }
 
-// A marching launch is the default from this share of used cells on (MarchGrid::use).
-// At full use it updates 29 G cells/s in FP32 against 18-19 of the one-step
-// kernels (FP64: 13 against 9). Both sides per step, by use: 40x40x400 FP32
-// (0.42) 40.5 against 32.7 us, 80^3 FP32 (0.59) 25.2 and 27.4, 64^3 FP64 (0.65)
-// 22.1 and 25.2, 96^3 FP32 (0.74) 34.8 and 43.1. With the extended model, whose
-// arithmetic weighs more: 96^3 FP32 (0.74) 48.5 against 45.3, 128^3 FP32 (0.85)
-// 104 and 114.
-// D2Q9, us a step against the one-step default: 700 x 500 FP32 (0.33) 10.1 and
-// 10.3, 300^2 FP32 (0.08) 7.3 and 5.9, 1000 x 800 FP32 (0.52) 15 and 20; extended:
-// 1000 x 800 FP32 (0.52) 29 and 22, FP64 (0.64) 32 and 37. With the correction:
-// 1000 x 800 FP32 (0.53) 26 and 25, 1531 x 1203 FP32 (0.69) 45 and 50, 700 x 500
-// FP64 (0.55) 18 and 21, 300^2 FP64 (0.18) 14 and 9; extended and corrected:
-// 2000 x 1800 FP32 145 and 118 (one wave per SIMD: never the default), FP64 (0.82)
-// 156 and 199.
-double least_march_use(const rlb_sim* h) {
-  if (!h->d2) return h->ext ? 0.8 : 0.6;
-  if (!h->corr) return h->ext ? 0.6 : 0.35;
-  if (h->precision == RLB_FP32) return h->ext ? 2.0 : 0.6;
-  return h->ext ? 0.7 : 0.5;
+// The marching variant that is the default from a share `use` of used cells of
+// its grid on (MarchGrid::use). us a step, marching and best one-step kernel:
+// D3Q19: 40 x 40 x 400 FP32 (use 0.42) 40.5 and 32.7, 80^3 FP32 (0.59) 25.2 and
+// 27.4, 64^3 FP64 (0.65) 22.1 and 25.2; eta/s: 80^3 FP32 (0.59) 29.2 and 28.0,
+// 60^3 FP64 (0.71) 23.1 and 22.2, 128 x 160 x 100 FP32 (0.73) 106 and 112, 160^3
+// FP32 (0.79) 195 and 208, 80^3 FP64 (0.79) 52 and 60.
+// D2Q9: 700 x 500 FP32 (0.33) 10.1 and 10.3, 300^2 FP32 (0.08) 7.3 and 5.9, 1000 x
+// 800 FP32 (0.52) 15 and 20. eta/s, where 3 steps a launch do as well as 4 at
+// 2000 x 1800 and better below: FP32 1000 x 800 (0.54) 21.4 and 21.2, 1100 x 900
+// (0.62) 23.3 and 27.1; FP64 500 x 400 (0.36) 11.2 and 11.3, 700 x 500 (0.57) 13.0
+// and 17.3. With the correction: 1000 x 800 FP32 (0.53) 26 and 25, 1531 x 1203 FP32
+// (0.69) 45 and 50, 300^2 FP64 (0.18) 14 and 9, 700 x 500 FP64 (0.55) 18 and 21; and
+// eta/s: FP64 1000 x 800 (0.63) 39.9 and 39.9, 1400 x 1000 (0.79) 59 and 92; FP32 2000 x
+// 1800 (0.82) 129 and 112 (one wave per SIMD: never the default). A general
+// equation of state repeats its root search in the halos: a higher share.
+struct MarchDefault {
+  int variant;
+  double least_use;
+};
+
+MarchDefault march_default(const rlb_sim* h) {
+  const bool fp32 = h->precision == RLB_FP32;
+  if (!h->d2) return {0, !h->ext ? 0.6 : h->eos ? 0.8 : 0.72};
+  if (h->corr) return {0, !h->ext ? (fp32 ? 0.6 : 0.5) : fp32 ? 2.0 : 0.7};
+  if (!h->ext) return {0, 0.35};
+  return {1, h->eos ? 0.7 : fp32 ? 0.56 : 0.45};
 }
 
 rlb_status launch_march(rlb_sim* h, int variant, const void* src, void* dst) {
@@ -1036,8 +1044,8 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     d.rt.s_q = 1.0 / tq;
     d.rt.s_v = 1.0 / p.tau_v;
     d.ext.eta_s = p.eta_over_s;
-    d.ext.kappa = p.kappa;
-    d.ext.dof = p.dof;
+    d.ext.visc = 3.0 * p.kappa * p.eta_over_s;
+    d.ext.inv_eq = rlb::kPiSquared / p.dof;
     d.ext.a_f = p.a_f;
     d.ext.a_e = p.a_e;
     d.ext.a_eps = p.a_eps;
@@ -1047,6 +1055,7 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     d.ext.mass = p.mass;
     d.ext.general_eos = paper_eos(p) ? 0 : 1;
     if (p.eta_over_s > 0.0 || d.ext.general_eos) h->ext = true;
+    if (d.ext.general_eos) h->eos = true;
     off += d.ncells;
   }
   if (hipDeviceGetAttribute(&h->num_cu, hipDeviceAttributeMultiprocessorCount, h->device) !=
@@ -1101,10 +1110,11 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   }
   if (h->lattice && can_march(h)) {
     if (!h->d2) h->march = rlb::march_grid(h->precision, h->geom, h->num_cu);
-    const double use =
-        h->d2 ? rlb::d2q9_march_use(h->precision, h->corr, h->ext, h->geom, h->num_cu)
-              : h->march.use;
-    if (use >= least_march_use(h)) h->variant = march_base(h);
+    const MarchDefault md = march_default(h);
+    const double use = h->d2 ? rlb::d2q9_march_use(h->precision, md.variant, h->corr, h->ext,
+                                                   h->geom, h->num_cu)
+                             : h->march.use;
+    if (use >= md.least_use) h->variant = march_base(h) + md.variant;
   }
   h->cur = 0;
   if (opt->ckpt_every > 0) {

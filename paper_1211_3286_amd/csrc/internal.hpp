@@ -327,7 +327,7 @@ int d2q9_num_march_variants(bool corr);
 int d2q9_march_steps(int variant, bool corr);
 bool d2q9_march_fits(const LatticeGeom& g);
 // Share of variant 0's cell slots that are cells of the lattice.
-double d2q9_march_use(int precision, bool corr, bool ext, const LatticeGeom& g, int cus);
+double d2q9_march_use(int precision, int variant, bool corr, bool ext, const LatticeGeom& g, int cus);
 const char* d2q9_march_kernel_name(int precision, int variant, bool corr);
 hipError_t d2q9_launch_march(int precision, int variant, bool corr, bool ext, const void* src,
                              void* dst, const LatticeGeom& g, int cus, unsigned long long* bad,

@@ -411,8 +411,8 @@ struct Use {
 int d2q9_num_march_variants(bool corr) { return num_of(corr); }
 int d2q9_march_steps(int v, bool corr) { return steps_of(corr, v); }
 
-double d2q9_march_use(int precision, bool corr, bool ext, const LatticeGeom& g, int cus) {
-  return with_form(precision, 0, corr, ext, Use{g, cus});
+double d2q9_march_use(int precision, int v, bool corr, bool ext, const LatticeGeom& g, int cus) {
+  return with_form(precision, v, corr, ext, Use{g, cus});
 }
 
 bool d2q9_march_fits(const LatticeGeom& g) { return g.ny >= 8 && (!g.bcx || g.nx >= 64); }
