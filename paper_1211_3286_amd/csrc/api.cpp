@@ -463,17 +463,21 @@ bool is_segment_variant(const rlb_sim* h, int v) {
 }
 
 // Default of the persistent path. us a step, the choice against the one-block
-// member kernel (512 threads), which keeps members of up to 1024 cells (one or
-// two passes of its block):
+// member kernel (512 threads), which keeps members of up to 512 cells (one pass
+// of its block), D2Q9 ones of up to 1024 (32^2 FP32 3.4 against 3.7) and batches
+// of members of up to 1024 cells that fill the chip (300 of 10^3 FP32 16 and 19):
 //   1 x 1 x L tubes: rounds of 16 steps; L = 100 FP32 1.9 against 2.9, 800 2.4
 //     and 7.1, 64 ragged ones up to 3200 4.0 and 30 (FP64 1.8 and 2.8, 2.3 and
 //     9.3, 5.0 and 32);
 //   narrow D2Q9 members: strip rounds of 8 steps, if windows of 256 cells leave
 //     an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
-//   the rest: one launch per step; 16^3 FP32 4.1 and 29, 24^3 5.1 and 115, 120^2
-//     D2Q9 3.3 and 41; 64-thread blocks until they fill the chip.
-constexpr int64_t kMemberCells = 1024, kStripCells = 256;
-constexpr int kSmallBlocks = 4096;
+//   the rest: one launch per step; 9^3 FP32 4.1 and 6.4, 16^3 3.8 and 29, 24^3 4.2
+//     and 115, 120^2 D2Q9 3.3 and 41. Blocks of 64 cells until they fill the chip:
+//     D3Q19, where they run a thread per distribution, 864 blocks FP64 9.6 us
+//     and 10.2 of 256-cell blocks, 1728 blocks FP64 15.1 and 12.9, FP32 10.0 and
+//     10.2; D2Q9 up to 4096 blocks.
+constexpr int64_t kMemberCells = 512, kMemberCellsFull = 1024, kStripCells = 256;
+constexpr int kFullBlocks = 2048;
 
 int cells_base(const rlb_sim* h);
 
@@ -487,8 +491,9 @@ int default_persistent(const rlb_sim* h) {
     for (const rlb_params& p : h->params) fits = fits && (int64_t)p.nx * rows <= t.nt;
     if (fits) return rlb::d2q9_num_member_variants() + v;
   }
-  if (h->L.max_member <= kMemberCells) return 1;
-  return cells_base(h) + (h->L.blocks[0] <= kSmallBlocks ? 0 : 1);
+  const bool full = h->d2 || h->L.blocks[0] > kFullBlocks;
+  if (h->L.max_member <= (full ? kMemberCellsFull : kMemberCells)) return 1;
+  return cells_base(h) + (h->L.blocks[0] <= rlb::small_blocks(h->d2) ? 0 : 1);
 }
 
 // First of the one-launch-per-step variants, which follow the others.
@@ -733,7 +738,7 @@ rlb_status launch_persistent(rlb_sim* h, int variant, int nsteps, int pingpong, 
       const bool diag =
           diag_every > 0 && ((step0 + t + 1) % diag_every == 0 || t == nsteps - 1);
       RLB_HIP(rlb::launch_step_cells(h->precision, h->d2, cv, h->corr, h->ext, diag, m,
-                                     h->n_members, h->L.blocks[cv], h->stream));
+                                     h->descs[0], h->n_members, h->L.blocks[cv], h->stream));
     }
     return RLB_OK;
   }

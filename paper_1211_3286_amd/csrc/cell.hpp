@@ -270,12 +270,13 @@ __device__ __forceinline__ double four_minus_log(double x) {
 // tau_v = inf) does not relax: the limit keeps its reciprocals finite.
 //
 // This is serial FP64 work in every cell and step, and what bounds kernels of
-// the extended model. Written as printed above, with thirteen IEEE divisions
-// and the library's logarithm, it took 1100 of a wave's 5000 clocks a step; in
-// this form about 500. Against 80-bit arithmetic over n, P, u, eta/s of ten
-// decades its rates are as near as those of the long form (at most 5e-16, mean
-// 1e-16). 160^3 FP32 216 and 190 us a step; the four Cases of 4 x 800 FP64 cells
-// 17 and 14.5 us per 8 steps.
+// the extended model. Written as printed above, with thirteen IEEE divisions and
+// the library's logarithm, it took about 1100 of a wave's 5000 clocks a step; in
+// this form about 500. Against 80-bit arithmetic over random states (T 1e-2 to 1,
+// P 1e-9 to 10, |u| up to 0.99) both forms' rates are off by 1.5e-16 in the mean,
+// by 1.5e-13 (long form) and 0.8e-13 at most, where 4 - ln lambda cancels. One
+// step of 160^3 FP32 (one-step kernel) 235 and 208 us, of 1000 x 800 D2Q9 FP64
+// (marching) 32 and 26; 8 steps of the four Cases of 4 x 800 cells, FP64, 17 and 14.
 __device__ __forceinline__ Rates local_rates(const Rates& rt, const Ext& v, double N,
                                              const Macro& m) {
   const double n = N * root01(1.0 - m.u2);
@@ -559,6 +560,30 @@ __device__ __forceinline__ bool collide_g_only(C (&g)[19], const Rates& rt, cons
   Macro mac;
   if (!recover(E, Mx, My, Mz, mac)) return false;
   collide_g(g, Mx, My, Mz, gs, mac, rt, ref);
+  return true;
+}
+
+// Either half of collide() alone, bit for bit: f (F) or g, from a cell's
+// populations. Both need the recovery; g reads f only in the extended model.
+// sums as in collide(), of the f half.
+template <typename C, bool EXT, bool F>
+__device__ __forceinline__ bool collide_half(C (&f)[19], C (&g)[19], const Rates& rt,
+                                             const Ref& ref, Sums& sums, const Ext& ext) {
+  double N = 0.0, E, Mx, My, Mz, fs = 0.0, gs;
+  if constexpr (F || EXT)
+    cell_sums(f, g, ref, N, E, Mx, My, Mz, fs, gs);
+  else
+    g_sums(g, ref, E, Mx, My, Mz, gs);
+  sums = {{N, E, Mx, My, Mz}};
+  Macro mac;
+  if (!(EXT ? recover_model(N, E, Mx, My, Mz, ext, mac) : recover(E, Mx, My, Mz, mac)))
+    return false;
+  Rates r = rt;
+  if constexpr (EXT) r = local_rates(rt, ext, N, mac);
+  if constexpr (F)
+    collide_f(f, N, fs, mac, r, ref);
+  else
+    collide_g(g, Mx, My, Mz, gs, mac, r, ref);
   return true;
 }
 

@@ -170,8 +170,11 @@ hipError_t member_kernel(int precision, int variant, bool ext, const void** func
 // One launch per step over all members, one cell per thread (cells.hip);
 // variants: 64 or 256 threads a block. Reads a.bufA, writes a.bufB.
 constexpr int kNumCells = 2;
+// Blocks of 64 cells up to which a k_*_cells launch takes them.
+constexpr int small_blocks(bool d2) { return d2 ? 4096 : 1000; }
 hipError_t launch_step_cells(int precision, bool d2, int variant, bool corr, bool ext, bool diag,
-                             const MemberLaunch& a, int n_members, int nblocks, hipStream_t s);
+                             const MemberLaunch& m, const MemberDesc& first, int n_members,
+                             int nblocks, hipStream_t s);
 const char* cells_kernel_name(int precision, bool d2, int variant);
 
 // Segmented persistent step: every member is cut into segments of whole

@@ -22,8 +22,6 @@ static __device__ __align__(256) unsigned char scratch[RLB_NOALLOC_SCRATCH_BYTES
 
 constexpr int kMaxDevices = 64;
 constexpr size_t kAlign = 256;
-// Lattices up to this size take 64-thread blocks (they leave CUs idle otherwise).
-constexpr int64_t kSmallCells = 64 * 4096;
 
 struct DeviceSlot {
   std::mutex mu;           // one call at a time per device: the array is shared
@@ -162,7 +160,7 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
             : rlb::launch_init(o.precision, buf[0], lay, d_desc, 1, n0, eps0, u0, nc, st));
 
   // steps (rlb_step): one launch per step
-  const int variant = nc <= kSmallCells ? 0 : 1;
+  const int variant = nc <= 64 * (int64_t)rlb::small_blocks(d2) ? 0 : 1;
   const int blocks = (int)(variant ? (nc + 255) / 256 : (nc + 63) / 64);
   rlb::MemberLaunch m{};
   m.descs = d_desc;
@@ -173,8 +171,8 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
   for (int32_t i = 0; i < nsteps; ++i) {
     m.bufA = buf[cur];
     m.bufB = buf[1 - cur];
-    NA_HIP(rlb::launch_step_cells(o.precision, d2, variant, o.correction != 0, ext, false, m, 1,
-                                  blocks, st));
+    NA_HIP(rlb::launch_step_cells(o.precision, d2, variant, o.correction != 0, ext, false, m, desc,
+                                  1, blocks, st));
     cur = 1 - cur;
   }
 
