@@ -463,26 +463,41 @@ bool is_segment_variant(const rlb_sim* h, int v) {
 }
 
 // Default of the persistent path. us a step, the choice against the one-block
-// member kernel (512 threads), which keeps members of up to 512 cells (one pass
-// of its block), D2Q9 ones of up to 1024 (32^2 FP32 3.4 against 3.7) and batches
-// of members of up to 1024 cells that fill the chip (300 of 10^3 FP32 16 and 19):
-//   1 x 1 x L tubes: rounds of 16 steps; L = 100 FP32 1.9 against 2.9, 800 2.4
-//     and 7.1, 64 ragged ones up to 3200 4.0 and 30 (FP64 1.8 and 2.8, 2.3 and
-//     9.3, 5.0 and 32);
+// member kernel (512 threads), which keeps members of up to 1024 cells, one or two
+// passes of its block (9^3 FP32 6.4 against 4.1, but 300 of 10^3 16 and 19):
+//   1 x 1 x L tubes: rounds. Windows of 128 cells with a thread per distribution
+//     while every segment has a CU, 32 steps a round (64 owned cells), else 16
+//     (96), and for tubes that one window holds; else windows of 256 cells, 16
+//     steps. By these three: 800 cells FP64 1.2, 1.3 and 1.7 (member kernel 9.3),
+//     24 of 800 1.9, 1.4 and 1.8, 64 of up to 1500 FP32 3.0, 2.6 and 2.7, 200 of
+//     1500 10.6, 8.0 and 6.6; 1500 tubes of 100 cells FP64 4.2 and 5.8;
 //   narrow D2Q9 members: strip rounds of 8 steps, if windows of 256 cells leave
 //     an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
-//   the rest: one launch per step; 9^3 FP32 4.1 and 6.4, 16^3 3.8 and 29, 24^3 4.2
-//     and 115, 120^2 D2Q9 3.3 and 41. Blocks of 64 cells until they fill the chip:
-//     D3Q19, where they run a thread per distribution, 864 blocks FP64 9.6 us
-//     and 10.2 of 256-cell blocks, 1728 blocks FP64 15.1 and 12.9, FP32 10.0 and
-//     10.2; D2Q9 up to 4096 blocks.
-constexpr int64_t kMemberCells = 512, kMemberCellsFull = 1024, kStripCells = 256;
-constexpr int kFullBlocks = 2048;
+//   the rest: one launch per step; 16^3 FP32 3.8 and 29, 24^3 4.2 and 115, 120^2
+//     D2Q9 3.3 and 41. Blocks of 64 cells until they fill the chip: D3Q19, where
+//     they run a thread per distribution, 864 blocks FP64 9.6 us and 10.2 of
+//     256-cell blocks, 1728 blocks FP64 15.1 and 12.9, FP32 10.0 and 10.2; D2Q9
+//     up to 4096 blocks.
+constexpr int64_t kMemberCells = 1024, kStripCells = 256;
 
 int cells_base(const rlb_sim* h);
 
+// The widest halo whose segments each find a CU, of the split windows; else 1.
+int default_tube(const rlb_sim* h) {
+  for (const int v : {6, 5}) {
+    const rlb::TubeVariant t = rlb::tube_variant(v);
+    if (h->L.max_member <= t.nt) return v;
+    int64_t n = 0;
+    for (const rlb_params& p : h->params)
+      n += p.nz <= t.nt ? 1 : (p.nz + t.nt - 2 * t.halo - 1) / (t.nt - 2 * t.halo);
+    if (n <= h->num_cu) return v;
+  }
+  return 1;
+}
+
 int default_persistent(const rlb_sim* h) {
-  if (h->all_tubes) return rlb::num_member_variants() + rlb::num_segment_variants() + 1;
+  if (h->all_tubes)
+    return rlb::num_member_variants() + rlb::num_segment_variants() + default_tube(h);
   if (h->d2 && h->L.max_member > kStripCells) {
     const int v = 3;
     const rlb::TubeVariant t = rlb::d2q9_strip_variant(v);
@@ -491,8 +506,7 @@ int default_persistent(const rlb_sim* h) {
     for (const rlb_params& p : h->params) fits = fits && (int64_t)p.nx * rows <= t.nt;
     if (fits) return rlb::d2q9_num_member_variants() + v;
   }
-  const bool full = h->d2 || h->L.blocks[0] > kFullBlocks;
-  if (h->L.max_member <= (full ? kMemberCellsFull : kMemberCells)) return 1;
+  if (h->L.max_member <= kMemberCells) return 1;
   return cells_base(h) + (h->L.blocks[0] <= rlb::small_blocks(h->d2) ? 0 : 1);
 }
 
@@ -1013,15 +1027,17 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   h->all_tubes = !h->d2;
   for (int i = 0; i < n_members; ++i)
     if (members[i].nx != 1 || members[i].ny != 1) h->all_tubes = false;
-  // default of the lattice path where nothing marches: the 256 x 1 block, or
-  // with the correction the 64 x 4 one, which shares the neighbours' fields
-  // (1531 x 1203 FP64 128 us a step against 135, FP32 50 against 70)
-  h->variant = h->lattice ? (h->d2 ? (h->corr ? 3 : 2) : 3) : default_persistent(h);
-
   auto fail = [&](rlb_status s) {
     delete h;
     return s;
   };
+  if (hipDeviceGetAttribute(&h->num_cu, hipDeviceAttributeMultiprocessorCount, h->device) !=
+      hipSuccess)
+    return fail(RLB_E_DEVICE);
+  // default of the lattice path where nothing marches: the 256 x 1 block, or
+  // with the correction the 64 x 4 one, which shares the neighbours' fields
+  // (1531 x 1203 FP64 128 us a step against 135, FP32 50 against 70)
+  h->variant = h->lattice ? (h->d2 ? (h->corr ? 3 : 2) : 3) : default_persistent(h);
   // member descriptors (refs are filled on the device)
   h->descs.resize(n_members);
   int64_t off = 0;
@@ -1063,9 +1079,6 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     if (d.ext.general_eos) h->eos = true;
     off += d.ncells;
   }
-  if (hipDeviceGetAttribute(&h->num_cu, hipDeviceAttributeMultiprocessorCount, h->device) !=
-      hipSuccess)
-    return fail(RLB_E_DEVICE);
   // The whole start is enqueued and its one answer read back at the end: the
   // refused cells and the reference the lattice kernels take as an argument.
   const double *dn, *de, *du;

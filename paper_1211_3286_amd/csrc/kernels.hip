@@ -185,21 +185,44 @@ __global__ __launch_bounds__(NT) void k_step_segments(SegLaunch a) {
 }
 
 // -------------------------------------------------------------------------
-// Tube rounds: one block per TubeSeg, one thread per window cell, all
-// populations of the window in LDS as [38][NT] (consecutive threads touch
-// consecutive words). Per step: every thread pulls its 38 values from the
-// LDS neighbours (a 1 x 1 x L lattice streams only along z: the x and y
-// components of e wrap onto the same cell), barrier, collides in registers,
-// writes them back to its own slot, barrier. Inadmissible counts and
+// Tube rounds: one block per TubeSeg. A 1 x 1 x L lattice streams only along z:
+// the x and y components of e wrap onto the same cell, so a thread keeps its
+// cell's populations with e_z = 0 and exchanges the others through LDS, planes of
+// NT consecutive words. SPLIT: two threads per window cell, in different waves,
+// one for f and one for g. The f thread also reads the cell's whole g for the
+// recovery, and in the extended model the g thread its f. Per step: pull,
+// barrier, collide in registers, write, barrier. Inadmissible counts and
 // diagnostics cover owned cells only (halo cells are computed twice). EXT:
 // relaxation times from eta/s and the general equation of state, per cell.
+//
+// Bound by the serial chain of a step, 5-6 clocks an instruction where a SIMD has
+// one wave (a tube of 800 cells is four blocks), and by the chip's issue rate
+// for batches that fill it: the split shortens the first (850 to some 500
+// instructions) and leaves the second as it was, as only the sums and the
+// recovery are done twice. Windows of 512 cells stay whole: 16 waves leave 128
+// registers to each, too few for a split FP64 cell; those of 256 because batches
+// take them. 800 cells FP64, us a step: one thread with all 38 values exchanged
+// 2.0 (rounds of 16 steps), this split 1.3, with rounds of 32 1.2; 64 tubes of up to
+// 3200 cells, FP64 4.8 and, whole, 4.3.
 // -------------------------------------------------------------------------
-template <typename T, int NT, bool EXT>
-__global__ __launch_bounds__(NT) void k_step_tubes(TubeRound a) {
-  __shared__ T lds[38][NT];
+template <bool EXT>
+struct TubePlanes {
+  // LDS planes: g, then f; without EXT nobody reads another cell's f with e_z = 0
+  static constexpr int n = EXT ? 38 : 29;
+  static constexpr int f(int q) {
+    int k = 19;
+    for (int i = 0; i < q; ++i) k += EXT || ez(i) != 0 ? 1 : 0;
+    return k;
+  }
+};
+
+// The work of a thread on the distributions it has (F: f, G: g).
+template <typename T, int NT, bool EXT, bool F, bool G>
+__device__ __forceinline__ void tube_cell(const TubeRound& a, T (*__restrict__ lds)[NT], int w) {
+  using P = TubePlanes<EXT>;
+  constexpr int kThreads = F && G ? NT : 2 * NT;
   const TubeSeg sg = a.segs[blockIdx.x];
   const MemberDesc d = a.descs[sg.member];
-  const int w = threadIdx.x;
   const int L = d.nz;
   const bool live = w < sg.wlen;
   const int own_lo = sg.own0 - sg.win0, own_hi = sg.own1 - sg.win0;
@@ -209,9 +232,21 @@ __global__ __launch_bounds__(NT) void k_step_tubes(TubeRound a) {
   if (z < 0) z += L;
   if (z >= L) z -= L;
   const int64_t gi = d.offset + z;
+  T f[19] = {}, g[19] = {};
+  const auto leave = [&]() {
+#pragma unroll
+    for (int q = 0; q < 19; ++q) {
+      if (G && (!F || ez(q) != 0)) lds[q][w] = g[q];
+      if (F && ((EXT && !G) || ez(q) != 0)) lds[P::f(q)][w] = f[q];
+    }
+  };
   if (live) {
 #pragma unroll
-    for (int p = 0; p < 38; ++p) lds[p][w] = ((const T*)a.src)[p * a.cs + gi];
+    for (int q = 0; q < 19; ++q) {
+      if (F) f[q] = ((const T*)a.src)[q * a.cs + gi];
+      if (G) g[q] = ((const T*)a.src)[(19 + q) * a.cs + gi];
+    }
+    leave();
   }
   // pull sources inside the window for e_z = +1 (from w-1) and e_z = -1 (from w+1)
   int sp = w - 1, sm = w + 1;
@@ -220,42 +255,36 @@ __global__ __launch_bounds__(NT) void k_step_tubes(TubeRound a) {
   if (!live) sp = sm = 0;
   __syncthreads();
   int nbad = 0;
-  double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   for (int t = 0; t < a.nsteps; ++t) {
-    T f[19], g[19];
     if (live) {
 #pragma unroll
       for (int q = 0; q < 19; ++q) {
         const int src = ez(q) > 0 ? sp : (ez(q) < 0 ? sm : w);
-        f[q] = lds[q][src];
-        g[q] = lds[19 + q][src];
+        if (!G || ez(q) != 0) g[q] = lds[q][src];
+        if (F ? ez(q) != 0 : EXT) f[q] = lds[P::f(q)][src];
       }
     }
     __syncthreads();
     const int64_t sidx = a.step0 + t + 1;
     const bool diag =
         a.diag_every > 0 && ((sidx % a.diag_every) == 0 || sidx == a.last_step);
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (live) {
       Sums s;
-      const bool ok = collide<T, EXT>(f, g, d.rt, d.ref, s, &d.ext);
-      if (owned) {
-        nbad += ok ? 0 : 1;
-        if (diag)
+      bool ok;
+      if constexpr (F && G)
+        ok = collide<T, EXT>(f, g, d.rt, d.ref, s, &d.ext);
+      else
+        ok = collide_half<T, EXT, F>(f, g, d.rt, d.ref, s, d.ext);
+      if (G && owned) nbad += ok ? 0 : 1;
+      if (F && owned && diag)
 #pragma unroll
-          for (int i = 0; i < 5; ++i) acc[i] = s.v[i];
-      }
-#pragma unroll
-      for (int q = 0; q < 19; ++q) {
-        lds[q][w] = f[q];
-        lds[19 + q][w] = g[q];
-      }
+        for (int i = 0; i < 5; ++i) acc[i] = s.v[i];
+      leave();
     }
     if (diag) {
-      if (!owned)
-#pragma unroll
-        for (int i = 0; i < 5; ++i) acc[i] = 0.0;
-      block_sum5<NT>(acc, w);
-      if (w == 0)
+      block_sum5<kThreads>(acc, threadIdx.x);
+      if (threadIdx.x == 0)
 #pragma unroll
         for (int i = 0; i < 5; ++i) a.partials[(int64_t)blockIdx.x * 5 + i] = acc[i];
     }
@@ -263,9 +292,25 @@ __global__ __launch_bounds__(NT) void k_step_tubes(TubeRound a) {
   }
   if (owned) {
 #pragma unroll
-    for (int p = 0; p < 38; ++p) ((T*)a.dst)[p * a.cs + gi] = lds[p][w];
+    for (int q = 0; q < 19; ++q) {
+      if (F) ((T*)a.dst)[q * a.cs + gi] = f[q];
+      if (G) ((T*)a.dst)[(19 + q) * a.cs + gi] = g[q];
+    }
   }
   if (nbad) count_bad(a.bad, nbad);
+}
+
+constexpr bool tube_split(int nt) { return nt <= 128; }
+
+template <typename T, int NT, bool EXT>
+__global__ __launch_bounds__(tube_split(NT) ? 2 * NT : NT) void k_step_tubes(TubeRound a) {
+  __shared__ T lds[TubePlanes<EXT>::n][NT];
+  if constexpr (!tube_split(NT))
+    tube_cell<T, NT, EXT, true, true>(a, lds, threadIdx.x);
+  else if (__builtin_amdgcn_readfirstlane(threadIdx.x) >= NT)
+    tube_cell<T, NT, EXT, true, false>(a, lds, (int)threadIdx.x - NT);
+  else
+    tube_cell<T, NT, EXT, false, true>(a, lds, threadIdx.x);
 }
 
 __device__ __forceinline__ int find_member(const MemberDesc* __restrict__ d, int n, int64_t c) {
@@ -491,7 +536,8 @@ const void* seg_func(int v) {
   return nullptr;
 }
 
-constexpr TubeVariant kTube[] = {{256, 8}, {256, 16}, {512, 16}, {512, 32}, {128, 8}};
+constexpr TubeVariant kTube[] = {{256, 8}, {256, 16}, {512, 16}, {512, 32},
+                                 {128, 8}, {128, 16}, {128, 32}};
 constexpr int kNumTube = sizeof(kTube) / sizeof(kTube[0]);
 
 template <typename T, bool EXT>
@@ -501,7 +547,7 @@ const void* tube_func(int v) {
     case 1: return (const void*)&k_step_tubes<T, 256, EXT>;
     case 2: return (const void*)&k_step_tubes<T, 512, EXT>;
     case 3: return (const void*)&k_step_tubes<T, 512, EXT>;
-    case 4: return (const void*)&k_step_tubes<T, 128, EXT>;
+    case 4: case 5: case 6: return (const void*)&k_step_tubes<T, 128, EXT>;
   }
   return nullptr;
 }
@@ -537,17 +583,19 @@ hipError_t tube_kernel(int precision, int v, bool ext, const void** func, dim3* 
     *func = precision ? tube_func<float, true>(v) : tube_func<double, true>(v);
   else
     *func = precision ? tube_func<float, false>(v) : tube_func<double, false>(v);
-  *block = dim3(kTube[v].nt, 1, 1);
+  *block = dim3((tube_split(kTube[v].nt) ? 2 : 1) * kTube[v].nt, 1, 1);
   return hipSuccess;
 }
 
 const char* tube_kernel_name(int precision, int v) {
   static const char* n32[] = {"k_step_tubes<float,256>/h8", "k_step_tubes<float,256>/h16",
                               "k_step_tubes<float,512>/h16", "k_step_tubes<float,512>/h32",
-                              "k_step_tubes<float,128>/h8"};
+                              "k_step_tubes<float,128>/h8", "k_step_tubes<float,128>/h16",
+                              "k_step_tubes<float,128>/h32"};
   static const char* n64[] = {"k_step_tubes<double,256>/h8", "k_step_tubes<double,256>/h16",
                               "k_step_tubes<double,512>/h16", "k_step_tubes<double,512>/h32",
-                              "k_step_tubes<double,128>/h8"};
+                              "k_step_tubes<double,128>/h8", "k_step_tubes<double,128>/h16",
+                              "k_step_tubes<double,128>/h32"};
   if (v < 0 || v >= kNumTube) return "?";
   return precision ? n32[v] : n64[v];
 }

@@ -79,13 +79,13 @@ def test_every_variant_equals_the_member_kernel(batch, prec):
 
 
 def test_default_variants():
-    """Members of up to 512 cells (1024 on D2Q9) stay on the one-block kernel, tubes
-    and narrow D2Q9 members take rounds, the rest one launch per step."""
+    """Members of up to 1024 cells stay on the one-block kernel, tubes and narrow
+    D2Q9 members take rounds, the rest one launch per step."""
     import paper_1211_3286_amd as rlb
     for probs, want in (
-            ([wl.random_modes(8, 8, 8, seed=1)], "k_step_members<double,512,1>"),
-            ([wl.random_modes(3, 9, 19, seed=1)], "k_step_cells<double,64>"),
-            ([_tube(300, 1, 1), _tube(50, 0, 2)], "k_step_tubes<double,256>/h16"),
+            ([wl.random_modes(8, 8, 16, seed=1)], "k_step_members<double,512,1>"),
+            ([wl.random_modes(5, 5, 41, seed=1)], "k_step_cells<double,64>"),
+            ([_tube(300, 1, 1), _tube(50, 0, 2)], "k_step_tubes<double,128>/h32"),
             ([_plane(15, 100, (0, 1, 0))], "k_d2q9_strips<double,256>/h8"),
             ([_plane(16, 100, (0, 1, 0))], "k_d2q9_cells<double,64>"),
             ([_plane(7, 100, (0, 1, 0), 1)], "k_d2q9_strips<double,256>/h8+c7"),
