@@ -301,6 +301,7 @@ struct rlb_sim {
   int seg_built = -1;             // variant the device segment table describes (segments:
                                   // sv; tube rounds: 1000 + tv; strip rounds: 2000 + sv)
   bool seg_whole = false;         // tube or strip segments: every member is one, whole
+  int seg_halo = 0;               // else the steps of a round
   bool all_tubes = false;
   int nseg = 0;
   int num_cu = 0;
@@ -471,8 +472,8 @@ bool is_segment_variant(const rlb_sim* h, int v) {
 //     steps. By these three: 800 cells FP64 1.2, 1.3 and 1.7 (member kernel 9.3),
 //     24 of 800 1.9, 1.4 and 1.8, 64 of up to 1500 FP32 3.0, 2.6 and 2.7, 200 of
 //     1500 10.6, 8.0 and 6.6; 1500 tubes of 100 cells FP64 4.2 and 5.8;
-//   narrow D2Q9 members: strip rounds of 8 steps, if windows of 256 cells leave
-//     an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
+//   narrow D2Q9 members: strip rounds of 8 or 16 steps, if windows of 256 cells
+//     leave an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
 //   the rest: one launch per step; 16^3 FP32 3.8 and 29, 24^3 4.2 and 115, 120^2
 //     D2Q9 3.3 and 41. Blocks of 64 cells until they fill the chip: D3Q19, where
 //     they run a thread per distribution, 864 blocks FP64 9.6 us and 10.2 of
@@ -575,8 +576,23 @@ rlb_status build_tube_segments(rlb_sim* h, int tv) {
   RLB_HIP(hipStreamSynchronize(h->stream));
   h->nseg = (int)segs.size();
   h->seg_whole = h->nseg == h->n_members;  // a cut member has two or more
+  h->seg_halo = v.halo;
   h->seg_built = 1000 + tv;
   return RLB_OK;
+}
+
+// A strip round takes twice its H steps where windows with that halo still own a
+// row and every segment finds a CU: a launch costs as much as two steps (eta/s,
+// FP64, by H = 8 and 16 of 256 threads: 4 members of 4 x 800 cells, 100 segments,
+// 1.9 and 1.6 us a step; 12 of them, 300 segments, 2.0 and 2.4).
+bool doubled_strips_fit(const rlb_sim* h, const rlb::TubeVariant& v) {
+  int64_t n = 0;
+  for (const rlb_params& p : h->params) {
+    const int R = v.nt / p.nx, S = R - 4 * v.halo * (h->corr ? 2 : 1);
+    if (p.ny > R && S < 1) return false;
+    n += p.ny > R ? (p.ny + S - 1) / S : 1;
+  }
+  return n <= h->num_cu;
 }
 
 // D2Q9 strip segments for a strip variant: windows of R = nt / nx rows, H
@@ -585,7 +601,8 @@ rlb_status build_tube_segments(rlb_sim* h, int tv) {
 // RLB_E_UNSUPPORTED when a member is wider than the block or leaves no
 // owned row.
 rlb_status build_strip_segments(rlb_sim* h, int sv) {
-  const rlb::TubeVariant v = rlb::d2q9_strip_variant(sv);
+  rlb::TubeVariant v = rlb::d2q9_strip_variant(sv);
+  if (doubled_strips_fit(h, v)) v.halo *= 2;
   const int hr = h->corr ? 2 * v.halo : v.halo;
   std::vector<rlb::TubeSeg> segs;
   for (int m = 0; m < h->n_members; ++m) {
@@ -627,6 +644,7 @@ rlb_status build_strip_segments(rlb_sim* h, int sv) {
   RLB_HIP(hipStreamSynchronize(h->stream));
   h->nseg = (int)segs.size();
   h->seg_whole = h->nseg == h->n_members;  // a cut member has two or more
+  h->seg_halo = v.halo;
   h->seg_built = 2000 + sv;
   return RLB_OK;
 }
@@ -642,7 +660,6 @@ rlb_status build_strip_segments(rlb_sim* h, int sv) {
 // kernel.)
 rlb_status launch_tubes(rlb_sim* h, int variant, int nsteps, int pingpong, void* a, void* b,
                         int diag_every, int64_t step0, bool* flip) {
-  rlb::TubeVariant v;
   const void* func;
   dim3 block;
   if (h->d2) {
@@ -651,7 +668,6 @@ rlb_status launch_tubes(rlb_sim* h, int variant, int nsteps, int pingpong, void*
       rlb_status st = build_strip_segments(h, sv);
       if (st != RLB_OK) return st;
     }
-    v = rlb::d2q9_strip_variant(sv);
     RLB_HIP(rlb::d2q9_strip_kernel(h->precision, sv, h->corr, h->ext, &func, &block));
   } else {
     const int tv = tube_index(variant);
@@ -660,10 +676,9 @@ rlb_status launch_tubes(rlb_sim* h, int variant, int nsteps, int pingpong, void*
       rlb_status st = build_tube_segments(h, tv);
       if (st != RLB_OK) return st;
     }
-    v = rlb::tube_variant(tv);
     RLB_HIP(rlb::tube_kernel(h->precision, tv, h->ext, &func, &block));
   }
-  const int per = h->seg_whole ? nsteps : v.halo;
+  const int per = h->seg_whole ? nsteps : h->seg_halo;
   const int rounds = (nsteps + per - 1) / per;
   rlb::TubeRound arg{};
   arg.descs = h->d_descs;

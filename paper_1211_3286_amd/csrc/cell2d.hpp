@@ -236,15 +236,6 @@ __device__ __forceinline__ C7Fields c7_fields(const Macro& m, bool ok) {
   return F;
 }
 
-// FP64 reciprocal: the hardware estimate refined by two Newton-Raphson steps
-// (each squares the relative error), within an ulp or two of the IEEE
-// quotient at a fraction of the instructions of a full division.
-__device__ __forceinline__ double rcp_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
-}
-
 // Eq. (10) with P = eps/3 in the plane: the subluminal root
 // u = 3 M / (2E + sqrt(4E^2 - 3|M|^2)), sigma = 4E / (3 + u^2),
 // P = sigma (1 - u^2) / 4; admissible iff E > 0 and |M| < E.
@@ -253,12 +244,12 @@ __device__ __forceinline__ bool recover_xy(double E, double Mx, double My, Macro
   const bool ok = (E > 0.0) && (M2 < E * E);
   const double Es = ok ? E : 1.0;
   const double M2s = ok ? M2 : 0.0;
-  const double q = 3.0 * rcp_nr(2.0 * Es + sqrt(4.0 * Es * Es - 3.0 * M2s));
+  const double q = 3.0 * recip(2.0 * Es + sqrt(4.0 * Es * Es - 3.0 * M2s));
   m.ux = ok ? q * Mx : 0.0;
   m.uy = ok ? q * My : 0.0;
   m.uz = 0.0;
   m.u2 = m.ux * m.ux + m.uy * m.uy;
-  m.sigma = 4.0 * Es * rcp_nr(3.0 + m.u2);
+  m.sigma = 4.0 * Es * recip(3.0 + m.u2);
   m.P = 0.25 * m.sigma * (1.0 - m.u2);
   return ok;
 }
