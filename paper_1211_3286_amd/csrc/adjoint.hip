@@ -10,9 +10,18 @@
 // in the interior, up to four at clamped corners, never an atomic), applies
 // the transposed collision Jacobian (adjoint_cell.hpp) and writes 19 values:
 // 3 x 19 populations of traffic per cell-step. dL/dtau is accumulated in FP64
-// per block across all steps and reduced once at the end. The whole reverse
-// sweep is one HIP graph in which the recomputation of the next segment runs
-// beside the reverse steps of the current one (two segment buffers).
+// per block across all steps and reduced once at the end. A launch runs one
+// reverse step of a segment together with one recomputed step of the segment
+// before it (two segment buffers), the blocks of both taking turns.
+//
+// Bound by memory and, in the reverse step, by FP64 arithmetic as much: 100
+// populations' traffic per cell and step, at 512 x 512 FP32 20 MB a g state that
+// the last-level cache holds: a pair of steps takes 21 us, 4.8 TB/s. (As separate
+// kernels on two branches of a graph they ran one after the other, 13.5 and 8.2
+// us, behind the building of the graph for each new handle.) Forward and
+// backward, 512 x 512 FP32 200 steps 8.2 and now 7.8 ms; smaller lattices are
+// bound by the launches, of which there are half as many: 150 x 170 FP32 60 steps
+// 1.6 and 1.1 ms, 100 x 90 FP64 80 steps 1.9 and 1.2.
 
 #include <hip/hip_runtime.h>
 
@@ -67,10 +76,9 @@ __device__ __forceinline__ void decompose(int c, const G& d, int& x, int& y, int
 // The step kernels' geometry: each wave takes 64 consecutive x-cells of one
 // row (y, z), a block kRows rows, one cell per thread. The row index is
 // uniform in a wave, so (y, z) come from a scalar division and no cell index
-// is divided; with no loop over cells the reverse step fits 101 VGPRs (4
-// waves per SIMD: a 512 x 512 step in one round of waves).
+// is divided; with no loop over cells the reverse step fits 117 VGPRs (4
+// waves per SIMD).
 constexpr int kRows = 4;
-constexpr int64_t kMaxGridY = 65535;
 
 // The 8 XCDs of the chip take the blocks of a launch in turn (block b on XCD
 // b mod 8), each XCD behind its own L2. Taken as launched, the 8 blocks of a
@@ -81,29 +89,21 @@ constexpr int64_t kMaxGridY = 65535;
 // whole rows: no row is split over XCDs.
 constexpr unsigned kXcds = 8;
 
-dim3 row_grid(const AdjGeom& g) {
-  const int64_t rows = (int64_t)g.ny * g.nz;
-  const int64_t nrb = (rows + kRows - 1) / kRows;
-  const int64_t gy = std::min(nrb, kMaxGridY);
-  return dim3((unsigned)((g.nx + 63) / 64), (unsigned)gy, (unsigned)((nrb + gy - 1) / gy));
-}
-
 int64_t row_blocks(const AdjGeom& g) {
-  const dim3 r = row_grid(g);
-  return (int64_t)r.x * r.y * r.z;
+  const int64_t rows = (int64_t)g.ny * g.nz;
+  return (g.nx + 63) / 64 * ((rows + kRows - 1) / kRows);
 }
 
-// This thread's cell: x, and its row r = y + ny z (uniform in its wave).
-// Launched block b, on XCD j = b mod 8, is the (b / 8)-th of that XCD's run
+// This thread's cell in block b of nb: x, and its row r = y + ny z (uniform in
+// its wave). Block b, on XCD j = b mod 8, is the (b / 8)-th of that XCD's run
 // of logical blocks: XCD j takes q + (j < rem) of the nb = 8q + rem blocks,
 // starting at jq + min(j, rem). The renumbering is one to one for any nb.
-__device__ __forceinline__ void row_cell(int& x, int& r) {
-  const unsigned nb = gridDim.x * gridDim.y * gridDim.z;
-  const unsigned b = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+__device__ __forceinline__ void row_cell(unsigned b, unsigned nb, int nx, int& x, int& r) {
   const unsigned j = b % kXcds, q = nb / kXcds, rem = nb % kXcds;
   const unsigned lb = j * q + (j < rem ? j : rem) + b / kXcds;
-  x = (int)((lb % gridDim.x) * 64 + threadIdx.x);
-  r = __builtin_amdgcn_readfirstlane((int)((lb / gridDim.x) * kRows + threadIdx.y));
+  const unsigned gx = (unsigned)(nx + 63) / 64;
+  x = (int)((lb % gx) * 64 + threadIdx.x);
+  r = __builtin_amdgcn_readfirstlane((int)((lb / gx) * kRows + threadIdx.y));
 }
 
 // Cells y with src(y, e) = c along one axis (the pull source is y - e,
@@ -196,11 +196,12 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // g-only forward step between g-plane buffers (recomputation of a segment).
 template <typename T>
-__global__ __launch_bounds__(256) void k_gstep(const T* __restrict__ src, T* __restrict__ dst,
-                                               int64_t cs, AdjGeom d) {
+__device__ __forceinline__ void gstep_block(const T* __restrict__ src, T* __restrict__ dst,
+                                            int64_t cs, const AdjGeom& d, unsigned b,
+                                            unsigned nb) {
   const uint32_t esz = sizeof(T);
   int x, r;
-  row_cell(x, r);
+  row_cell(b, nb, d.nx, x, r);
   if (x < d.nx && r < d.ny * d.nz) {
     const int y = r % d.ny, z = r / d.ny;
     uint32_t off[19], self;
@@ -234,17 +235,18 @@ __global__ __launch_bounds__(256) void k_adj_loss(const T* __restrict__ state, i
 // One reverse step. state: g*(t) (the step's input); adj_in: either the
 // adjoint of g*(t+1) (GATHER = false, straight from the loss) or the
 // pre-collision adjoint of step t+1 (GATHER = true, transposed streaming
-// applied here). adj_out: pre-collision adjoint of step t. Row geometry of
-// k_gstep; dL/dtau partials per block.
+// applied here). adj_out: pre-collision adjoint of step t. dL/dtau partials per
+// block.
 template <typename T, bool GATHER>
-__global__ __launch_bounds__(256) void k_adj_step(const T* __restrict__ state,
-                                                  const T* __restrict__ adj_in,
-                                                  T* __restrict__ adj_out, int64_t cs, AdjGeom d,
-                                                  double* __restrict__ partials) {
+__device__ __forceinline__ void adjoint_block(const T* __restrict__ state,
+                                              const T* __restrict__ adj_in,
+                                              T* __restrict__ adj_out, int64_t cs,
+                                              const AdjGeom& d, double* __restrict__ partials,
+                                              unsigned b, unsigned nb) {
   const uint32_t esz = sizeof(T);
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   int x, r;
-  row_cell(x, r);
+  row_cell(b, nb, d.nx, x, r);
   if (x < d.nx && r < d.ny * d.nz) {
     const int y = r % d.ny, z = r / d.ny;
     uint32_t off[19], self;
@@ -278,8 +280,7 @@ __global__ __launch_bounds__(256) void k_adj_step(const T* __restrict__ state,
     for (int q = 0; q < 4; ++q) sh[threadIdx.y][q] = acc[q];
   __syncthreads();
   if (threadIdx.x == 0 && threadIdx.y == 0) {
-    double* p =
-        partials + (((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 5;
+    double* p = partials + (int64_t)b * 5;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       double s = 0.0;
@@ -288,6 +289,37 @@ __global__ __launch_bounds__(256) void k_adj_step(const T* __restrict__ state,
       p[q] += s;
     }
   }
+}
+
+// A launch of the reverse sweep: a reverse step (adj_in set), a recomputed step
+// (gsrc set) or both. With both, groups of 8 blocks alternate, so that either
+// keeps its XCDs and the CUs hold waves of both kinds at a time.
+template <typename T>
+struct SweepLaunch {
+  const T* state;
+  const T* adj_in;
+  T* adj_out;
+  const T* gsrc;
+  T* gdst;
+  int64_t cs;
+  AdjGeom d;
+  double* partials;
+  uint32_t nb;  // blocks of either
+};
+
+template <typename T, bool GATHER>
+__global__ __launch_bounds__(256) void k_sweep(SweepLaunch<T> a) {
+  unsigned b = blockIdx.x;
+  bool g = a.gsrc != nullptr;
+  if (g && a.adj_in) {
+    g = b & kXcds;
+    b = b / (2 * kXcds) * kXcds + b % kXcds;
+  }
+  if (b >= a.nb) return;
+  if (g)
+    gstep_block(a.gsrc, a.gdst, a.cs, a.d, b, a.nb);
+  else
+    adjoint_block<T, GATHER>(a.state, a.adj_in, a.adj_out, a.cs, a.d, a.partials, b, a.nb);
 }
 
 // dL/deps0, dL/du0 from the adjoint of the initial state.
@@ -326,113 +358,64 @@ __global__ __launch_bounds__(256) void k_sum_parts(const double* parts, int n, d
     for (int k = 0; k < 5; ++k) out[k] = v[k];
 }
 
-void release_graph(Tape& t) {
-  if (t.graph_exec) (void)hipGraphExecDestroy(t.graph_exec);
-  if (t.graph) (void)hipGraphDestroy(t.graph);
-  t.graph_exec = nullptr;
-  t.graph = nullptr;
-  t.graph_steps = -1;
-}
-
-// Adds one kernel node after the given dependencies.
-template <typename... A>
-hipError_t add_node(hipGraph_t g, hipGraphNode_t* out, const hipGraphNode_t* deps, int ndeps,
-                    const void* func, dim3 grid, dim3 block, A... args) {
-  void* params[] = {(void*)&args...};
-  hipKernelNodeParams kp{};
-  kp.func = const_cast<void*>(func);
-  kp.gridDim = grid;
-  kp.blockDim = block;
-  kp.sharedMemBytes = 0;
-  kp.kernelParams = params;
-  kp.extra = nullptr;
-  return hipGraphAddKernelNode(out, g, ndeps ? deps : nullptr, ndeps, &kp);
-}
-
-// The reverse sweep over every checkpointed segment, last first, as one HIP
-// graph of kernel nodes: per segment k, the g-only recomputation of its
-// states from checkpoint k (chain G(k)), then one reverse step per step of
-// the segment (chain R(k)). Segments alternate between two state buffers, so
-// that G(k-1) runs beside R(k), as a parallel branch of the graph: G(k-1)
-// waits only for R(k+1), the last reader of its buffer, and R(k) for G(k)
-// and R(k+1). The graph depends only on the step count and the tape's
-// buffers: it is built once per step count and kept with the tape.
+// The reverse sweep over every checkpointed segment, last first. R(k): the
+// reverse steps of segment k; G(k): the g-only recomputation of its states from
+// checkpoint k. Segments alternate between two state buffers: G(k-1) runs in the
+// launches of R(k), after R(k+1), the last reader of its buffer. *cur: the
+// adjoint buffer written last.
 template <typename T>
-rlb_status chain_graph(Tape& t, const GradContext& c) {
+hipError_t sweep(const Tape& t, const GradContext& c, int* cur) {
   const TapeLayout& L = t.L;
-  const AdjGeom d = adj_geom(c.desc);
-  const int64_t cs = c.cs;
-  const int64_t T_steps = c.steps;
   const int K = L.K;
-  const dim3 grid(row_grid(d)), block(64, kRows);
   auto ckpt = [&](int64_t k) { return (const T*)(t.base + L.off_ckpt + (size_t)k * L.gbytes); };
   auto seg = [&](int64_t k, int64_t j) {
     return (T*)(t.base + L.off_seg + (size_t)((k & 1) * K + j) * L.gbytes);
   };
-  T* adj[2] = {(T*)(t.base + L.off_adj), (T*)(t.base + L.off_adj + L.gbytes)};
-  double* parts = (double*)(t.base + L.off_tparts);
-  hipGraph_t g = nullptr;
-  if (hipGraphCreate(&g, 0) != hipSuccess) return RLB_E_DEVICE;
-  hipError_t e = hipSuccess;
-  // G(k) after dep (null: no dependency); *last = its last node (null when
-  // the segment has a single step and nothing to recompute)
-  auto add_G = [&](int64_t k, hipGraphNode_t dep, hipGraphNode_t* last) {
-    const int64_t t0 = k * K;
-    const int64_t t1 = std::min<int64_t>(t0 + K, T_steps);
-    const T* src = ckpt(k);
-    hipGraphNode_t prev = dep;
-    *last = nullptr;
-    for (int64_t tt = t0 + 1; tt < t1 && e == hipSuccess; ++tt) {
-      T* dst = seg(k, tt - t0);
-      hipGraphNode_t n;
-      e = add_node(g, &n, &prev, prev ? 1 : 0, (const void*)&k_gstep<T>, grid, block, src, dst,
-                   cs, d);
-      prev = *last = n;
-      src = dst;
-    }
-  };
-  int cur = 0;
+  T* const adj[2] = {(T*)(t.base + L.off_adj), (T*)(t.base + L.off_adj + L.gbytes)};
+  SweepLaunch<T> a{};
+  a.cs = c.cs;
+  a.d = adj_geom(c.desc);
+  a.partials = (double*)(t.base + L.off_tparts);
+  a.nb = (uint32_t)row_blocks(a.d);
   bool gathered = false;
-  const int64_t kmax = (T_steps - 1) / K;
-  hipGraphNode_t lastG = nullptr, lastR = nullptr;
-  add_G(kmax, nullptr, &lastG);
-  for (int64_t k = kmax; k >= 0 && e == hipSuccess; --k) {
-    const int64_t t0 = k * K;
-    const int64_t t1 = std::min<int64_t>(t0 + K, T_steps);
-    hipGraphNode_t nextG = nullptr;
-    if (k > 0) add_G(k - 1, lastR, &nextG);  // beside R(k): after R(k+1) only
-    hipGraphNode_t deps[2];
-    int nd = 0;
-    if (lastG) deps[nd++] = lastG;
-    if (lastR) deps[nd++] = lastR;
-    hipGraphNode_t prev = nullptr;
-    for (int64_t tt = t1 - 1; tt >= t0 && e == hipSuccess; --tt) {
-      const T* st = (tt == t0) ? ckpt(k) : (const T*)seg(k, tt - t0);
-      const T* in = adj[cur];
-      T* out = adj[1 - cur];
-      const void* f = gathered ? (const void*)&k_adj_step<T, true>
-                               : (const void*)&k_adj_step<T, false>;
-      hipGraphNode_t n;
-      e = prev ? add_node(g, &n, &prev, 1, f, grid, block, st, in, out, cs, d, parts)
-               : add_node(g, &n, deps, nd, f, grid, block, st, in, out, cs, d, parts);
-      prev = n;
-      cur = 1 - cur;
+  *cur = 0;
+  const auto steps_of = [&](int64_t k) { return std::min<int64_t>(K, c.steps - k * K); };
+  const auto recompute = [&](int64_t k, int64_t j) {  // state j - 1 of segment k to state j
+    a.gsrc = j == 1 ? ckpt(k) : (const T*)seg(k, j - 1);
+    a.gdst = seg(k, j);
+  };
+  const auto launch = [&]() {
+    const bool both = a.adj_in && a.gsrc;
+    const unsigned n = both ? 2 * ((a.nb + kXcds - 1) / kXcds * kXcds) : a.nb;
+    if (a.adj_in && !gathered)
+      hipLaunchKernelGGL((k_sweep<T, false>), dim3(n), dim3(64, kRows), 0, c.stream, a);
+    else
+      hipLaunchKernelGGL((k_sweep<T, true>), dim3(n), dim3(64, kRows), 0, c.stream, a);
+    if (a.adj_in) {
       gathered = true;
+      *cur = 1 - *cur;
     }
-    lastR = prev;
-    lastG = nextG;
+    a.adj_in = a.gsrc = nullptr;
+  };
+  const int64_t kmax = (c.steps - 1) / K;
+  for (int64_t j = 1; j < steps_of(kmax); ++j) {
+    recompute(kmax, j);
+    launch();
   }
-  hipGraphExec_t x = nullptr;
-  if (e == hipSuccess) e = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(g);
-    return RLB_E_DEVICE;
+  for (int64_t k = kmax; k >= 0; --k) {
+    const int64_t nr = steps_of(k), ng = k > 0 ? K - 1 : 0;
+    for (int64_t i = 0; i < std::max(nr, ng); ++i) {
+      if (i < nr) {
+        const int64_t j = nr - 1 - i;
+        a.state = j == 0 ? ckpt(k) : (const T*)seg(k, j);
+        a.adj_in = adj[*cur];
+        a.adj_out = adj[1 - *cur];
+      }
+      if (i < ng) recompute(k - 1, i + 1);
+      launch();
+    }
   }
-  release_graph(t);
-  t.graph = g;
-  t.graph_exec = x;
-  t.graph_steps = T_steps;
-  return RLB_OK;
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -448,17 +431,12 @@ rlb_status run_grad(Tape& t, const GradContext& c, const double* dLdu, const dou
   T* adj[2] = {(T*)(t.base + L.off_adj), (T*)(t.base + L.off_adj + L.gbytes)};
   const double* f0 = (const double*)(t.base + L.off_fields);
   double* parts = (double*)(t.base + L.off_tparts);
-  if (T_steps > 0 && (!t.graph_exec || t.graph_steps != T_steps)) {
-    const rlb_status st = chain_graph<T>(t, c);
-    if (st != RLB_OK) return st;
-  }
   if (hipMemsetAsync(parts, 0, sizeof(double) * 5 * (size_t)nparts, s) != hipSuccess)
     return RLB_E_DEVICE;
   const T* final_g = (const T*)((const char*)c.state + 19 * (size_t)cs * sizeof(T));
   hipLaunchKernelGGL(k_adj_loss<T>, grid, block, 0, s, final_g, cs, d, dLdu, dLdeps, adj[0]);
-  if (T_steps > 0 && hipGraphLaunch(t.graph_exec, s) != hipSuccess) return RLB_E_DEVICE;
-  // the chain's last reverse step wrote adj[T_steps & 1]
-  const int cur = (int)(T_steps & 1);
+  int cur = 0;
+  if (T_steps > 0 && sweep<T>(t, c, &cur) != hipSuccess) return RLB_E_DEVICE;
   if (T_steps > 0)
     hipLaunchKernelGGL((k_adj_init<T, true>), grid, block, 0, s, adj[cur], cs, d, f0, deps0, du0);
   else
@@ -568,7 +546,6 @@ rlb_status tape_grad(Tape& t, const GradContext& c, const double* dL_du, const d
 }
 
 void tape_release(Tape& t) {
-  release_graph(t);
   t.base = nullptr;
 }
 

@@ -32,10 +32,6 @@ struct Tape {
   TapeLayout L;
   int precision = 0;
   int64_t ncells = 0, cs = 0;
-  // the reverse sweep's kernel chain, instantiated for graph_steps steps
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
-  int64_t graph_steps = -1;
 };
 
 rlb_status tape_init(Tape& t, const TapeLayout& L, char* base, int precision, int64_t ncells,
@@ -57,6 +53,6 @@ struct GradContext {
 
 rlb_status tape_grad(Tape& t, const GradContext& c, const double* dL_du, const double* dL_deps,
                      double dL_dtau[3], double* dL_deps0, double* dL_du0, int io_on_device);
-void tape_release(Tape& t);  // also destroys the kept graph
+void tape_release(Tape& t);
 
 }  // namespace rlb
