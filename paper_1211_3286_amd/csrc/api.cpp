@@ -456,6 +456,31 @@ rlb_status launch_tile_rounds(rlb_sim* h, int variant, int nsteps, int pingpong,
   return RLB_OK;
 }
 
+// Default of the lattice path where nothing marches. us a step by the choice and
+// by 256 x 1 blocks:
+//   D3Q19: 64 x 4 blocks, 26^3 FP32 5.3 and 6.1, 60^3 12.4 and 15.6, 31 x 31 x 300
+//     19.6 and 27.4, 512 x 512 the same; rows of 65 to 128 cells 128 x 2 blocks, 66^3
+//     18.6 and 21.5 (64 x 4 21.6), 80^3 with eta/s 28.0 and 32.7;
+//   D2Q9: rounds of 3 steps on 32 x 16 windows, 110 x 160 FP32 2.8 and 3.7, 300^2 4.6
+//     and 6.0, 550^2 8.7 and 10.1, FP64 3.2 and 4.2, 5.1 and 8.0, 10.9 and 15.7. With
+//     eta/s or the correction, whose halos cost more, only while every window finds
+//     a CU: eta/s 250^2 FP32 4.1 and 5.3, 270 x 260 7.3 and 6.5; correction 150^2
+//     FP64 4.3 and 5.8, 250^2 10.0 and 9.4; else 64 x 4 blocks with the correction,
+//     which share the neighbours' fields (1531 x 1203 FP64 128 and 135, FP32 50 and
+//     70), and 256 x 1.
+int default_lattice(const rlb_sim* h) {
+  const rlb_params& p = h->params[0];
+  if (!h->d2) return p.nx > 64 && p.nx <= 128 ? 2 : 1;
+  const int tv = 6;
+  rlb::TileRound a{};
+  dim3 grid;
+  if (rlb::d2q9_tile_fits(h->precision, tv, h->corr) &&
+      tile_geometry(rlb::d2q9_tile_variant(tv), p.nx, p.ny, h->corr, a, grid) &&
+      ((!h->ext && !h->corr) || (int64_t)grid.x * grid.y <= h->num_cu))
+    return rlb::d2q9_num_lattice_variants() + tv;
+  return h->corr ? 3 : 2;
+}
+
 constexpr int kSpinLimit = 1 << 24;  // about a second of polling per wait
 
 bool is_segment_variant(const rlb_sim* h, int v) {
@@ -1049,10 +1074,6 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   if (hipDeviceGetAttribute(&h->num_cu, hipDeviceAttributeMultiprocessorCount, h->device) !=
       hipSuccess)
     return fail(RLB_E_DEVICE);
-  // default of the lattice path where nothing marches: the 256 x 1 block, or
-  // with the correction the 64 x 4 one, which shares the neighbours' fields
-  // (1531 x 1203 FP64 128 us a step against 135, FP32 50 against 70)
-  h->variant = h->lattice ? (h->d2 ? (h->corr ? 3 : 2) : 3) : default_persistent(h);
   // member descriptors (refs are filled on the device)
   h->descs.resize(n_members);
   int64_t off = 0;
@@ -1094,6 +1115,7 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     if (d.ext.general_eos) h->eos = true;
     off += d.ncells;
   }
+  h->variant = h->lattice ? default_lattice(h) : default_persistent(h);
   // The whole start is enqueued and its one answer read back at the end: the
   // refused cells and the reference the lattice kernels take as an argument.
   const double *dn, *de, *du;

@@ -94,3 +94,27 @@ def test_default_variants():
         assert sim.kernel_name == want
         sim.step(2)
         sim.close()
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_lattice_defaults_equal_the_first_variant(prec):
+    """Lattices too small to march take 64 x 4 or 128 x 2 blocks, D2Q9 ones rounds
+    of three steps (with eta/s or the correction while each window finds a CU):
+    names, and populations of variant 0 bit for bit after 7 and after 1 more."""
+    import paper_1211_3286_amd as rlb
+    t = "double" if prec == FP64 else "float"
+    corr = _plane(145, 130, (1, 1, 0), 1)
+    wide = _plane(300, 260, (0, 1, 0), 1)
+    for prob, want in (
+            (wl.random_modes(27, 25, 26, seed=3), f"k_step_lattice<{t},64,4,1>"),
+            (wl.random_modes(65, 20, 14, seed=3), f"k_step_lattice<{t},128,2,1>"),
+            (_plane(300, 260, (0, 1, 0)), f"k_d2q9_tiles<{t},32,16>/h3"),
+            (corr, f"k_d2q9_tiles<{t},32,16>/h3+c7"), (wide, f"k_d2q9_lattice<{t},64,4,1>+c7")):
+        sim, ref = (rlb.from_problems([prob], precision=prec) for _ in range(2))
+        assert sim.kernel_name == want
+        ref.variant = 0
+        for n in (7, 1):
+            sim.step(n)
+            ref.step(n)
+            for x, y in zip(sim.populations(), ref.populations()):
+                assert bool((x == y).all()), (prob.name, n)
