@@ -10,18 +10,18 @@
 // in the interior, up to four at clamped corners, never an atomic), applies
 // the transposed collision Jacobian (adjoint_cell.hpp) and writes 19 values:
 // 3 x 19 populations of traffic per cell-step. dL/dtau is accumulated in FP64
-// per block across all steps and reduced once at the end. A launch runs one
-// reverse step of a segment together with one recomputed step of the segment
-// before it (two segment buffers), the blocks of both taking turns.
+// per block across all steps and reduced once at the end. The recomputation of
+// a segment runs beside the reverse steps of the one after it (two segment
+// buffers): on a second stream, or on small lattices in the same launches.
 //
 // Bound by memory and, in the reverse step, by FP64 arithmetic as much: 100
 // populations' traffic per cell and step, at 512 x 512 FP32 20 MB a g state that
-// the last-level cache holds: a pair of steps takes 21 us, 4.8 TB/s. (As separate
-// kernels on two branches of a graph they ran one after the other, 13.5 and 8.2
-// us, behind the building of the graph for each new handle.) Forward and
-// backward, 512 x 512 FP32 200 steps 8.2 and now 7.8 ms; smaller lattices are
-// bound by the launches, of which there are half as many: 150 x 170 FP32 60 steps
-// 1.6 and 1.1 ms, 100 x 90 FP64 80 steps 1.9 and 1.2.
+// the last-level cache holds: a pair of steps takes 20 us, 5 TB/s. The launches go
+// out one by one: a graph of them, built anew for each handle, kept the GPU idle
+// for 0.9 ms per 200 steps. Forward and backward, 512 x 512 FP32 200 steps 8.2 and
+// now 7.1 ms; smaller lattices are bound by the launches, of which there are
+// half as many: 150 x 170 FP32 60 steps 1.6 and 1.1 ms, 100 x 90 FP64 80 steps 1.9
+// and 1.2.
 
 #include <hip/hip_runtime.h>
 
@@ -358,13 +358,31 @@ __global__ __launch_bounds__(256) void k_sum_parts(const double* parts, int n, d
     for (int k = 0; k < 5; ++k) out[k] = v[k];
 }
 
+// Up to this many blocks of 256 cells a launch of the sweep runs both kinds of
+// steps. Above, where they fill the chip, each kind has its stream: kernels of
+// their own overlap better than blocks of one (512 x 512 FP32, 1000 steps: 20.0
+// and 22.4 ms; 300 x 300, 375 blocks, 400 steps 4.1 and 4.2), while 150 x 170, 129
+// blocks, is bound by the launches (60 steps forward and backward 1.1 ms, with a
+// graph of single kernels 1.6).
+constexpr int64_t kPairBlocks = 256;
+
+// The second stream and its events, made at the first gradient that wants them
+// and kept with the tape.
+hipError_t side_stream(Tape& t) {
+  if (t.side) return hipSuccess;
+  hipError_t e = hipStreamCreateWithFlags(&t.side, hipStreamNonBlocking);
+  for (hipEvent_t* v : {&t.recomputed, &t.reversed})
+    if (e == hipSuccess) e = hipEventCreateWithFlags(v, hipEventDisableTiming);
+  return e;
+}
+
 // The reverse sweep over every checkpointed segment, last first. R(k): the
 // reverse steps of segment k; G(k): the g-only recomputation of its states from
-// checkpoint k. Segments alternate between two state buffers: G(k-1) runs in the
-// launches of R(k), after R(k+1), the last reader of its buffer. *cur: the
-// adjoint buffer written last.
+// checkpoint k. Segments alternate between two state buffers: G(k-1) runs beside
+// R(k), after R(k+1), the last reader of its buffer. *cur: the adjoint buffer
+// written last.
 template <typename T>
-hipError_t sweep(const Tape& t, const GradContext& c, int* cur) {
+hipError_t sweep(Tape& t, const GradContext& c, int* cur) {
   const TapeLayout& L = t.L;
   const int K = L.K;
   auto ckpt = [&](int64_t k) { return (const T*)(t.base + L.off_ckpt + (size_t)k * L.gbytes); };
@@ -372,50 +390,70 @@ hipError_t sweep(const Tape& t, const GradContext& c, int* cur) {
     return (T*)(t.base + L.off_seg + (size_t)((k & 1) * K + j) * L.gbytes);
   };
   T* const adj[2] = {(T*)(t.base + L.off_adj), (T*)(t.base + L.off_adj + L.gbytes)};
-  SweepLaunch<T> a{};
-  a.cs = c.cs;
-  a.d = adj_geom(c.desc);
-  a.partials = (double*)(t.base + L.off_tparts);
-  a.nb = (uint32_t)row_blocks(a.d);
-  bool gathered = false;
+  SweepLaunch<T> r{};  // the reverse step of a launch
+  r.cs = c.cs;
+  r.d = adj_geom(c.desc);
+  r.partials = (double*)(t.base + L.off_tparts);
+  r.nb = (uint32_t)row_blocks(r.d);
+  SweepLaunch<T> g = r;  // its recomputed step
   *cur = 0;
+  const int64_t kmax = (c.steps - 1) / K;
   const auto steps_of = [&](int64_t k) { return std::min<int64_t>(K, c.steps - k * K); };
-  const auto recompute = [&](int64_t k, int64_t j) {  // state j - 1 of segment k to state j
-    a.gsrc = j == 1 ? ckpt(k) : (const T*)seg(k, j - 1);
-    a.gdst = seg(k, j);
+  const bool pair = r.nb <= kPairBlocks;
+  const bool side = !pair && kmax > 0 && K > 1;
+  hipError_t e = hipSuccess;
+  if (side) e = side_stream(t);
+  const auto reverse = [&](int64_t k, int64_t j) {
+    r.state = j == 0 ? ckpt(k) : (const T*)seg(k, j);
+    r.adj_in = adj[*cur];
+    r.adj_out = adj[1 - *cur];
   };
-  const auto launch = [&]() {
+  const auto recompute = [&](int64_t k, int64_t j) {  // state j - 1 of segment k to state j
+    g.gsrc = j == 1 ? ckpt(k) : (const T*)seg(k, j - 1);
+    g.gdst = seg(k, j);
+  };
+  bool gathered = false;
+  const auto launch = [&](const SweepLaunch<T>& a, hipStream_t s) {
     const bool both = a.adj_in && a.gsrc;
     const unsigned n = both ? 2 * ((a.nb + kXcds - 1) / kXcds * kXcds) : a.nb;
     if (a.adj_in && !gathered)
-      hipLaunchKernelGGL((k_sweep<T, false>), dim3(n), dim3(64, kRows), 0, c.stream, a);
+      hipLaunchKernelGGL((k_sweep<T, false>), dim3(n), dim3(64, kRows), 0, s, a);
     else
-      hipLaunchKernelGGL((k_sweep<T, true>), dim3(n), dim3(64, kRows), 0, c.stream, a);
+      hipLaunchKernelGGL((k_sweep<T, true>), dim3(n), dim3(64, kRows), 0, s, a);
     if (a.adj_in) {
       gathered = true;
       *cur = 1 - *cur;
     }
-    a.adj_in = a.gsrc = nullptr;
   };
-  const int64_t kmax = (c.steps - 1) / K;
   for (int64_t j = 1; j < steps_of(kmax); ++j) {
     recompute(kmax, j);
-    launch();
+    launch(g, c.stream);
   }
-  for (int64_t k = kmax; k >= 0; --k) {
+  const auto after = [&](hipEvent_t v, hipStream_t done, hipStream_t waits) {
+    if (e == hipSuccess) e = hipEventRecord(v, done);
+    if (e == hipSuccess) e = hipStreamWaitEvent(waits, v, 0);
+  };
+  for (int64_t k = kmax; k >= 0 && e == hipSuccess; --k) {
     const int64_t nr = steps_of(k), ng = k > 0 ? K - 1 : 0;
+    if (side && ng) after(t.reversed, c.stream, t.side);
     for (int64_t i = 0; i < std::max(nr, ng); ++i) {
-      if (i < nr) {
-        const int64_t j = nr - 1 - i;
-        a.state = j == 0 ? ckpt(k) : (const T*)seg(k, j);
-        a.adj_in = adj[*cur];
-        a.adj_out = adj[1 - *cur];
-      }
       if (i < ng) recompute(k - 1, i + 1);
-      launch();
+      if (i < nr) reverse(k, nr - 1 - i);
+      if (pair && i < ng && i < nr) {
+        r.gsrc = g.gsrc;
+        r.gdst = g.gdst;
+        launch(r, c.stream);
+        r.gsrc = nullptr;
+        continue;
+      }
+      if (i < ng) launch(g, side ? t.side : c.stream);
+      if (i < nr) launch(r, c.stream);
     }
+    if (side && ng) after(t.recomputed, t.side, c.stream);
   }
-  return hipGetLastError();
+  // an error on the way leaves nothing of the sweep behind on the side stream
+  if (e != hipSuccess && t.side) (void)hipStreamSynchronize(t.side);
+  return e == hipSuccess ? hipGetLastError() : e;
 }
 
 template <typename T>
@@ -546,6 +584,11 @@ rlb_status tape_grad(Tape& t, const GradContext& c, const double* dL_du, const d
 }
 
 void tape_release(Tape& t) {
+  for (hipEvent_t v : {t.recomputed, t.reversed})
+    if (v) (void)hipEventDestroy(v);
+  if (t.side) (void)hipStreamDestroy(t.side);
+  t.recomputed = t.reversed = nullptr;
+  t.side = nullptr;
   t.base = nullptr;
 }
 

@@ -32,6 +32,9 @@ struct Tape {
   TapeLayout L;
   int precision = 0;
   int64_t ncells = 0, cs = 0;
+  // the recomputation's stream, from the first gradient that uses one on
+  hipStream_t side = nullptr;
+  hipEvent_t recomputed = nullptr, reversed = nullptr;
 };
 
 rlb_status tape_init(Tape& t, const TapeLayout& L, char* base, int precision, int64_t ncells,
@@ -53,6 +56,6 @@ struct GradContext {
 
 rlb_status tape_grad(Tape& t, const GradContext& c, const double* dL_du, const double* dL_deps,
                      double dL_dtau[3], double* dL_deps0, double* dL_du0, int io_on_device);
-void tape_release(Tape& t);
+void tape_release(Tape& t);  // also destroys the stream
 
 }  // namespace rlb
