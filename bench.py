@@ -5,22 +5,24 @@ Headline workload: a 256^3 periodic lattice (D3Q19, two distributions), smooth
 random flow from 16 Fourier modes (|k| <= 4, max|u| = 0.1, eps and n = 1 +
 0.05 noise, seed 1211), tau_v = 0.8, tau_e = 0.55, tau_eps = 0.7, tau_f = 0.8,
 FP32 populations with FP64 recovery and FP64 conservation sums fused into
-every step. One timed step = one fused kernel launch over all 16.8M cells.
+every step. One timed step = one update of all 16.8M cells; the marching
+kernel the tuner picks makes two per launch.
 
 Also reported ("forms"): the same step in FP64, the 1 x 1 x 800 FP64 shock
-tube (2000 steps), the batch of 64 ragged shock tubes (3000 steps, one HIP
-graph launch whose kernel nodes are rounds of H steps: kernel_nodes states
-how many), the adjoint gradient of a 512 x 512 run (1000 steps, checkpoints
-every 50), the 512^3 blast, the D2Q9 MRT model of Sec. V (a 4096^2 lattice,
-the 4 x 800 Cases A-D batch, the correction of Eqs. 37-38), and relaxation
-times set per cell from eta/s. Every form states its error: a short live run
-of the timed kernel variant against the FP64 oracle from the same input
-(error_vs_oracle), and for the adjoint the error of dL/dtau against central
-finite differences and of every output against the oracle's own adjoint.
+tube (2000 steps), the batch of 64 ragged shock tubes (3000 steps, in rounds
+of H steps a launch: launches states how many), the adjoint gradient of a 512
+x 512 run (1000 steps, checkpoints every 50), the 512^3 blast, the D2Q9 MRT
+model of Sec. V (a 4096^2 lattice, the 4 x 800 Cases A-D batch, the correction
+of Eqs. 37-38), and relaxation times set per cell from eta/s. Every form
+states its error: a short live run of the timed kernel variant against the
+FP64 oracle from the same input (error_vs_oracle), and for the adjoint the
+error of dL/dtau against central finite differences and of every output
+against the oracle's own adjoint.
 
 Prints one JSON line. ``value`` is MLUPS (million lattice-cell updates per
 second) with the populations resident in HBM; ``roofline`` prices the fused
-kernel at its algorithmic traffic (2 x 38 populations per cell update);
+kernel at its algorithmic traffic (2 x 38 populations per cell and pass over
+memory; a marching kernel makes H updates a pass);
 ``cpu_baseline`` times the FP64 CPU oracle on a bounded sample of the same
 workload on the host cores; ``error_vs_oracle`` then runs the GPU path from
 the same input for the same number of steps, in the kernel variants that were
@@ -48,10 +50,10 @@ D2Q9_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_d2q9.json")
 VALU_FILE = os.path.join(ROOT, "profiles", "valu_d2q9.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1211_3286_amd", "csrc", f)
                   for f in ("cell.hpp", "device_util.hpp", "internal.hpp", "kernels.hip",
-                            "api.cpp")]
+                            "step_lattice.hpp", "blocks.hip", "march.hip", "cells.hip", "api.cpp")]
 D2Q9_SOURCES = [os.path.join(ROOT, "paper_1211_3286_amd", "csrc", f)
                 for f in ("cell.hpp", "cell2d.hpp", "device_util.hpp", "internal.hpp",
-                          "kernels2d.hip", "api.cpp")]
+                          "kernels2d.hip", "march2d.hip", "cells.hip", "api.cpp")]
 # MI355X: 256 CUs at 2.4 GHz, each issuing at most one wave64 VALU
 # instruction a cycle (4 SIMDs, 4 cycles per wave64 instruction)
 VALU_PEAK_GINST = 256 * 2.4
@@ -151,7 +153,8 @@ def bench_lattice(torch, rlb, wl, n: int, precision: int, steps: int, warmup: in
     s1 = sim.sums()
     diag, dstep, bad = sim.diagnostics()
     cells = prob.params.ncells
-    bytes_per_cell = 2 * 38 * (4 if precision == rlb.FP32 else 8)
+    bytes_per_cell = 2 * 38 * (4 if precision == rlb.FP32 else 8) // steps_per_pass(
+        sim.kernel_name)
     drift = float(abs(s1 - s0).max() / abs(s0[:2]).max())
     out = {"ms_per_step": ms, "mlups": cells / (ms * 1e-3) / 1e6, "cells": cells,
            "kernel": sim.kernel_name, "bytes_per_cell": bytes_per_cell,
@@ -163,11 +166,27 @@ def bench_lattice(torch, rlb, wl, n: int, precision: int, steps: int, warmup: in
     return out
 
 
+def steps_per_pass(kernel: str) -> int:
+    """Updates a marching kernel makes per pass over the populations (1 for
+    the one-step kernels; tile rounds are priced by tile_traffic)."""
+    m = re.search(r"march.*/h(\d+)", kernel)
+    return int(m.group(1)) if m else 1
+
+
+def launch_shape(kernel: str, steps: int) -> dict:
+    """Launches of one rlb_step on the persistent path and steps per launch
+    (for strip rounds at least: they double while every segment has a CU)."""
+    if "_cells<" in kernel:
+        return {"launches": steps, "steps_per_launch": 1}
+    g = graph_shape(kernel, steps)
+    return {"launches": g["kernel_nodes"], "steps_per_launch": g["steps_per_node"]}
+
+
 def graph_shape(kernel: str, steps: int) -> dict:
-    """What one rlb_step of a persistent-path variant launches: the tube and
-    strip rounds are a HIP graph of ceil(steps / H) kernel nodes (H steps
-    each, from the variant name's /hH); the one-block and segmented kernels
-    are one node doing every step."""
+    """One rlb_step of a persistent-path variant as a chain of launches: the
+    tube and strip rounds are ceil(steps / H) of them (H steps each, from the
+    variant name's /hH); the one-block and segmented kernels do every step in
+    one."""
     m = re.search(r"/h(\d+)", kernel)
     h = int(m.group(1)) if m else None
     return {"graph_launches": 1, "kernel_nodes": -(-steps // h) if h else 1,
@@ -236,7 +255,7 @@ def bench_batched(torch, rlb, wl, steps: int = 3000, check_steps: int = 200):
            "tube_steps_per_s": len(tubes) * steps / (ms * 1e-3),
            "mlups": cells * steps / (ms * 1e-3) / 1e6,
            "effective_gbs": 304 * cells * steps / (ms * 1e-3) / 1e9,
-           "kernel": sim.kernel_name, **graph_shape(sim.kernel_name, steps),
+           "kernel": sim.kernel_name, **launch_shape(sim.kernel_name, steps),
            "inadmissible": m["bad"],
            "note": "working set ~35 MB stays in L2/MALL; effective GB/s is not HBM traffic"}
     sim.close()
@@ -290,7 +309,7 @@ def bench_shock_tube(torch, rlb, wl, steps: int = 2000, dump_every: int = 200):
         sim.close()
         out[name] = {"ms_total": ms, "steps_per_s": steps / (ms * 1e-3),
                      "mlups": 800 * steps / (ms * 1e-3) / 1e6, "kernel": tune["name"],
-                     **graph_shape(tune["name"], steps),
+                     **launch_shape(tune["name"], steps),
                      "error_vs_oracle_over_dumps": worst}
     return out
 
@@ -308,10 +327,10 @@ def bench_blast(torch, rlb, wl, L: int = 512, steps: int = 400, warmup: int = 10
     ms, wall = time_steps(torch, sim, steps, warmup)
     m = sim.moments(allow_unphysical=True)
     cells = L ** 3
+    gbs = 304 / steps_per_pass(tune["name"]) * cells / (ms * 1e-3) / 1e9
     res = {"lattice": f"{L}x{L}x{L}", "steps": steps, "ms_per_step": ms,
            "mlups": cells / (ms * 1e-3) / 1e6, "kernel": tune["name"],
-           "achieved_gbs": 304 * cells / (ms * 1e-3) / 1e9,
-           "frac": 304 * cells / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+           "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS,
            "inadmissible_cell_updates": m["bad"],
            "inadmissible_fraction": m["bad"] / float(cells * (steps + warmup)),
            "max_u_admissible": float(torch.nan_to_num(m["u"].norm(dim=0), nan=0.0).max().item()),
@@ -340,7 +359,7 @@ def bench_adjoint(torch, rlb, wl, L: int = 512, steps: int = 1000, K: int = 50,
     relaxation times plus 1 % noise. Times (HIP events on the handle's
     stream): the taped forward in the autotuned step variant, and the
     gradient (rlb_grad): the median of
-    grad_reps calls after one untimed call that instantiates its graph.
+    grad_reps calls after one untimed call, which makes the second stream.
     Errors: dL/dtau against central finite differences of the FP64 forward
     (h = 1e-4), over max(|FD|, |grad|); and
     every output against the oracle's FP64 adjoint on the oracle_L^2 instance,
@@ -388,7 +407,7 @@ def bench_adjoint(torch, rlb, wl, L: int = 512, steps: int = 1000, K: int = 50,
     du = torch.from_numpy(2.0 * (u - ut)).to(sim.device)
     de = torch.from_numpy(2.0 * (e - et)).to(sim.device)
     t0 = time.perf_counter()
-    sim.grad(du, de)  # builds and instantiates the reverse sweep's graph
+    sim.grad(du, de)  # makes the sweep's second stream
     first_s = time.perf_counter() - t0
     grad_runs = []
     for _ in range(grad_reps):
@@ -436,7 +455,6 @@ def bench_adjoint(torch, rlb, wl, L: int = 512, steps: int = 1000, K: int = 50,
             "achieved_gbs": 684 * cell_steps / (total_ms * 1e-3) / 1e9,
             "frac": 684 * cell_steps / (total_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             "gradient_reverse_gbs": 380 * cell_steps / (grad_ms * 1e-3) / 1e9,
-            "graph_launches_per_gradient": 1,
             "loss": loss(u, e), "dL_dtau": [float(x) for x in dtau],
             "dL_dtau_fd": [float(x) for x in fd],
             "error_vs_fd": float(np.abs(dtau - fd).max() / scale),
@@ -465,11 +483,11 @@ def tile_traffic(kernel: str, nx: int, ny: int, cell_bytes: int, corr: int):
 
 def bench_d2q9(torch, rlb, wl, n: int = 4096, steps: int = 100, warmup: int = 10):
     """The D2Q9 MRT model of Sec. V.A: an n x n periodic random flow in FP32
-    and FP64 (one fused launch per step, 2 x 18 populations per cell update),
-    also in FP32 with the correction term of Eqs. (37)-(38) (bytes counted at
-    the same 144 per cell: the neighbour re-reads are cache hits); the four
-    Sec. V.B cases on 4 x 800 as one persistent batch, 400 steps; and the
-    corrected moderately relativistic Cases A and D."""
+    and FP64 (2 x 18 populations per cell and pass over memory, of one step or
+    of the H steps of a marching kernel), also in FP32 with the correction term
+    of Eqs. (37)-(38) (the neighbour re-reads of its one-step kernels are cache
+    hits); the four Sec. V.B cases on 4 x 800 as one persistent batch, 400
+    steps; and the corrected moderately relativistic Cases A and D."""
     prob = wl.random_modes(n, n, 1, seed=1211, umax=0.1, amp=0.05, tau_v=0.8, tau_e=0.55,
                            tau_eps=0.7, tau_f=0.8)
     prob.params.lattice = "d2q9"
@@ -483,13 +501,13 @@ def bench_d2q9(torch, rlb, wl, n: int = 4096, steps: int = 100, warmup: int = 10
         s0 = sim.sums()
         ms, _ = time_steps(torch, sim, steps, warmup)
         s1 = sim.sums()
-        bpc = 2 * 18 * (4 if prec == rlb.FP32 else 8)
+        bpc = 2 * 18 * (4 if prec == rlb.FP32 else 8) / steps_per_pass(tune["name"])
         gbs = bpc * cells / (ms * 1e-3) / 1e9
         out[name] = {"ms_per_step": ms, "mlups": cells / (ms * 1e-3) / 1e6,
                      "kernel": tune["name"], "bytes_per_cell": bpc, "achieved_gbs": gbs,
                      "frac": gbs / HBM_PEAK_GBS,
                      "conservation_drift": float(abs(s1 - s0).max() / abs(s0[:2]).max())}
-        tiles = tile_traffic(tune["name"], n, n, bpc // 2, corr)
+        tiles = tile_traffic(tune["name"], n, n, bpc / 2, corr)
         if tiles:
             # tile rounds move fewer bytes than one step's 2 x 18 values per
             # cell update: achieved_gbs and frac count the round's own HBM
@@ -513,9 +531,9 @@ def bench_d2q9(torch, rlb, wl, n: int = 4096, steps: int = 100, warmup: int = 10
                     "frac": rate / VALU_PEAK_GINST,
                     "note": "VALU wave-instructions per cell update (SQ_INSTS_VALU) x cell "
                             "updates per second, against one wave-instruction per CU and cycle"}
-        # the timed variant against the oracle: one tile round (3 steps) of the
-        # whole lattice
-        out[name]["error_vs_oracle"] = live_error(torch, rlb, prob, 3, prec, tune["name"],
+        # the timed variant against the oracle, whole lattice: 4 steps, a full
+        # launch of every kernel that makes several
+        out[name]["error_vs_oracle"] = live_error(torch, rlb, prob, 4, prec, tune["name"],
                                                   diag_every=50, correction=corr)
         sim.close()
     del prob
@@ -538,7 +556,7 @@ def bench_d2q9(torch, rlb, wl, n: int = 4096, steps: int = 100, warmup: int = 10
         out[name] = {"members": " ".join(c.name for c in batch), "steps": 400,
                      "ms_total": ms, "us_per_step": 1e3 * ms / 400,
                      "mlups": nc * 400 / (ms * 1e-3) / 1e6, "kernel": tune["name"],
-                     **graph_shape(tune["name"], 400), "inadmissible": sim.moments()["bad"]}
+                     **launch_shape(tune["name"], 400), "inadmissible": sim.moments()["bad"]}
         sim.close()
         out[name]["error_vs_oracle"] = live_error(torch, rlb, batch, 400, prec, tune["name"])
     return out
@@ -556,7 +574,7 @@ def bench_eta_s(torch, rlb, wl, n: int = 256, steps: int = 50, warmup: int = 5):
     tune = sim.tune(trial_steps=10)
     ms, _ = time_steps(torch, sim, steps, warmup)
     cells = prob.params.ncells
-    gbs = 304 * cells / (ms * 1e-3) / 1e9
+    gbs = 304 / steps_per_pass(tune["name"]) * cells / (ms * 1e-3) / 1e9
     out = {"lattice": f"{n}^3 FP32, eta/s = 0.1", "ms_per_step": ms,
            "mlups": cells / (ms * 1e-3) / 1e6, "kernel": tune["name"], "achieved_gbs": gbs,
            "frac": gbs / HBM_PEAK_GBS}
@@ -568,7 +586,7 @@ def bench_eta_s(torch, rlb, wl, n: int = 256, steps: int = 50, warmup: int = 5):
     sim = rlb.from_problems(prob, precision=rlb.FP32, diag_every=50)
     tune = sim.tune(trial_steps=10)
     ms, _ = time_steps(torch, sim, steps, warmup)
-    gbs = 304 * cells / (ms * 1e-3) / 1e9
+    gbs = 304 / steps_per_pass(tune["name"]) * cells / (ms * 1e-3) / 1e9
     out["general_eos"] = {"eos": "Gamma 1.5, m 0.6", "ms_per_step": ms,
                           "mlups": cells / (ms * 1e-3) / 1e6, "kernel": tune["name"],
                           "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS}
@@ -588,7 +606,7 @@ def bench_eta_s(torch, rlb, wl, n: int = 256, steps: int = 50, warmup: int = 5):
     torch.cuda.synchronize()
     out["sec3_tube_batch"] = {"members": "3 x (1x1x800), tau_f = tau_g, 1.0, 0.6", "steps": 400,
                               "ms_total": e0.elapsed_time(e1), "kernel": tune["name"],
-                              **graph_shape(tune["name"], 400)}
+                              **launch_shape(tune["name"], 400)}
     sim.close()
     out["sec3_tube_batch"]["error_vs_oracle"] = live_error(torch, rlb, tubes, 400, rlb.FP64,
                                                            tune["name"])
@@ -1158,7 +1176,7 @@ def main():
     roof = {"bound": "hbm", "achieved": round(head["achieved_gbs"], 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(head["frac"], 4), "traffic": traffic,
             "kernel": head["kernel"], "algorithmic_bytes_per_launch":
-                head["bytes_per_cell"] * head["cells"]}
+                head["bytes_per_cell"] * steps_per_pass(head["kernel"]) * head["cells"]}
     forms = {}
     sel = set(args.forms.split(",")) if args.forms else None
 
@@ -1185,7 +1203,7 @@ def main():
         # the runtime's own device-to-device copy of the bytes one FP32 step
         # moves (38 x 4 B per cell read, the same written), as context for the
         # step's rate: step_speed_over_copy is a ratio of speeds, not a
-        # fraction of a peak (the fused step moves its bytes faster than it)
+        # fraction of a peak
         cc = copy_calibration(torch, nbytes=38 * 4 * head["cells"], reps=20)
         cc["step_speed_over_copy"] = head["achieved_gbs"] / cc["gbs"]
         forms["copy_ceiling"] = cc

@@ -50,8 +50,10 @@
  * memory: all device state lives in the caller's workspace, whose size
  * rlb_workspace_size reports, and which must stay valid (and untouched by the
  * caller) until rlb_free. All device work is enqueued on the caller's HIP
- * stream given to rlb_init (NULL = the null stream); calls that return host
- * data synchronise that stream. Pointers marked "device" must be device
+ * stream given to rlb_init (NULL = the null stream), except that rlb_grad runs
+ * the recomputation of large lattices on a stream of the handle's own, joined
+ * to the caller's by events; calls that return host data synchronise the
+ * caller's stream. Pointers marked "device" must be device
  * memory of the device that was current at rlb_init; "host" pointers are
  * ordinary host memory. A handle must not be used from two threads at once.
  *
@@ -236,11 +238,13 @@ rlb_status rlb_grad(rlb_handle h, const double* dL_du, const double* dL_deps,
 
 /* Kernel variants (block shape x cells per thread; for the lattice step also
  * the waves per SIMD: a name ending in "/w3" reserves unused LDS so that 3
- * waves per SIMD run instead of 4; for round kernels the steps per launch,
- * "/hH", which strip rounds double where every segment still finds a CU) of the path this handle dispatches to. rlb_tune times every variant with HIP events on trial steps
- * that read the current state and write only the spare buffer (the state is
- * unchanged), selects the fastest, and returns all timings (ms per step,
- * host array of rlb_num_variants doubles, may be NULL). */
+ * waves per SIMD run instead of 4; for round and marching kernels the steps
+ * per launch, "/hH", which strip rounds double where every segment still finds
+ * a CU) of the path this handle dispatches to. rlb_tune times every variant
+ * with HIP events on trial steps that read the current state and write only
+ * the spare buffer (the state is unchanged), selects the fastest, and returns
+ * all timings (ms per step, host array of rlb_num_variants doubles, may be
+ * NULL). */
 rlb_status rlb_num_variants(rlb_handle h, int32_t* count);
 rlb_status rlb_variant_name(rlb_handle h, int32_t variant, char* buf, size_t buflen);
 rlb_status rlb_set_variant(rlb_handle h, int32_t variant);

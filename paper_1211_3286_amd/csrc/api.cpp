@@ -1,5 +1,5 @@
 // C ABI of the relativistic lattice Boltzmann library (include/rlb.h):
-// argument validation, workspace carving, dispatch, graphs, autotuning.
+// argument validation, workspace carving, dispatch, autotuning.
 
 #include <hip/hip_runtime.h>
 
@@ -366,17 +366,17 @@ int march_steps(const rlb_sim* h, int v) {
 // The marching variant that is the default from a share `use` of used cells of
 // its grid on (MarchGrid::use). us a step, marching and best one-step kernel:
 // D3Q19: 40 x 40 x 400 FP32 (use 0.42) 40.5 and 32.7, 80^3 FP32 (0.59) 25.2 and
-// 27.4, 64^3 FP64 (0.65) 22.1 and 25.2; eta/s: 80^3 FP32 (0.59) 29.2 and 28.0,
-// 60^3 FP64 (0.71) 23.1 and 22.2, 128 x 160 x 100 FP32 (0.73) 106 and 112, 160^3
-// FP32 (0.79) 195 and 208, 80^3 FP64 (0.79) 52 and 60.
+// 27.4, 64^3 FP64 (0.65) 22.1 and 25.2; eta/s: 60^3 FP64 (0.71) 23.1 and 22.2,
+// 96^3 FP32 (0.74) 43.9 and 44.0, 160^3 FP32 (0.79) 205 and 207, 128^3 FP32 (0.85)
+// 100 and 114, 80^3 FP64 (0.79) 52 and 60.
 // D2Q9: 700 x 500 FP32 (0.33) 10.1 and 10.3, 300^2 FP32 (0.08) 7.3 and 5.9, 1000 x
 // 800 FP32 (0.52) 15 and 20. eta/s, where 3 steps a launch do as well as 4 at
-// 2000 x 1800 and better below: FP32 1000 x 800 (0.54) 21.4 and 21.2, 1100 x 900
-// (0.62) 23.3 and 27.1; FP64 500 x 400 (0.36) 11.2 and 11.3, 700 x 500 (0.57) 13.0
+// 2000 x 1800 and better below: FP32 1000 x 800 (0.54) 23.3 and 21.0, 1100 x 900
+// (0.62) 25.6 and 26.4; FP64 500 x 400 (0.36) 11.2 and 11.3, 700 x 500 (0.57) 13.0
 // and 17.3. With the correction: 1000 x 800 FP32 (0.53) 26 and 25, 1531 x 1203 FP32
 // (0.69) 45 and 50, 300^2 FP64 (0.18) 14 and 9, 700 x 500 FP64 (0.55) 18 and 21; and
 // eta/s: FP64 1000 x 800 (0.63) 39.9 and 39.9, 1400 x 1000 (0.79) 59 and 92; FP32 2000 x
-// 1800 (0.82) 129 and 112 (one wave per SIMD: never the default). A general
+// 1800 (0.82) 140 and 111 (one wave per SIMD: never the default). A general
 // equation of state repeats its root search in the halos: a higher share.
 struct MarchDefault {
   int variant;
@@ -1101,6 +1101,8 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     d.rt.s_q = 1.0 / tq;
     d.rt.s_v = 1.0 / p.tau_v;
     d.ext.eta_s = p.eta_over_s;
+    d.ext.kappa = p.kappa;
+    d.ext.dof = p.dof;
     d.ext.visc = 3.0 * p.kappa * p.eta_over_s;
     d.ext.inv_eq = rlb::kPiSquared / p.dof;
     d.ext.a_f = p.a_f;

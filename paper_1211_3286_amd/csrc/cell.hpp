@@ -46,8 +46,10 @@ constexpr double kPiSquared = 9.869604401089358;
 // state P = (Gamma - 1)(eps - m n) (recover_general).
 struct Ext {
   double eta_s;   // > 0: tau_v of each cell from eta/s (Rates are the fallback)
-  double visc;    // 3 kappa eta_s (kappa: shear-viscosity transformation factor)
-  double inv_eq;  // pi^2 / d_G (n_eq = d_G T^3 / pi^2)
+  double kappa;   // shear-viscosity transformation factor
+  double dof;     // degeneracy d_G of n_eq = d_G T^3 / pi^2
+  double visc;    // 3 kappa eta_s
+  double inv_eq;  // pi^2 / d_G
   double a_f, a_e, a_eps, a_q;  // > 0: tau_x - 1/2 = a_x (tau_v - 1/2)
   double eos_gamma;             // Gamma (general_eos only)
   double mass;                  // rest mass m (general_eos only)
@@ -262,21 +264,49 @@ __device__ __forceinline__ double four_minus_log(double x) {
 //   n_eq = d_G T^3 / pi^2, lambda = n / n_eq, s = 4n - n ln(lambda),
 //   eta = (eta/s) s, and the relation after Eq. (10) solved for tau:
 //   tau_v = 1/2 + kappa eta / (c_s^2 (eps + P) gamma), (eps + P) gamma = sigma / gamma.
-// With n = N / gamma the factors gamma cancel: tau_v - 1/2 =
-// 3 kappa (eta/s) (N / sigma) (4 - ln lambda), lambda = (n / P)^3 n pi^2 / d_G.
 // tau_x (x = f, e, eps, q) with a_x > 0 follow as tau_x - 1/2 = a_x (tau_v - 1/2);
 // tau_q also follows tau_v when tied. A cell with n <= 0 or P <= 0 keeps the
-// member's fixed rates; one at the edge of a vacuum (lambda underflows,
-// tau_v = inf) does not relax: the limit keeps its reciprocals finite.
+// member's fixed rates; one at the edge of a vacuum (lambda underflows, tau_v =
+// inf) does not relax: below, the limits of w keep the reciprocals finite.
 //
-// This is serial FP64 work in every cell and step, and what bounds kernels of
-// the extended model. Written as printed above, with thirteen IEEE divisions and
-// the library's logarithm, it took about 1100 of a wave's 5000 clocks a step; in
-// this form about 500. Against 80-bit arithmetic over random states (T 1e-2 to 1,
-// P 1e-9 to 10, |u| up to 0.99) both forms' rates are off by 1.5e-16 in the mean,
-// by 1.5e-13 (long form) and 0.8e-13 at most, where 4 - ln lambda cancels. One
-// step of 160^3 FP32 (one-step kernel) 235 and 208 us, of 1000 x 800 D2Q9 FP64
-// (marching) 32 and 26; 8 steps of the four Cases of 4 x 800 cells, FP64, 17 and 14.
+// As printed (rates_printed) that takes thirteen IEEE divisions and the library's
+// logarithm, 1100 of a wave's 5000 clocks a step, in one serial chain.
+__device__ __forceinline__ void rates_printed(const Ext& v, double N, const Macro& m, Rates& r) {
+  constexpr double kPi = 3.141592653589793;
+  const double gam = 1.0 / sqrt(1.0 - m.u2);
+  const double n = N / gam;
+  const double T = m.P / n;
+  const double n_eq = v.dof * T * T * T / (kPi * kPi);
+  const double s = 4.0 * n - n * log(n / n_eq);
+  const double eta = v.eta_s * s;
+  const double tv = 0.5 + v.kappa * eta / ((1.0 / 3.0) * (m.sigma / gam));
+  r.s_v = 1.0 / tv;
+  if (v.q_tied) r.s_q = r.s_v;
+  if (v.a_f > 0.0) r.w_f = 1.0 / (0.5 + v.a_f * (tv - 0.5));
+  if (v.a_e > 0.0) r.s_e = 1.0 / (0.5 + v.a_e * (tv - 0.5));
+  if (v.a_eps > 0.0) r.s_eps = 1.0 / (0.5 + v.a_eps * (tv - 0.5));
+  if (v.a_q > 0.0) r.s_q = 1.0 / (0.5 + v.a_q * (tv - 0.5));
+}
+
+// Whether x is so near to halfway between two floats that 3e-12 of it could
+// change the float it rounds to (1 in 16000 values).
+__device__ __forceinline__ bool float_in_doubt(double x) {
+  constexpr uint32_t kHalf = 1u << 28, kNear = 1u << 14;  // of the 29 bits a float drops
+  const uint32_t low = (uint32_t)__double_as_longlong(x) & ((1u << 29) - 1);
+  return low - (kHalf - kNear) < 2 * kNear;
+}
+
+// With n = N / gamma the factors gamma cancel: tau_v - 1/2 =
+// 3 kappa (eta/s) (N / sigma) (4 - ln lambda), lambda = (n / P)^3 n pi^2 / d_G,
+// which takes about 500 clocks. Against 80-bit arithmetic over random states (T
+// 1e-2 to 1, P 1e-9 to 10, |u| up to 0.99) both forms' rates are off by 1.5e-16 in
+// the mean, by 1.5e-13 (as printed) and 0.8e-13 at most, where 4 - ln lambda
+// cancels. FP32 collisions use the rates rounded to floats: where a rounding
+// hangs on the last bits the printed form decides, so that both give the same
+// populations. One step of 1000 x 800 D2Q9 FP64 (marching) 32 and 26 us; 8 steps of
+// the four Cases of 4 x 800 cells, FP64, 17 and 14; 160^3 FP32 (one-step) 236 and
+// 207.
+template <typename C>
 __device__ __forceinline__ Rates local_rates(const Rates& rt, const Ext& v, double N,
                                              const Macro& m) {
   const double n = N * root01(1.0 - m.u2);
@@ -287,11 +317,18 @@ __device__ __forceinline__ Rates local_rates(const Rates& rt, const Ext& v, doub
   w = fmin(fmax(w, -1e150), 1e150);
   Rates r = rt;
   r.s_v = recip(0.5 + w);
+  bool doubt = float_in_doubt(r.s_v);
+  const auto rate = [&](double a) {
+    const double y = recip(fma(a, w, 0.5));
+    doubt = doubt || float_in_doubt(y);
+    return y;
+  };
   if (v.q_tied) r.s_q = r.s_v;
-  if (v.a_f > 0.0) r.w_f = recip(fma(v.a_f, w, 0.5));
-  if (v.a_e > 0.0) r.s_e = recip(fma(v.a_e, w, 0.5));
-  if (v.a_eps > 0.0) r.s_eps = recip(fma(v.a_eps, w, 0.5));
-  if (v.a_q > 0.0) r.s_q = recip(fma(v.a_q, w, 0.5));
+  if (v.a_f > 0.0) r.w_f = rate(v.a_f);
+  if (v.a_e > 0.0) r.s_e = rate(v.a_e);
+  if (v.a_eps > 0.0) r.s_eps = rate(v.a_eps);
+  if (v.a_q > 0.0) r.s_q = rate(v.a_q);
+  if (sizeof(C) == 4 && doubt) rates_printed(v, N, m, r);
   return r;
 }
 
@@ -541,7 +578,7 @@ __device__ __forceinline__ bool collide(C (&f)[19], C (&g)[19], const Rates& rt,
   Macro mac;
   if constexpr (EXT) {
     if (!recover_model(N, E, Mx, My, Mz, *ext, mac)) return false;
-    const Rates r = local_rates(rt, *ext, N, mac);
+    const Rates r = local_rates<C>(rt, *ext, N, mac);
     collide_f(f, N, fs, mac, r, ref);
     collide_g(g, Mx, My, Mz, gs, mac, r, ref);
   } else {
@@ -579,7 +616,7 @@ __device__ __forceinline__ bool collide_half(C (&f)[19], C (&g)[19], const Rates
   if (!(EXT ? recover_model(N, E, Mx, My, Mz, ext, mac) : recover(E, Mx, My, Mz, mac)))
     return false;
   Rates r = rt;
-  if constexpr (EXT) r = local_rates(rt, ext, N, mac);
+  if constexpr (EXT) r = local_rates<C>(rt, ext, N, mac);
   if constexpr (F)
     collide_f(f, N, fs, mac, r, ref);
   else

@@ -338,7 +338,7 @@ __device__ __forceinline__ bool collide_recovered(C (&f)[9], C (&g)[9], const Re
   sums.v[4] = 0.0;
   if (!r.ok) return false;
   Rates rt = rt_member;
-  if constexpr (EXT) rt = local_rates(rt_member, *ext, r.N, r.mac);
+  if constexpr (EXT) rt = local_rates<C>(rt_member, *ext, r.N, r.mac);
   double c7 = 0.0;
   if constexpr (CORR) c7 = d2q9::c7_row(r.mac, *fm, *fp);
   d2q9::collide_f(f, r.N, r.fs, r.mac, rt, ref);

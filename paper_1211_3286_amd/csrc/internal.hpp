@@ -150,8 +150,7 @@ const char* march_kernel_name(int precision, int variant);
 hipError_t launch_step_march(int precision, int variant, bool ext, const void* src, void* dst,
                              const LatticeGeom& g, const MarchGrid& m, unsigned long long* bad,
                              hipStream_t s);
-// Kernel function pointer and launch shape of the persistent member kernel
-// (for graph nodes). args must outlive the launch.
+// Kernel function pointer and launch shape of the persistent member kernel.
 struct MemberLaunch {
   const MemberDesc* descs;
   void* bufA;

@@ -84,7 +84,7 @@ __device__ __forceinline__ void g_half(const T (&f)[19], T (&g)[19], const Latti
     g_sums(g, geo.ref, E, Mx, My, Mz, gs);
     h.ok = recover_model(N, E, Mx, My, Mz, geo.ext, h.mac);
     if (h.ok) {
-      h.rt = local_rates(geo.rt, geo.ext, N, h.mac);
+      h.rt = local_rates<T>(geo.rt, geo.ext, N, h.mac);
       collide_g(g, Mx, My, Mz, gs, h.mac, h.rt, geo.ref);
     }
   } else {

@@ -134,6 +134,8 @@ rlb_status run(unsigned char* ws, const rlb_params& p, const rlb_options& o, con
   desc.rt.s_q = 1.0 / tq;
   desc.rt.s_v = 1.0 / p.tau_v;
   desc.ext.eta_s = p.eta_over_s;
+  desc.ext.kappa = p.kappa;
+  desc.ext.dof = p.dof;
   desc.ext.visc = 3.0 * p.kappa * p.eta_over_s;
   desc.ext.inv_eq = rlb::kPiSquared / p.dof;
   desc.ext.a_f = p.a_f;
