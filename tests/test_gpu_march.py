@@ -176,3 +176,23 @@ def test_d2q9_corrected_march_counts_inadmissible_cells():
     st = oracle.run(prob, 4)
     sim = _run(prob, FP64, 17, (4,))
     assert sim.moments(allow_unphysical=True)["bad"] == st.bad > 50
+
+
+@pytest.mark.parametrize("eta", [0.0, 0.1], ids=["fixed", "eta_s"])
+@pytest.mark.parametrize("variant", [17, 18])
+def test_d2q9_march_mixes_its_launches(variant, eta):
+    """Calls of 1 to 13 steps, as launches of 4 and 3 and single ones, leave the
+    populations of single steps; so do runs with diagnostics every 6th step."""
+    import paper_1211_3286_amd as rlb
+    prob = _plane(300, 290, (1, 0, 0), eta)
+    for every in (0, 6):
+        sim, ref = (rlb.from_problems([prob], precision=FP64, diag_every=every) for _ in range(2))
+        sim.variant, ref.variant = variant, 0
+        for n in (1, 2, 3, 4, 5, 6, 7, 9, 10, 13):
+            sim.step(n)
+            ref.step(n)
+            for x, y in zip(sim.populations(), ref.populations()):
+                assert bool((x == y).all()), (n, every)
+        if every:
+            a, b = sim.diagnostics(), ref.diagnostics()
+            assert a[1] == b[1] and relmax(a[0], b[0]) < 1e-13
