@@ -184,7 +184,7 @@ def test_d2q9_march_mixes_its_launches(variant, eta):
     """Calls of 1 to 13 steps, as launches of 4 and 3 and single ones, leave the
     populations of single steps; so do runs with diagnostics every 6th step."""
     import paper_1211_3286_amd as rlb
-    prob = _plane(300, 290, (1, 0, 0), eta)
+    prob = _plane(300, 290, (1, 0), eta)
     for every in (0, 6):
         sim, ref = (rlb.from_problems([prob], precision=FP64, diag_every=every) for _ in range(2))
         sim.variant, ref.variant = variant, 0
