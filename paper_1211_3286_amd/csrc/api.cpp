@@ -507,12 +507,13 @@ bool is_segment_variant(const rlb_sim* h, int v) {
 // Default of the persistent path. us a step, the choice against the one-block
 // member kernel (512 threads), which keeps members of up to 1024 cells, one or two
 // passes of its block (9^3 FP32 6.4 against 4.1, but 300 of 10^3 16 and 19):
-//   1 x 1 x L tubes: rounds. Windows of 128 cells with a thread per distribution
-//     while every segment has a CU, 32 steps a round (64 owned cells), else 16
-//     (96), and for tubes that one window holds; else windows of 256 cells, 16
-//     steps. By these three: 800 cells FP64 1.2, 1.3 and 1.7 (member kernel 9.3),
-//     24 of 800 1.9, 1.4 and 1.8, 64 of up to 1500 FP32 3.0, 2.6 and 2.7, 200 of
-//     1500 10.6, 8.0 and 6.6; 1500 tubes of 100 cells FP64 4.2 and 5.8;
+//   1 x 1 x L tubes: rounds. Windows of 128 cells with a thread per distribution,
+//     up to 32 steps a round, while their segments are few, and for tubes that one
+//     window holds; else windows of 256 cells, up to 16 steps. The first and the
+//     second: 800 cells FP64 1.2 and 1.7 (member kernel 9.3), 24 of 800 FP32 1.3 and
+//     1.9, 30 of up to 1500 the same, 100 of up to 1300 3.1 and 2.8, 64 of up to 3200
+//     4.3 and 3.8; eta/s FP64 40 of 400 1.9 and 2.2, FP32 64 of up to 1500 4.1 and
+//     3.5; 1500 tubes of 100 cells FP64 4.2 and 5.8;
 //   narrow D2Q9 members: strip rounds of 8 or 16 steps, if windows of 256 cells
 //     leave an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
 //   the rest: one launch per step; 16^3 FP32 3.8 and 29, 24^3 4.2 and 115, 120^2
@@ -524,15 +525,34 @@ constexpr int64_t kMemberCells = 1024, kStripCells = 256;
 
 int cells_base(const rlb_sim* h);
 
-// The widest halo whose segments each find a CU, of the split windows; else 1.
+// Tube segments with windows of nt cells and `halo` of them a side.
+int64_t tube_segments(const rlb_sim* h, int nt, int halo) {
+  int64_t n = 0;
+  for (const rlb_params& p : h->params)
+    n += p.nz <= nt ? 1 : (p.nz + nt - 2 * halo - 1) / (nt - 2 * halo);
+  return n;
+}
+
+// Steps of a tube variant's rounds: H, or less (down to half) where that saves
+// the fullest CU a segment: a round waits for it, while a launch costs as much as
+// two steps. 64 tubes of up to 3200 cells, FP32, 256 CUs: 521 segments at H = 16,
+// 509 at 14: 3.45 and 3.15 us a step, start and fields included.
+int tube_halo(const rlb_sim* h, const rlb::TubeVariant& v) {
+  const auto fullest = [&](int halo) {
+    return (tube_segments(h, v.nt, halo) + h->num_cu - 1) / h->num_cu;
+  };
+  int halo = v.halo;
+  while (halo > v.halo / 2 && fullest(halo) > fullest(v.halo / 2)) --halo;
+  return halo;
+}
+
+// The split windows up to two segments per CU (one in the extended model, where
+// both threads of a cell work out its rates), as tube_halo would cut them; else 1.
 int default_tube(const rlb_sim* h) {
+  const int64_t most = (int64_t)h->num_cu * (h->ext ? 1 : 2);
   for (const int v : {6, 5}) {
     const rlb::TubeVariant t = rlb::tube_variant(v);
-    if (h->L.max_member <= t.nt) return v;
-    int64_t n = 0;
-    for (const rlb_params& p : h->params)
-      n += p.nz <= t.nt ? 1 : (p.nz + t.nt - 2 * t.halo - 1) / (t.nt - 2 * t.halo);
-    if (n <= h->num_cu) return v;
+    if (h->L.max_member <= t.nt || tube_segments(h, t.nt, t.halo / 2) <= most) return v;
   }
   return 1;
 }
@@ -579,7 +599,8 @@ int strip_index(int v) { return v - rlb::d2q9_num_member_variants(); }
 // windows extended by H halo cells (cut at zero-gradient ends); a tube that
 // fits the block whole is one segment with exact ends.
 rlb_status build_tube_segments(rlb_sim* h, int tv) {
-  const rlb::TubeVariant v = rlb::tube_variant(tv);
+  rlb::TubeVariant v = rlb::tube_variant(tv);
+  v.halo = tube_halo(h, v);
   const int S = v.nt - 2 * v.halo;
   std::vector<rlb::TubeSeg> segs;
   for (int m = 0; m < h->n_members; ++m) {
