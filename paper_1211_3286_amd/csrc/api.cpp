@@ -643,18 +643,24 @@ rlb_status build_tube_segments(rlb_sim* h, int tv) {
   return RLB_OK;
 }
 
-// A strip round takes twice its H steps where windows with that halo still own a
-// row and every segment finds a CU: a launch costs as much as two steps (eta/s,
-// FP64, by H = 8 and 16 of 256 threads: 4 members of 4 x 800 cells, 100 segments,
-// 1.9 and 1.6 us a step; 12 of them, 300 segments, 2.0 and 2.4).
-bool doubled_strips_fit(const rlb_sim* h, const rlb::TubeVariant& v) {
-  int64_t n = 0;
-  for (const rlb_params& p : h->params) {
-    const int R = v.nt / p.nx, S = R - 4 * v.halo * (h->corr ? 2 : 1);
-    if (p.ny > R && S < 1) return false;
-    n += p.ny > R ? (p.ny + S - 1) / S : 1;
-  }
-  return n <= h->num_cu;
+// Steps of a strip variant's rounds: H, or up to twice as many while windows with
+// that halo own a row and the fullest CU gets no segment more: a launch costs as
+// much as two steps (eta/s, FP64, by 8 and 16 steps of 256 threads: 4 members of 4
+// x 800 cells, 100 segments, 1.9 and 1.6 us a step; 12 of them, 300 segments, 2.0
+// and 2.4: they take 12 steps, 1.9).
+int strip_halo(const rlb_sim* h, const rlb::TubeVariant& v) {
+  const auto fullest = [&](int halo) {  // 0: some window owns no row
+    int64_t n = 0;
+    for (const rlb_params& p : h->params) {
+      const int R = v.nt / p.nx, S = R - 2 * halo * (h->corr ? 2 : 1);
+      if (p.ny > R && S < 1) return (int64_t)0;
+      n += p.ny > R ? (p.ny + S - 1) / S : 1;
+    }
+    return (n + h->num_cu - 1) / h->num_cu;
+  };
+  int halo = 2 * v.halo;
+  while (halo > v.halo && (fullest(halo) == 0 || fullest(halo) > fullest(v.halo))) --halo;
+  return halo;
 }
 
 // D2Q9 strip segments for a strip variant: windows of R = nt / nx rows, H
@@ -664,7 +670,7 @@ bool doubled_strips_fit(const rlb_sim* h, const rlb::TubeVariant& v) {
 // owned row.
 rlb_status build_strip_segments(rlb_sim* h, int sv) {
   rlb::TubeVariant v = rlb::d2q9_strip_variant(sv);
-  if (doubled_strips_fit(h, v)) v.halo *= 2;
+  v.halo = strip_halo(h, v);
   const int hr = h->corr ? 2 * v.halo : v.halo;
   std::vector<rlb::TubeSeg> segs;
   for (int m = 0; m < h->n_members; ++m) {
