@@ -174,8 +174,9 @@ def steps_per_pass(kernel: str) -> int:
 
 
 def launch_shape(kernel: str, steps: int) -> dict:
-    """Launches of one rlb_step on the persistent path and steps per launch
-    (for strip rounds at least: they double while every segment has a CU)."""
+    """Launches of one rlb_step on the persistent path and steps per launch, at
+    the H of the variant's name (tube rounds may take as few as half of it,
+    strip rounds as many as twice)."""
     if "_cells<" in kernel:
         return {"launches": steps, "steps_per_launch": 1}
     g = graph_shape(kernel, steps)

@@ -238,13 +238,13 @@ rlb_status rlb_grad(rlb_handle h, const double* dL_du, const double* dL_deps,
 
 /* Kernel variants (block shape x cells per thread; for the lattice step also
  * the waves per SIMD: a name ending in "/w3" reserves unused LDS so that 3
- * waves per SIMD run instead of 4; for round and marching kernels the steps
- * per launch, "/hH"; tube rounds take fewer, no less than half, and strip rounds more,
- * up to twice as many, as the segments then load the CUs) of the path this handle dispatches to. rlb_tune times every variant
- * with HIP events on trial steps that read the current state and write only
- * the spare buffer (the state is unchanged), selects the fastest, and returns
- * all timings (ms per step, host array of rlb_num_variants doubles, may be
- * NULL). */
+ * waves per SIMD run instead of 4; for round and marching kernels the steps per
+ * launch, "/hH"; tube rounds take fewer, no less than half, and strip rounds
+ * more, up to twice as many, as the segments then load the CUs) of the path
+ * this handle dispatches to. rlb_tune times every variant with HIP events on
+ * trial steps that read the current state and write only the spare buffer (the
+ * state is unchanged), selects the fastest, and returns all timings (ms per
+ * step, host array of rlb_num_variants doubles, may be NULL). */
 rlb_status rlb_num_variants(rlb_handle h, int32_t* count);
 rlb_status rlb_variant_name(rlb_handle h, int32_t variant, char* buf, size_t buflen);
 rlb_status rlb_set_variant(rlb_handle h, int32_t variant);
