@@ -1162,7 +1162,8 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
   }
   h->variant = h->lattice ? default_lattice(h) : default_persistent(h);
   // The whole start is enqueued and its one answer read back at the end: the
-  // refused cells and the reference the lattice kernels take as an argument.
+  // refused cells and the reference the lattice kernels take as an argument. That
+  // wait also ends the last read of the caller's fields.
   const double *dn, *de, *du;
   static_assert(sizeof(rlb::HostView) <= 256, "the small area holds the view and more");
   if (rlb::launch_begin((unsigned long long*)h->d_small,
@@ -1185,6 +1186,12 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
              : rlb::launch_init(h->precision, h->buf[0], L.lay, h->d_descs, n_members, dn, de, du,
                                 L.ncells, h->stream);
   if (ie != hipSuccess) return fail(RLB_E_DEVICE);
+  if (opt->ckpt_every > 0) {  // reads the caller's fields too: ahead of the wait
+    rlb_status ts = rlb::tape_init(h->tape, L.tape, h->ws + L.off_tape, h->precision, L.ncells,
+                                   L.cs, opt->ckpt_every, opt->tape_steps, dn, de, du,
+                                   h->buf[0], h->stream);
+    if (ts != RLB_OK) return fail(ts);
+  }
   rlb::HostView view;
   if (read_view(h, &view) != RLB_OK) return fail(RLB_E_DEVICE);
   if (view.refused) return fail(RLB_E_UNPHYSICAL);
@@ -1217,13 +1224,7 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     if (use >= md.least_use) h->variant = march_base(h) + md.variant;
   }
   h->cur = 0;
-  if (opt->ckpt_every > 0) {
-    rlb_status ts = rlb::tape_init(h->tape, L.tape, h->ws + L.off_tape, h->precision, L.ncells,
-                                   L.cs, opt->ckpt_every, opt->tape_steps, dn, de, du,
-                                   h->buf[0], h->stream);
-    if (ts != RLB_OK) return fail(ts);
-    h->tape_ok = true;
-  }
+  h->tape_ok = opt->ckpt_every > 0;
   *out = h;
   return RLB_OK;
 }
