@@ -207,6 +207,7 @@ class Simulation:
         e_t = dev_field(eps0, (nc,))
         u_t = dev_field(u0, (3, nc))
         h = ctypes.c_void_p(0)
+        self._after_current()
         with torch.cuda.device(dev):
             code = lib().rlb_init(ctypes.byref(h), self._arr, len(self.members),
                                   ctypes.byref(self.opt), _dptr(n_t), _dptr(e_t), _dptr(u_t), 1,
@@ -215,6 +216,14 @@ class Simulation:
         self.h = h
 
     # -- lifetime --------------------------------------------------------
+    def _after_current(self) -> None:
+        """A handle's stream waits for the current one, on which the tensors of
+        the coming call were made: inputs still being written, and outputs in
+        memory whose last user may still run."""
+        cur = self.torch.cuda.current_stream(self.device)
+        if cur != self.stream:
+            self.stream.wait_stream(cur)
+
     def close(self) -> None:
         if getattr(self, "h", None) and self.h.value:
             lib().rlb_free(self.h)
@@ -258,6 +267,7 @@ class Simulation:
         out["u"] = torch.empty(3, nc, dtype=torch.float64, device=self.device)
         sums = (ctypes.c_double * 5)()
         bad = ctypes.c_int64(0)
+        self._after_current()
         code = lib().rlb_moments(self.h, _dptr(out["n"]), _dptr(out["eps"]), _dptr(out["P"]),
                                  _dptr(out["gamma"]), _dptr(out["u"]), sums, ctypes.byref(bad),
                                  1)
@@ -288,6 +298,7 @@ class Simulation:
         torch = self.torch
         f = torch.empty(self.q, self.ncells, dtype=torch.float64, device=self.device)
         g = torch.empty(self.q, self.ncells, dtype=torch.float64, device=self.device)
+        self._after_current()
         _check(lib().rlb_populations(self.h, _dptr(f), _dptr(g), 1), "rlb_populations")
         return f, g
 
@@ -300,6 +311,7 @@ class Simulation:
         dtau = (ctypes.c_double * 3)()
         de0 = torch.empty(nc, dtype=torch.float64, device=self.device)
         du0 = torch.empty(3, nc, dtype=torch.float64, device=self.device)
+        self._after_current()
         _check(lib().rlb_grad(self.h, _dptr(du), _dptr(de), dtau, _dptr(de0), _dptr(du0), 1),
                "rlb_grad")
         return np.array(dtau[:]), de0, du0
@@ -381,7 +393,10 @@ def run_noalloc(params, n0, eps0, u0, nsteps: int, precision: int = FP32, lattic
     arr = cparams([params])
     sums = (ctypes.c_double * 5)()
     bad = ctypes.c_int64(0)
-    st = stream if stream is not None else torch.cuda.current_stream(dev)
+    cur = torch.cuda.current_stream(dev)
+    st = stream if stream is not None else cur
+    if st != cur:  # the fields and outputs were made on the current stream
+        st.wait_stream(cur)
     code = lib().rlb_run_noalloc(arr, ctypes.byref(opt), *[_dptr(t) for t in fields], int(nsteps),
                                  _dptr(out["n"]), _dptr(out["eps"]), _dptr(out["P"]),
                                  _dptr(out["gamma"]), _dptr(out["u"]), sums, ctypes.byref(bad),

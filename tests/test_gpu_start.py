@@ -41,3 +41,40 @@ def test_taped_start_has_read_the_fields_when_it_returns(prec):
     for a, b in zip(got[0], got[1]):
         assert np.array_equal(np.asarray(torch.as_tensor(a).cpu()),
                               np.asarray(torch.as_tensor(b).cpu()))
+
+
+def test_a_stream_of_its_own_waits_for_the_current_one():
+    """Fields that the current stream is still computing, and gradients' inputs
+    likewise, reach a handle on another stream as if on the same one; so they do
+    the allocation-free run."""
+    import paper_1211_3286_amd as rlb
+    prob = wl.random_modes(64, 48, 40, seed=6, umax=0.1, amp=0.05)
+    nc = prob.params.ncells
+    n0, e0, u0 = [torch.from_numpy(np.ascontiguousarray(a)).cuda()
+                  for a in rlb.problem_fields([prob])]
+    w = torch.rand(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+
+    def late(t):
+        """t, but only after some milliseconds of the current stream's work."""
+        out, v = torch.full_like(t, 0.25), w
+        for _ in range(12):
+            v = (v @ w) * 1e-4
+        return out.copy_(t + 0.0 * v.flatten()[0].clamp(0, 1))
+
+    got = []
+    for stream in (None, torch.cuda.Stream()):
+        say("handle on", "the current stream" if stream is None else "another stream")
+        sim = rlb.Simulation([prob.params], late(n0), late(e0), late(u0), precision=0,
+                             ckpt_every=2, tape_steps=4, stream=stream)
+        sim.step(4)
+        m = sim.moments()
+        dtau, de0, du0 = sim.grad(late(m["u"]), late(m["eps"]))
+        r = rlb.run_noalloc(prob.params, late(n0), late(e0), late(u0), 3, precision=1,
+                            stream=stream)
+        torch.cuda.synchronize()
+        got.append([m["u"], m["eps"], torch.as_tensor(dtau), de0, du0, r["u"], r["eps"]])
+        sim.close()
+    assert nc == got[0][1].numel()
+    for a, b in zip(*got):
+        assert bool((a == b).all())
