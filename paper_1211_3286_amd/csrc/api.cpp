@@ -514,7 +514,7 @@ bool is_segment_variant(const rlb_sim* h, int v) {
 //     1.9, 30 of up to 1500 the same, 100 of up to 1300 3.1 and 2.8, 64 of up to 3200
 //     4.3 and 3.8; eta/s FP64 40 of 400 1.9 and 2.2, FP32 64 of up to 1500 4.1 and
 //     3.5; 1500 tubes of 100 cells FP64 4.2 and 5.8;
-//   narrow D2Q9 members: strip rounds of 8 or 16 steps, if windows of 256 cells
+//   narrow D2Q9 members: strip rounds (default_strip), if windows of 256 cells
 //     leave an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
 //   the rest: one launch per step; 16^3 FP32 3.8 and 29, 24^3 4.2 and 115, 120^2
 //     D2Q9 3.3 and 41. Blocks of 64 cells until they fill the chip: D3Q19, where
@@ -557,16 +557,58 @@ int default_tube(const rlb_sim* h) {
   return 1;
 }
 
+// Strip segments with windows of nt cells and rounds of `halo` steps; 0 where a
+// window owns no row.
+int64_t strip_segments(const rlb_sim* h, int nt, int halo) {
+  int64_t n = 0;
+  for (const rlb_params& p : h->params) {
+    const int R = nt / p.nx, S = R - 2 * halo * (h->corr ? 2 : 1);
+    if (p.ny > R && S < 1) return 0;
+    n += p.ny > R ? (p.ny + S - 1) / S : 1;
+  }
+  return n;
+}
+
+// Steps of a strip variant's rounds: H, or up to twice as many while windows with
+// that halo own a row and the fullest CU gets no segment more: a launch costs as
+// much as two steps (eta/s, FP64, by 8 and 16 steps of 256 threads: 4 members of 4
+// x 800 cells, 100 segments, 1.9 and 1.6 us a step; 12 of them, 300 segments, 2.0
+// and 2.4: they take 12 steps, 1.9).
+int strip_halo(const rlb_sim* h, const rlb::TubeVariant& v) {
+  const auto fullest = [&](int halo) {  // 0: some window owns no row
+    return (strip_segments(h, v.nt, halo) + h->num_cu - 1) / h->num_cu;
+  };
+  int halo = 2 * v.halo;
+  while (halo > v.halo && (fullest(halo) == 0 || fullest(halo) > fullest(v.halo))) --halo;
+  return halo;
+}
+
+// Strip variant of a batch of narrow members, -1 where windows of 256 cells leave
+// no owned row. Those windows while each segment has a CU; beyond, windows of 512
+// cells where they compute fewer cells, which wide members need: a window of nx
+// cells a row owns 256 / nx - 16 rows (15 x 500, one: 17 times the work). us a
+// step by 256 and 512 cells, and the member kernel: 16 of 15 x 500 FP64 20.9, 4.0 and
+// 35; 256 of 15 x 100 FP32 50, 7.8 and 8.8; 64 of 12 x 500 FP32 13.9, 7.0 and 20;
+// 256 of 4 x 100, whole in 512 cells, FP32 2.6, 1.7 and 2.2. By how much fewer: the
+// larger blocks lose more registers with eta/s or the correction, 64 of 7 x 500 (0.72
+// of the cells) eta/s FP64 8.2 and 8.6, but 64 of 10 x 500 (0.53) 13.8 and 10.5.
+int default_strip(const rlb_sim* h) {
+  const int small = 3, large = 4;
+  const rlb::TubeVariant s = rlb::d2q9_strip_variant(small), l = rlb::d2q9_strip_variant(large);
+  const int rows = 2 * s.halo * (h->corr ? 2 : 1) + 1;
+  for (const rlb_params& p : h->params)
+    if ((int64_t)p.nx * rows > s.nt) return -1;
+  const int64_t ns = strip_segments(h, s.nt, s.halo), nl = strip_segments(h, l.nt, l.halo);
+  const double fewer = h->ext || h->corr ? 0.7 : 0.9;
+  return ns > h->num_cu && nl * l.nt < fewer * ns * s.nt ? large : small;
+}
+
 int default_persistent(const rlb_sim* h) {
   if (h->all_tubes)
     return rlb::num_member_variants() + rlb::num_segment_variants() + default_tube(h);
   if (h->d2 && h->L.max_member > kStripCells) {
-    const int v = 3;
-    const rlb::TubeVariant t = rlb::d2q9_strip_variant(v);
-    const int rows = 2 * t.halo * (h->corr ? 2 : 1) + 1;
-    bool fits = true;
-    for (const rlb_params& p : h->params) fits = fits && (int64_t)p.nx * rows <= t.nt;
-    if (fits) return rlb::d2q9_num_member_variants() + v;
+    const int v = default_strip(h);
+    if (v >= 0) return rlb::d2q9_num_member_variants() + v;
   }
   if (h->L.max_member <= kMemberCells) return 1;
   return cells_base(h) + (h->L.blocks[0] <= rlb::small_blocks(h->d2) ? 0 : 1);
@@ -641,26 +683,6 @@ rlb_status build_tube_segments(rlb_sim* h, int tv) {
   h->seg_halo = v.halo;
   h->seg_built = 1000 + tv;
   return RLB_OK;
-}
-
-// Steps of a strip variant's rounds: H, or up to twice as many while windows with
-// that halo own a row and the fullest CU gets no segment more: a launch costs as
-// much as two steps (eta/s, FP64, by 8 and 16 steps of 256 threads: 4 members of 4
-// x 800 cells, 100 segments, 1.9 and 1.6 us a step; 12 of them, 300 segments, 2.0
-// and 2.4: they take 12 steps, 1.9).
-int strip_halo(const rlb_sim* h, const rlb::TubeVariant& v) {
-  const auto fullest = [&](int halo) {  // 0: some window owns no row
-    int64_t n = 0;
-    for (const rlb_params& p : h->params) {
-      const int R = v.nt / p.nx, S = R - 2 * halo * (h->corr ? 2 : 1);
-      if (p.ny > R && S < 1) return (int64_t)0;
-      n += p.ny > R ? (p.ny + S - 1) / S : 1;
-    }
-    return (n + h->num_cu - 1) / h->num_cu;
-  };
-  int halo = 2 * v.halo;
-  while (halo > v.halo && (fullest(halo) == 0 || fullest(halo) > fullest(v.halo))) --halo;
-  return halo;
 }
 
 // D2Q9 strip segments for a strip variant: windows of R = nt / nx rows, H

@@ -1,0 +1,56 @@
+"""Default variants of batches: which kernel a handle starts with, by the work that
+its forms would do for the batch, and its populations, which are the one-block
+member kernel's (variant 0) bit for bit."""
+
+import pytest
+
+import workloads as wl
+from gpu_helpers import say
+
+pytestmark = pytest.mark.gpu
+
+FP64, FP32 = 0, 1
+
+
+def _plane(nx, ny, corr=0, eta=0.0):
+    p = wl.random_modes(nx, ny, 1, seed=5, umax=0.2, amp=0.1, bc=(0, 1, 0))
+    p.params.lattice, p.params.correction = "d2q9", corr
+    if eta:
+        p.n *= 1.7e-7 / 0.0314
+        p.eps *= 5.1e-7
+        q = p.params
+        q.eta_s, q.tau_v, q.tau_e, q.tau_eps, q.a_e, q.a_eps = eta, 0.8, 0.8, 0.8, 1.0, 1.0
+    return p
+
+
+def _default_is(prob, members, prec, want, steps=(9, 1)):
+    import paper_1211_3286_amd as rlb
+    a, b = (rlb.from_problems([prob] * members, precision=prec) for _ in range(2))
+    say(members, "of", prob.params.shape, "prec", prec, a.kernel_name)
+    assert a.kernel_name == want
+    b.variant = 0
+    for n in steps:
+        a.step(n)
+        b.step(n)
+        for x, y in zip(a.populations(), b.populations()):
+            assert bool((x == y).all())
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("nx,ny,members,corr,eta,window", [
+    (4, 800, 4, 0, 0.0, 256),     # every segment has a CU
+    (15, 100, 2, 0, 0.0, 256),    # 200 segments, a row each
+    (15, 100, 64, 0, 0.0, 512),   # 6400 of them compute 17 times the cells
+    (12, 500, 64, 0, 0.0, 512),
+    (4, 800, 64, 0, 0.0, 256),    # the smaller windows lose little
+    (4, 100, 256, 0, 0.0, 512),   # whole members in the larger windows
+    (7, 500, 64, 1, 0.0, 512),
+    (4, 800, 64, 1, 0.0, 256),
+    (15, 500, 64, 0, 0.1, 512),
+    (7, 500, 64, 0, 0.1, 256),
+])
+def test_strip_windows_by_the_cells_they_compute(nx, ny, members, corr, eta, window):
+    for prec, t in ((FP64, "double"), (FP32, "float")):
+        _default_is(_plane(nx, ny, corr, eta), members, prec,
+                    f"k_d2q9_strips<{t},{window}>/h8" + ("+c7" if corr else ""))
