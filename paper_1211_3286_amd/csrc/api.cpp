@@ -516,6 +516,7 @@ bool is_segment_variant(const rlb_sim* h, int v) {
 //     3.5; 1500 tubes of 100 cells FP64 4.2 and 5.8;
 //   narrow D2Q9 members: strip rounds (default_strip), if windows of 256 cells
 //     leave an owned row; 4 x 800 FP32 1.6 and 9.4, with the correction 2.0 and 20;
+//   batches of members of a few passes: the member kernel (members_fill_the_chip);
 //   the rest: one launch per step; 16^3 FP32 3.8 and 29, 24^3 4.2 and 115, 120^2
 //     D2Q9 3.3 and 41. Blocks of 64 cells until they fill the chip: D3Q19, where
 //     they run a thread per distribution, 864 blocks FP64 9.6 us and 10.2 of
@@ -603,6 +604,35 @@ int default_strip(const rlb_sim* h) {
   return ns > h->num_cu && nl * l.nt < fewer * ns * s.nt ? large : small;
 }
 
+// Is the one-block member kernel better than one launch per step? It takes
+// max_member cells in passes of 512, all members at once where they are as many as
+// the CUs, and keeps a member's populations near its CU; a launch per step
+// spreads the cells over the chip and streams them all. us a step by member kernel
+// and launches (256 CUs; 11^3 is 3 passes, 13^3 5, 16^3 and 64^2 8, 40^2 4):
+//   D3Q19 FP32: 128 of 11^3 16 and 13, 192 17 and 18, 1024 71 and 119; 256 of 13^3 29
+//     and 34, of 16^3 81 and 66; with eta/s 256 of 11^3 30 and 24;
+//   FP64: 64 of 11^3 15 and 13, 96 16 and 17, 1024 135 and 193; 128 of 13^3 27 and 32;
+//     256 of 16^3 124 and 136, 384 206 and 191, 512 253 and 265; eta/s the same;
+//   D2Q9: 64 of 40^2 FP32 5.4 and 7.3, FP64 7.9 and 8.7; 256 of 64^2 FP32 21 and 26,
+//     FP64 47 and 55; one of 33 x 32 FP32 4.0 and 4.8; eta/s FP32 256 of 40^2 19
+//     and 14; correction: 128 of 40^2 FP32 11.8 and 13.7, FP64 14 and 18.
+bool members_fill_the_chip(const rlb_sim* h) {
+  const auto passes_of = [](int64_t cells) { return (cells + 511) / 512; };
+  const int64_t passes = passes_of(h->L.max_member);
+  int64_t total = 0;
+  for (const MemberDesc& d : h->descs) total += passes_of(d.ncells);
+  // members, were they all as large as the largest, per CU
+  const double load = (double)total / passes / h->num_cu;
+  const bool fp32 = h->precision == RLB_FP32;
+  if (fp32 && h->ext) return h->corr && passes <= 4 && load >= 0.75 && load <= 1.0;
+  if (h->d2 && !h->corr) {
+    if (fp32) return passes <= 3 || (passes <= 16 && load >= (passes <= 5 ? 0.25 : 0.5));
+    return passes <= 8 && load >= (passes <= 4 ? 0.25 : passes <= 5 ? 0.375 : 0.5);
+  }
+  if (passes <= 5) return load >= (fp32 && (!h->d2 || passes == 5) ? 0.75 : 0.375);
+  return !fp32 && passes <= 8 && std::ceil(load) - load <= 0.25;  // no CU waits for another
+}
+
 int default_persistent(const rlb_sim* h) {
   if (h->all_tubes)
     return rlb::num_member_variants() + rlb::num_segment_variants() + default_tube(h);
@@ -610,7 +640,7 @@ int default_persistent(const rlb_sim* h) {
     const int v = default_strip(h);
     if (v >= 0) return rlb::d2q9_num_member_variants() + v;
   }
-  if (h->L.max_member <= kMemberCells) return 1;
+  if (h->L.max_member <= kMemberCells || members_fill_the_chip(h)) return 1;
   return cells_base(h) + (h->L.blocks[0] <= rlb::small_blocks(h->d2) ? 0 : 1);
 }
 

@@ -54,3 +54,52 @@ def test_strip_windows_by_the_cells_they_compute(nx, ny, members, corr, eta, win
     for prec, t in ((FP64, "double"), (FP32, "float")):
         _default_is(_plane(nx, ny, corr, eta), members, prec,
                     f"k_d2q9_strips<{t},{window}>/h8" + ("+c7" if corr else ""))
+
+
+def _box(nx, ny, nz, eta=0.0):
+    p = wl.random_modes(nx, ny, nz, seed=5, umax=0.2, amp=0.1, bc=(0, 1, 0))
+    if eta:
+        p.n *= 1.7e-7 / 0.0314
+        p.eps *= 5.1e-7
+        q = p.params
+        q.eta_s, q.tau_v, q.tau_e, q.tau_eps, q.a_e, q.a_eps = eta, 0.8, 0.8, 0.8, 1.0, 1.0
+    return p
+
+
+MEMBERS, LAUNCHES = "members", "cells"
+
+
+@pytest.mark.parametrize("make,members,want", [
+    (lambda: _box(11, 11, 11), 64, {FP32: LAUNCHES, FP64: LAUNCHES}),
+    (lambda: _box(11, 11, 11), 128, {FP32: LAUNCHES, FP64: MEMBERS}),
+    (lambda: _box(11, 11, 11), 256, {FP32: MEMBERS, FP64: MEMBERS}),
+    (lambda: _box(16, 16, 16), 256, {FP32: LAUNCHES, FP64: MEMBERS}),
+    (lambda: _box(24, 24, 24), 96, {FP32: LAUNCHES, FP64: LAUNCHES}),
+    (lambda: _box(11, 11, 11, 0.1), 256, {FP32: LAUNCHES, FP64: MEMBERS}),
+    (lambda: _plane(40, 40), 16, {FP32: LAUNCHES, FP64: LAUNCHES}),
+    (lambda: _plane(40, 40), 64, {FP32: MEMBERS, FP64: MEMBERS}),
+    (lambda: _plane(33, 32), 1, {FP32: MEMBERS, FP64: LAUNCHES}),
+    (lambda: _plane(64, 64), 256, {FP32: MEMBERS, FP64: MEMBERS}),
+    (lambda: _plane(40, 40, 1), 128, {FP32: MEMBERS, FP64: MEMBERS}),
+    (lambda: _plane(40, 40, 0, 0.1), 128, {FP32: LAUNCHES, FP64: MEMBERS}),
+])
+def test_batches_that_fill_the_chip_take_the_member_kernel(make, members, want):
+    prob = make()
+    for prec, t in ((FP64, "double"), (FP32, "float")):
+        name = "k_d2q9_" if prob.params.lattice == "d2q9" else "k_step_"
+        if want[prec] == MEMBERS:
+            name += f"members<{t},512,1>"
+        else:
+            small = 4096 if prob.params.lattice == "d2q9" else 1000
+            name += f"cells<{t},{64 if members * -(-prob.params.ncells // 64) <= small else 256}>"
+        _default_is(prob, members, prec, name + ("+c7" if prob.params.correction else ""),
+                    steps=(3, 1))
+
+
+def test_a_large_member_among_small_ones_spreads_over_the_chip():
+    """The member kernel would wait for one block; the small members fill no CU."""
+    import paper_1211_3286_amd as rlb
+    probs = [_box(20, 15, 8)] + [_box(3, 3, 3)] * 300
+    sim = rlb.from_problems(probs, precision=FP64)
+    assert sim.kernel_name == "k_step_cells<double,64>"
+    sim.close()
