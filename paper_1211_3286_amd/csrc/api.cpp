@@ -593,8 +593,11 @@ int strip_halo(const rlb_sim* h, const rlb::TubeVariant& v) {
 // 256 of 4 x 100, whole in 512 cells, FP32 2.6, 1.7 and 2.2. By how much fewer: the
 // larger blocks lose more registers with eta/s or the correction, 64 of 7 x 500 (0.72
 // of the cells) eta/s FP64 8.2 and 8.6, but 64 of 10 x 500 (0.53) 13.8 and 10.5.
+// FP32 with eta/s takes rounds of 4 steps instead, whose halos are half as wide: 128
+// of 15 x 500 208 by 8 steps, 29.9 by 4, 36.9 by the windows of 512 cells; 256 of 10
+// x 500 48, 30 and 40.
 int default_strip(const rlb_sim* h) {
-  const int small = 3, large = 4;
+  const int small = 3, large = h->precision == RLB_FP32 && h->ext && h->L.max_member > 512 ? 2 : 4;
   const rlb::TubeVariant s = rlb::d2q9_strip_variant(small), l = rlb::d2q9_strip_variant(large);
   const int rows = 2 * s.halo * (h->corr ? 2 : 1) + 1;
   for (const rlb_params& p : h->params)

@@ -52,8 +52,11 @@ def _default_is(prob, members, prec, want, steps=(9, 1)):
 ])
 def test_strip_windows_by_the_cells_they_compute(nx, ny, members, corr, eta, window):
     for prec, t in ((FP64, "double"), (FP32, "float")):
+        form = f"{window}>/h8"
+        if prec == FP32 and eta and window == 512:  # shorter rounds instead
+            form = "256>/h4"
         _default_is(_plane(nx, ny, corr, eta), members, prec,
-                    f"k_d2q9_strips<{t},{window}>/h8" + ("+c7" if corr else ""))
+                    f"k_d2q9_strips<{t},{form}" + ("+c7" if corr else ""))
 
 
 def _box(nx, ny, nz, eta=0.0):
