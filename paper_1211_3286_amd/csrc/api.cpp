@@ -435,6 +435,18 @@ int lattice_parts(const rlb_sim* h, int variant) {
                : rlb::lattice_partials(variant, h->geom);
 }
 
+// The steps left over by rounds on `tiles` windows, 1 or 2 of 3, that run one by one
+// instead, and their kernel. us a step, as a round and singly: one step of 128^2
+// FP32 6.7 and 5.1, of 300^2 9.9 and 6.5, FP64 11.2 and 8.3; two steps of 300^2 FP32
+// (346 windows, 256 CUs) 6.1 and 6.4, 450^2 (779) 9.1 and 8.9, 550^2 (1163) 11.1 and
+// 10.2; FP64 300^2 6.8 and 8.1, 550^2 14.5 and 15.8.
+int tile_singles(const rlb_sim* h, int64_t tiles, int left) {
+  if (left == 2 && h->precision == RLB_FP32 && tiles > 4 * h->num_cu) return 2;
+  return left == 1 ? 1 : 0;
+}
+
+int tile_single(const rlb_sim* h) { return h->corr ? 3 : 2; }
+
 // D2Q9 tile rounds: ceil(n / H) launches, each advancing up to H steps of the
 // whole lattice; rounds alternate the buffers (pingpong) or always read a and
 // write b (trials). *flip tells whether the state changed buffers.
@@ -458,17 +470,28 @@ rlb_status launch_tile_rounds(rlb_sim* h, int variant, int nsteps, int pingpong,
   arg.ext = h->geom.ext;
   arg.partials = h->d_partials;
   arg.bad = h->d_bad;
-  const int rounds = (nsteps + v.h - 1) / v.h;
-  for (int r = 0; r < rounds; ++r) {
+  const int singles = pingpong ? tile_singles(h, (int64_t)grid.x * grid.y, nsteps % v.h) : 0;
+  const int rounds = (nsteps - singles + v.h - 1) / v.h;
+  for (int r = 0; r < rounds + singles; ++r) {
     const bool odd = pingpong && (r & 1);
     arg.src = odd ? b : a;
     arg.dst = odd ? a : b;
+    if (r >= rounds) {
+      const bool diag = diag_every > 0 && r + 1 == rounds + singles;  // the step of the call kept
+      rlb_status st = launch_lattice_step(h, tile_single(h), diag, arg.src, arg.dst);
+      if (st != RLB_OK) return st;
+      continue;
+    }
     arg.nsteps = std::min(v.h, nsteps - r * v.h);
     arg.step0 = step0 + (int64_t)r * v.h;
     RLB_HIP(rlb::d2q9_launch_tiles(h->precision, tile_index(variant), h->corr, h->ext, arg, grid,
                                    h->stream));
   }
-  *flip = pingpong && (rounds & 1);
+  *flip = pingpong && ((rounds + singles) & 1);
+  if (pingpong && diag_every > 0) {
+    h->diag_step = step0 + nsteps;
+    h->diag_parts = lattice_parts(h, singles ? tile_single(h) : variant);
+  }
   return RLB_OK;
 }
 
@@ -954,10 +977,6 @@ rlb_status advance(rlb_sim* h, int32_t n) {
     rlb_status st =
         launch_tile_rounds(h, h->variant, n, 1, state_buf(h), spare_buf(h), D, h->steps, &flip);
     if (st != RLB_OK) return st;
-    if (D > 0) {
-      h->diag_step = h->steps + n;
-      h->diag_parts = lattice_parts(h, h->variant);
-    }
     h->steps += n;
     if (flip) h->cur = 1 - h->cur;
     return RLB_OK;

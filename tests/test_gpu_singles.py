@@ -1,0 +1,70 @@
+"""Calls of few steps, and runs with diagnostics, on handles whose kernels make
+several steps a launch: the steps left over run one by one. Populations are the
+first one-step kernel's bit for bit, lattice sums the same up to rounding."""
+
+import time
+
+import pytest
+import torch
+
+import workloads as wl
+from gpu_helpers import relmax, say
+
+pytestmark = pytest.mark.gpu
+
+FP64, FP32 = 0, 1
+
+
+def _plane(nx, ny, corr=0, bc=(0, 1, 0)):
+    p = wl.random_modes(nx, ny, 1, seed=5, umax=0.2, amp=0.1, bc=bc)
+    p.params.lattice, p.params.correction = "d2q9", corr
+    return p
+
+
+def _us(sim, calls, n=1, reps=9):
+    best = 1e30
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(calls):
+            sim.step(n)
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) / (calls * n) * 1e6)
+    return best
+
+
+@pytest.mark.parametrize("every", [0, 1, 4])
+@pytest.mark.parametrize("shape,corr,prec", [
+    ((300, 260), 0, FP32), ((300, 260), 0, FP64), ((560, 540), 0, FP32), ((145, 130), 1, FP64),
+], ids=["fp32", "fp64", "two-singles", "c7"])
+def test_tile_rounds_with_steps_left_over(shape, corr, prec, every):
+    import paper_1211_3286_amd as rlb
+    sim, ref = (rlb.from_problems([_plane(*shape, corr)], precision=prec, diag_every=every)
+                for _ in range(2))
+    sim.variant = next(i for i, n in enumerate(sim.variants()) if "tiles" in n and ",32,16>/h3" in n)
+    ref.variant = 0
+    say("tiles", shape, "prec", prec, "diagnostics every", every)
+    for n in (1, 2, 3, 4, 5, 6, 1, 8):
+        sim.step(n)
+        ref.step(n)
+        for x, y in zip(sim.populations(), ref.populations()):
+            assert bool((x == y).all()), n
+        if every:
+            a, b = sim.diagnostics(), ref.diagnostics()
+            assert a[1] == b[1] == sim.steps and relmax(a[0], b[0]) < 1e-13
+    sim.close()
+    ref.close()
+
+
+def test_single_steps_of_a_tile_default_cost_a_one_step_kernel():
+    """A loop of step(1), as a program that looks at each step runs it: the tile
+    default made a round of each, 1.5 to 1.8 times the time at these sizes."""
+    import paper_1211_3286_amd as rlb
+    sim, one = (rlb.from_problems([_plane(500, 460)], precision=FP32) for _ in range(2))
+    assert "tiles" in sim.kernel_name
+    one.variant = 2
+    a, b = _us(sim, 40), _us(one, 40)
+    say("step(1) us", f"{a:.2f}", "one-step kernel", f"{b:.2f}")
+    assert a < 1.3 * b  # between 1 and the 1.5 and more of a round
+    sim.close()
+    one.close()
