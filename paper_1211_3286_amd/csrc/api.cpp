@@ -506,18 +506,30 @@ rlb_status launch_tile_rounds(rlb_sim* h, int variant, int nsteps, int pingpong,
 //     a CU: eta/s 250^2 FP32 4.1 and 5.3, 270 x 260 7.3 and 6.5; correction 150^2
 //     FP64 4.3 and 5.8, 250^2 10.0 and 9.4; else 64 x 4 blocks with the correction,
 //     which share the neighbours' fields (1531 x 1203 FP64 128 and 135, FP32 50 and
-//     70), and 256 x 1.
+//     70), and 256 x 1. No tiles either where a window is less than half full of rows
+//     (100000 x 4 FP32 17.0 and 11.7, x 7 11.5 and 10.5; one row with the correction
+//     100000 x 1 7.4 in 64 x 4 blocks and 6.5), nor in FP32 with more than 5
+//     windows a CU (700 x 500, 1350, 10.1 and 10.4) or, with diagnostics at every
+//     step or two, which end a round's arithmetic in sums, with more than 2 (at every
+//     step 550^2, 1163 windows, 13.9 and 11.2, 300^2, 346, 6.8 and 7.5; FP64 550^2
+//     16.4 and 16.8).
 int default_lattice(const rlb_sim* h) {
   const rlb_params& p = h->params[0];
   if (!h->d2) return p.nx > 64 && p.nx <= 128 ? 2 : 1;
   const int tv = 6;
+  const rlb::TileVariant v = rlb::d2q9_tile_variant(tv);
+  const bool often = h->opt.diag_every == 1 || h->opt.diag_every == 2;
+  const int64_t per_cu = h->ext || h->corr          ? 1
+                         : h->precision == RLB_FP64 ? INT32_MAX
+                         : often                    ? 2
+                                                    : 5;
   rlb::TileRound a{};
   dim3 grid;
-  if (rlb::d2q9_tile_fits(h->precision, tv, h->corr) &&
-      tile_geometry(rlb::d2q9_tile_variant(tv), p.nx, p.ny, h->corr, a, grid) &&
-      ((!h->ext && !h->corr) || (int64_t)grid.x * grid.y <= h->num_cu))
+  if (2 * p.ny >= v.ty && rlb::d2q9_tile_fits(h->precision, tv, h->corr) &&
+      tile_geometry(v, p.nx, p.ny, h->corr, a, grid) &&
+      (int64_t)grid.x * grid.y <= per_cu * h->num_cu)
     return rlb::d2q9_num_lattice_variants() + tv;
-  return h->corr ? 3 : 2;
+  return h->corr && p.ny > 1 ? 3 : 2;
 }
 
 constexpr int kSpinLimit = 1 << 24;  // about a second of polling per wait

@@ -106,3 +106,28 @@ def test_a_large_member_among_small_ones_spreads_over_the_chip():
     sim = rlb.from_problems(probs, precision=FP64)
     assert sim.kernel_name == "k_step_cells<double,64>"
     sim.close()
+
+
+def test_tiles_by_default_where_their_windows_are_full():
+    """Thin lattices, and diagnostics at every step over many windows, keep the
+    one-step kernel; so do FP32 lattices of more than 5 windows a CU."""
+    import paper_1211_3286_amd as rlb
+    for shape, prec, every, want in (
+            ((9000, 4), FP32, 0, "lattice"), ((9000, 7), FP64, 0, "lattice"),
+            ((20000, 1), FP32, 0, "lattice"), ((2500, 8), FP32, 0, "tiles"),
+            ((550, 540), FP32, 0, "tiles"), ((550, 540), FP32, 1, "lattice"),
+            ((550, 540), FP32, 2, "lattice"), ((550, 540), FP32, 3, "tiles"),
+            ((300, 260), FP32, 1, "tiles"), ((450, 430), FP64, 1, "tiles"),
+            ((700, 500), FP32, 0, "lattice"), ((20000, 1, 1), FP32, 0, "lattice<float,256,1,1>+c7"),
+            ((10000, 2, 1), FP64, 0, "lattice<double,64,4,1>+c7")):
+        prob = _plane(*shape)
+        sim, ref = (rlb.from_problems([prob], precision=prec, diag_every=every) for _ in range(2))
+        say(shape, prec, every, sim.kernel_name)
+        assert want in sim.kernel_name, (shape, prec, every)
+        ref.variant = 0
+        sim.step(7)
+        ref.step(7)
+        for x, y in zip(sim.populations(), ref.populations()):
+            assert bool((x == y).all())
+        sim.close()
+        ref.close()
