@@ -340,8 +340,17 @@ rlb_status launch_lattice_step(rlb_sim* h, int variant, bool diag, const void* s
 }
 
 // Marching variants (D3Q19: two steps per launch, D2Q9: H); steps that do not
-// fill a launch (the last of a call, diagnostics steps) run a one-step kernel.
-int march_step(const rlb_sim* h) { return h->d2 ? 3 : 2; }
+// fill a launch (the last of a call, diagnostics steps) run a one-step kernel, in
+// blocks as the rows are long. us a step, 128 x 2, 64 x 4 and 256 x 1 blocks: D3Q19
+// 96^3 FP32 44, 47, 44, 160^3 245, 213, 208, 187 x 150 x 131 339, 319, 343, 256^3 880,
+// 874, 885; D2Q9, the last two: 300^2 FP64 6.4 and 8.2, 700 x 500 FP32 11.9 and 10.8,
+// 1000 x 800 22.8 and 20.9, 1531 x 1203 FP64 122 and 117, 2048^2 223 and 226; with
+// the correction 64 x 4 is the better one everywhere.
+int march_step(const rlb_sim* h) {
+  const int nx = h->params[0].nx;
+  if (h->d2) return h->corr || nx <= 384 ? 3 : 2;
+  return nx > 64 && nx <= 128 ? 2 : 1;
+}
 
 int march_base(const rlb_sim* h) {
   return h->d2 ? rlb::d2q9_num_lattice_variants() + rlb::d2q9_num_tile_variants()

@@ -68,3 +68,29 @@ def test_single_steps_of_a_tile_default_cost_a_one_step_kernel():
     assert a < 1.3 * b  # between 1 and the 1.5 and more of a round
     sim.close()
     one.close()
+
+
+@pytest.mark.parametrize("shape,lattice,prec,blocks", [
+    ((96, 80, 64), "d3q19", FP32, 2), ((160, 72, 64), "d3q19", FP32, 1),
+    ((45, 60, 140), "d3q19", FP64, 1), ((300, 290, 1), "d2q9", FP64, 3),
+    ((700, 400, 1), "d2q9", FP64, 2), ((1000, 300, 1), "d2q9", FP32, 2),
+], ids=["d3q19-96", "d3q19-160", "d3q19-45", "d2q9-300", "d2q9-700", "d2q9-1000"])
+def test_steps_between_marching_launches_by_row_length(shape, lattice, prec, blocks):
+    """Single and diagnostics steps of a marching handle take the block shape that
+    suits the rows: the sums are added in its order."""
+    import numpy as np
+    import paper_1211_3286_amd as rlb
+    prob = wl.random_modes(*shape, seed=8, umax=0.2, amp=0.1, bc=(0, 1, 0))
+    prob.params.lattice = lattice
+    sim, ref = (rlb.from_problems(prob, precision=prec, diag_every=1) for _ in range(2))
+    sim.variant = next(i for i, n in enumerate(sim.variants()) if "march" in n)
+    ref.variant = blocks
+    say(shape, sim.kernel_name, ref.kernel_name)
+    for n in (1, 3):
+        sim.step(n)
+        ref.step(n)
+        assert np.array_equal(sim.diagnostics()[0], ref.diagnostics()[0])
+    for x, y in zip(sim.populations(), ref.populations()):
+        assert bool((x == y).all())
+    sim.close()
+    ref.close()
