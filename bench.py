@@ -35,6 +35,7 @@ from __future__ import annotations
 import argparse
 import hashlib
 import json
+import math
 import os
 import re
 import sys
@@ -734,22 +735,29 @@ def adjoint_trace(csv_path: str, command: str, grid: str = "512x512x1",
                   steps: int = 1000) -> str:
     """Markdown summary of the reverse sweeps in a rocprofv3 kernel trace of
     the adjoint form: launches and durations of the reverse step (k_adj_step)
-    and the recomputation (k_gstep) on one lattice's grid, how many reverse
-    steps a recomputation kernel overlapped in time, and per sweep the span
-    against the sum of its kernels' durations (a sweep: `steps` consecutive
-    reverse steps, one gradient of a run of that many steps)."""
+    and the recomputation (k_gstep) on one lattice (`grid`, or any launch grid
+    of as many threads), how many reverse steps a recomputation kernel
+    overlapped in time, and per sweep the span against the sum of its kernels'
+    durations (a sweep: `steps` consecutive reverse steps, one gradient of a run
+    of that many steps). Small lattices run both steps in one kernel
+    (k_sweep_pair), which counts as a reverse step."""
     import csv
     import statistics
 
+    cells = math.prod(int(n) for n in grid.split("x"))
+    kinds = {"k_adj_step": "adj", "k_gstep": "g", "k_sweep_pair": "pair"}
     rows = []
     for r in csv.DictReader(open(csv_path)):
-        name = r["Kernel_Name"]
-        kind = "adj" if "k_adj_step" in name else ("g" if "k_gstep" in name else None)
-        if kind is None or "x".join(r[f"Grid_Size_{a}"] for a in "XYZ") != grid:
+        kind = next((v for k, v in kinds.items() if k in r["Kernel_Name"]), None)
+        threads = math.prod(int(r[f"Grid_Size_{a}"]) for a in "XYZ")
+        # a pair: the blocks of both steps, either kind rounded up to 8 of 256 threads
+        if kind is None or (threads != cells if kind != "pair"
+                            else not 2 * cells <= threads < 2 * cells + 16 * 256):
             continue
         rows.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), kind))
     rows.sort()
-    adj = [(s, e) for s, e, k in rows if k == "adj"]
+    adj = [(s, e) for s, e, k in rows if k != "g"]
+    pairs = [(s, e) for s, e, k in rows if k == "pair"]
     rec = [(s, e) for s, e, k in rows if k == "g"]
     out = [f"Command: `{command}`", ""]
     if not adj:
@@ -776,7 +784,11 @@ def adjoint_trace(csv_path: str, command: str, grid: str = "512x512x1",
     out += [f"Kernels on the {grid} grid:", "",
             "| kernel | launches | mean (us) | median (us) |", "|---|---|---|---|",
             f"| `k_adj_step` (reverse step) | {na} | {ma:.2f} | {da:.2f} |",
-            f"| `k_gstep` (recomputation) | {ng} | {mg:.2f} | {dg:.2f} |", "",
+            f"| `k_gstep` (recomputation) | {ng} | {mg:.2f} | {dg:.2f} |"]
+    if pairs:
+        np_, mp, dp = stat(pairs)
+        out += [f"| `k_sweep_pair` (both; of the reverse steps above) | {np_} | {mp:.2f} | {dp:.2f} |"]
+    out += ["",
             f"Reverse steps overlapped in time by a recomputation kernel: {overlapped} of {na} "
             f"({100.0 * overlapped / na:.1f} %).", "",
             "| sweep | reverse steps | span (ms) | reverse-step time (ms) | recomputation time "
@@ -870,7 +882,9 @@ def summarize_trace(csv_path: str, command: str, top: int = 25, min_launches: in
         groups = collections.defaultdict(list)
         for r in csv.DictReader(open(trace)):
             name = short(r["Kernel_Name"])
-            if not name.startswith(("k_step", "k_adj_step", "k_gstep", "k_d2q9_lattice", "k_d2q9_members")):
+            if not name.startswith(("k_step", "k_adj_step", "k_gstep", "k_sweep_pair",
+                                    "k_d2q9_lattice", "k_d2q9_members", "k_d2q9_march",
+                                    "k_d2q9_tiles", "k_d2q9_strips", "k_d2q9_cells")):
                 continue
             grid = "x".join(r[f"Grid_Size_{a}"] for a in "XYZ")
             block = "x".join(r[f"Workgroup_Size_{a}"] for a in "XYZ")
@@ -964,7 +978,7 @@ def valu_summary(csv_path: str, command: str) -> str:
     dur = collections.defaultdict(dict)
     for r in csv.DictReader(open(csv_path)):
         name = short(r["Kernel_Name"])
-        if not name.startswith(("k_step", "k_d2q9", "k_adj_step", "k_gstep")):
+        if not name.startswith(("k_step", "k_d2q9", "k_adj_step", "k_gstep", "k_sweep_pair")):
             continue
         key = (name, int(r["Grid_Size"]), int(r["Workgroup_Size"]))
         groups[key][r["Counter_Name"]].append(float(r["Counter_Value"]))

@@ -216,3 +216,43 @@ def test_adjoint_traffic_summary(tmp_path):
     # (38 + 19 * 1.1) / 57 = 1.0333
     assert "| `k_adj_step<float, true>` | 3 | 6.2259e+05 | 3.4243e+05 | 1.0333 |" in md
     assert "| `k_gstep<float>` | 3 | 3.1130e+05 | 3.1130e+05 | 1.0000 |" in md
+
+
+def _trace(path, rows):
+    import csv
+    with open(path, "w", newline="") as fh:
+        w = csv.writer(fh)
+        w.writerow(["Kernel_Name", "Start_Timestamp", "End_Timestamp",
+                    "Grid_Size_X", "Grid_Size_Y", "Grid_Size_Z"])
+        w.writerows(rows)
+
+
+def test_adjoint_trace_reads_the_kernels_of_the_sweep(tmp_path):
+    """The names and launch grids the sweep has: one dimension of blocks of 64 x 4
+    threads, and on small lattices one kernel for both steps."""
+    import os
+    import re
+    here = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    with open(os.path.join(here, "paper_1211_3286_amd", "csrc", "adjoint.hip")) as fh:
+        src = fh.read()
+    sweep = set(re.findall(r"void (k_\w+)\(SweepLaunch<T> a\)", src))
+    assert sweep == {"k_adj_step", "k_gstep", "k_sweep_pair"}
+    p = tmp_path / "run_kernel_trace.csv"
+    rows = [[f"void rlb::k_adj_step<float, {g}>(rlb::SweepLaunch<float>)", 20000 * i,
+             20000 * i + 13000, 65536, 4, 1] for i, g in enumerate(["false"] + ["true"] * 9)]
+    rows += [["void rlb::k_gstep<float>(rlb::SweepLaunch<float>)", 20000 * i + 1000,
+              20000 * i + 9000, 65536, 4, 1] for i in range(4)]
+    _trace(p, rows)
+    md = bench.adjoint_trace(str(p), "cmd", steps=10)
+    assert "| `k_adj_step` (reverse step) | 10 | 13.00 | 13.00 |" in md
+    assert "| `k_gstep` (recomputation) | 4 | 8.00 | 8.00 |" in md
+    assert "4 of 10 (40.0 %)" in md and "k_sweep_pair" not in md
+    # 64 x 60 cells: 15 row blocks of either kind, 32 in a pair
+    rows = [["void rlb::k_gstep<float>(x)", 5000 * i, 5000 * i + 3000, 960, 4, 1] for i in range(4)]
+    rows += [["void rlb::k_sweep_pair<float, true>(x)", 5000 * i, 5000 * i + 4000, 2048, 4, 1]
+             for i in range(4, 8)]
+    rows += [["void rlb::k_adj_step<float, true>(x)", 40000, 43500, 960, 4, 1]]
+    _trace(p, rows)
+    md = bench.adjoint_trace(str(p), "cmd", grid="64x60x1", steps=5)
+    assert "| `k_sweep_pair` (both; of the reverse steps above) | 4 | 4.00 | 4.00 |" in md
+    assert "| 0 | 5 |" in md
