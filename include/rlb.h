@@ -181,7 +181,10 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
                     const double* u0, int32_t fields_on_device, void* workspace,
                     size_t workspace_bytes, void* hip_stream);
 
-/* Advance every member by nsteps >= 0 steps, asynchronously on the stream.
+/* Advance every member by nsteps >= 0 steps, asynchronously on the stream: the
+ * call only launches kernels (and may be captured into a HIP graph), except that
+ * the first step in a round or segmented variant chosen by rlb_set_variant or
+ * rlb_tune copies its segment table to the device and waits for that.
  * One step of a cell is the update of Sec. II and V.A: streaming, the left-
  * hand side of Eqs. (5), (6) and (35) (pull from x - e_a); the moments of
  * Eq. (10) and the recovery of (n, eps, P, gamma, u) from them; the

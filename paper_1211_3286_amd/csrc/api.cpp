@@ -717,11 +717,10 @@ int strip_index(int v) { return v - rlb::d2q9_num_member_variants(); }
 // Tube segments for a tube variant: owned ranges of at most NT - 2H cells,
 // windows extended by H halo cells (cut at zero-gradient ends); a tube that
 // fits the block whole is one segment with exact ends.
-rlb_status build_tube_segments(rlb_sim* h, int tv) {
+rlb_status build_tube_segments(rlb_sim* h, int tv, std::vector<rlb::TubeSeg>& segs) {
   rlb::TubeVariant v = rlb::tube_variant(tv);
   v.halo = tube_halo(h, v);
   const int S = v.nt - 2 * v.halo;
-  std::vector<rlb::TubeSeg> segs;
   for (int m = 0; m < h->n_members; ++m) {
     const MemberDesc& d = h->descs[m];
     const int L = d.nz;
@@ -754,7 +753,6 @@ rlb_status build_tube_segments(rlb_sim* h, int tv) {
   if ((int64_t)segs.size() > h->L.max_segs) return RLB_E_ARG;
   RLB_HIP(hipMemcpyAsync(h->d_segs, segs.data(), sizeof(rlb::TubeSeg) * segs.size(),
                          hipMemcpyHostToDevice, h->stream));
-  RLB_HIP(hipStreamSynchronize(h->stream));
   h->nseg = (int)segs.size();
   h->seg_whole = h->nseg == h->n_members;  // a cut member has two or more
   h->seg_halo = v.halo;
@@ -767,11 +765,10 @@ rlb_status build_tube_segments(rlb_sim* h, int tv) {
 // R - 2H rows; a member of at most R rows is one segment with exact ends.
 // RLB_E_UNSUPPORTED when a member is wider than the block or leaves no
 // owned row.
-rlb_status build_strip_segments(rlb_sim* h, int sv) {
+rlb_status build_strip_segments(rlb_sim* h, int sv, std::vector<rlb::TubeSeg>& segs) {
   rlb::TubeVariant v = rlb::d2q9_strip_variant(sv);
   v.halo = strip_halo(h, v);
   const int hr = h->corr ? 2 * v.halo : v.halo;
-  std::vector<rlb::TubeSeg> segs;
   for (int m = 0; m < h->n_members; ++m) {
     const MemberDesc& d = h->descs[m];
     if (d.nx > v.nt) return RLB_E_UNSUPPORTED;
@@ -808,12 +805,22 @@ rlb_status build_strip_segments(rlb_sim* h, int sv) {
   if ((int64_t)segs.size() > h->L.max_segs) return RLB_E_ARG;
   RLB_HIP(hipMemcpyAsync(h->d_segs, segs.data(), sizeof(rlb::TubeSeg) * segs.size(),
                          hipMemcpyHostToDevice, h->stream));
-  RLB_HIP(hipStreamSynchronize(h->stream));
   h->nseg = (int)segs.size();
   h->seg_whole = h->nseg == h->n_members;  // a cut member has two or more
   h->seg_halo = v.halo;
   h->seg_built = 2000 + sv;
   return RLB_OK;
+}
+
+// The device table of a round variant's segments, unless it is there already. The
+// copy is enqueued: segs, empty if there was nothing to do, must outlive it.
+rlb_status build_round_segments(rlb_sim* h, int variant, std::vector<rlb::TubeSeg>& segs) {
+  if (h->d2) {
+    const int sv = strip_index(variant);
+    return h->seg_built == 2000 + sv ? RLB_OK : build_strip_segments(h, sv, segs);
+  }
+  const int tv = tube_index(variant);
+  return h->seg_built == 1000 + tv ? RLB_OK : build_tube_segments(h, tv, segs);
 }
 
 // Tube rounds: ceil(n / H) launches (one when every member fits its block
@@ -829,22 +836,16 @@ rlb_status launch_tubes(rlb_sim* h, int variant, int nsteps, int pingpong, void*
                         int diag_every, int64_t step0, bool* flip) {
   const void* func;
   dim3 block;
-  if (h->d2) {
-    const int sv = strip_index(variant);
-    if (h->seg_built != 2000 + sv) {
-      rlb_status st = build_strip_segments(h, sv);
-      if (st != RLB_OK) return st;
-    }
-    RLB_HIP(rlb::d2q9_strip_kernel(h->precision, sv, h->corr, h->ext, &func, &block));
-  } else {
-    const int tv = tube_index(variant);
-    if (!h->all_tubes) return RLB_E_UNSUPPORTED;
-    if (h->seg_built != 1000 + tv) {
-      rlb_status st = build_tube_segments(h, tv);
-      if (st != RLB_OK) return st;
-    }
-    RLB_HIP(rlb::tube_kernel(h->precision, tv, h->ext, &func, &block));
-  }
+  if (!h->d2 && !h->all_tubes) return RLB_E_UNSUPPORTED;
+  std::vector<rlb::TubeSeg> segs;
+  rlb_status st = build_round_segments(h, variant, segs);
+  if (st != RLB_OK) return st;
+  if (!segs.empty()) RLB_HIP(hipStreamSynchronize(h->stream));
+  if (h->d2)
+    RLB_HIP(rlb::d2q9_strip_kernel(h->precision, strip_index(variant), h->corr, h->ext, &func,
+                                   &block));
+  else
+    RLB_HIP(rlb::tube_kernel(h->precision, tube_index(variant), h->ext, &func, &block));
   const int per = h->seg_whole ? nsteps : h->seg_halo;
   const int rounds = (nsteps + per - 1) / per;
   rlb::TubeRound arg{};
@@ -1285,6 +1286,12 @@ rlb_status rlb_init(rlb_handle* out, const rlb_params* members, int32_t n_member
     rlb_status ts = rlb::tape_init(h->tape, L.tape, h->ws + L.off_tape, h->precision, L.ncells,
                                    L.cs, opt->ckpt_every, opt->tape_steps, dn, de, du,
                                    h->buf[0], h->stream);
+    if (ts != RLB_OK) return fail(ts);
+  }
+  // The default's segments too, so that no step of a fresh handle waits.
+  std::vector<rlb::TubeSeg> segs;
+  if (is_tube_variant(h, h->variant) || is_strip_variant(h, h->variant)) {
+    const rlb_status ts = build_round_segments(h, h->variant, segs);
     if (ts != RLB_OK) return fail(ts);
   }
   rlb::HostView view;
