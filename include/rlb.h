@@ -246,10 +246,14 @@ rlb_status rlb_grad(rlb_handle h, const double* dL_du, const double* dL_deps,
  * waves per SIMD run instead of 4; for round and marching kernels the steps per
  * launch, "/hH"; tube rounds take fewer, no less than half, and strip rounds
  * more, up to twice as many, as the segments then load the CUs) of the path
- * this handle dispatches to. rlb_tune times every variant with HIP events on
+ * this handle dispatches to. A marching variant that cannot launch on the handle's
+ * lattice (D3Q19 stored in planes: a tape, or small; D2Q9 of fewer than 64 columns
+ * between faces or 8 rows) runs one-step kernels; its name is theirs, ending in
+ * "(no march)". rlb_tune times every variant with HIP events on
  * trial steps that read the current state and write only the spare buffer (the
  * state is unchanged), selects the fastest, and returns all timings (ms per
- * step, host array of rlb_num_variants doubles, may be NULL). */
+ * step, host array of rlb_num_variants doubles, may be NULL; HUGE_VAL for variants
+ * the handle cannot run). */
 rlb_status rlb_num_variants(rlb_handle h, int32_t* count);
 rlb_status rlb_variant_name(rlb_handle h, int32_t variant, char* buf, size_t buflen);
 rlb_status rlb_set_variant(rlb_handle h, int32_t variant);

@@ -1113,6 +1113,18 @@ const char* kernel_name_of(const rlb_sim* h, int v) {
   return rlb::tube_kernel_name(h->precision, tube_index(v));
 }
 
+// A marching variant that cannot launch on this lattice runs single steps: it has
+// the name of their kernel.
+bool is_idle_march(const rlb_sim* h, int v) {
+  return is_march_variant(h, v) && march_steps(h, v) < 2;
+}
+
+void put_name(const rlb_sim* h, int v, char* buf, size_t buflen) {
+  const bool idle = is_idle_march(h, v);
+  std::snprintf(buf, buflen, "%s%s%s", kernel_name_of(h, idle ? march_step(h) : v),
+                h->corr ? "+c7" : "", idle ? " (no march)" : "");
+}
+
 // A persistent segment launch whose neighbour wait timed out leaves a sticky
 // error word; it is reported at the next synchronising call.
 rlb_status persistent_error(rlb_sim* h) {
@@ -1489,7 +1501,7 @@ rlb_status rlb_variant_name(rlb_handle h, int32_t v, char* buf, size_t buflen) {
   int32_t n;
   if (rlb_num_variants(h, &n) != RLB_OK || !buf || buflen == 0) return RLB_E_ARG;
   if (v < 0 || v >= n) return RLB_E_ARG;
-  std::snprintf(buf, buflen, "%s%s", kernel_name_of(h, v), h->corr ? "+c7" : "");
+  put_name(h, v, buf, buflen);
   return RLB_OK;
 }
 
@@ -1526,7 +1538,7 @@ rlb_status rlb_tune(rlb_handle h, int32_t trial_steps, int32_t* best_variant,
   rlb_status st = RLB_OK;
   for (int v = 0; v < n && st == RLB_OK; ++v) {
     float ms = 0.0f;
-    bool usable = true;
+    bool usable = !is_idle_march(h, v);  // else another variant's kernel, timed already
     for (int rep = 0; rep < 2 && st == RLB_OK && usable; ++rep) {  // rep 0 warms up
       if (hipEventRecord(e0, h->stream) != hipSuccess) st = RLB_E_DEVICE;
       if (h->lattice && is_tile_variant(h, v)) {
@@ -1582,9 +1594,7 @@ rlb_status rlb_tune(rlb_handle h, int32_t trial_steps, int32_t* best_variant,
 rlb_status rlb_info(rlb_handle h, int64_t* steps, char* kernel_name, size_t buflen) {
   if (!h) return RLB_E_ARG;
   if (steps) *steps = h->steps;
-  if (kernel_name && buflen)
-    std::snprintf(kernel_name, buflen, "%s%s", kernel_name_of(h, h->variant),
-                  h->corr ? "+c7" : "");
+  if (kernel_name && buflen) put_name(h, h->variant, kernel_name, buflen);
   return RLB_OK;
 }
 
