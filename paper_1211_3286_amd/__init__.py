@@ -16,6 +16,7 @@ models: D3Q19 (default) and the D2Q9 MRT model of Sec. V.A
 from __future__ import annotations
 
 import ctypes
+import hashlib
 import json
 import os
 from typing import Dict, List, Optional, Sequence
@@ -341,16 +342,19 @@ class Simulation:
         """Time every kernel variant (the native autotuner) and keep the fastest.
 
         With ``cache`` (a JSON file path), a previous choice for ``key`` is
-        reused instead of timing again, and new results are stored.
+        reused instead of timing again, and new results are stored. A stored
+        choice counts only while this handle has a variant of that number and
+        name.
         """
         key = key or self.tune_key()
+        names = self.variants()
         if cache and os.path.exists(cache):
             with open(cache) as fh:
                 db = json.load(fh)
-            if key in db:
-                self.variant = int(db[key]["variant"])
-                return db[key]
-        names = self.variants()
+            rec = db.get(key)
+            if rec and dict(enumerate(names)).get(rec["variant"]) == rec["name"]:
+                self.variant = rec["variant"]
+                return rec
         ms = (ctypes.c_double * len(names))()
         best = ctypes.c_int32(0)
         _check(lib().rlb_tune(self.h, int(trial_steps), ctypes.byref(best), ms), "rlb_tune")
@@ -367,11 +371,22 @@ class Simulation:
         return res
 
     def tune_key(self) -> str:
+        """What the choice of a variant depends on: device, model, precision, the
+        shapes and faces of the members, whether the cells work out their own
+        relaxation times or equation of state, and whether there is a tape."""
         torch = self.torch
         dev = torch.cuda.get_device_name(self.device)
-        shapes = [(int(p.nx), int(p.ny), int(p.nz)) for p in self.members]
-        shape = shapes[0] if len(shapes) == 1 else f"{len(shapes)}x{self.ncells}"
-        lat = ("d2q9|" if self.lattice == D2Q9 else "") + ("c7|" if self.opt.correction else "")
+        eta = any(c.eta_over_s > 0.0 for c in self._arr)
+        eos = any(c.mass != 0.0 or c.eos_gamma not in (0.0, 4.0 / 3.0) for c in self._arr)
+        members = [(c.nx, c.ny, c.nz, tuple(c.bc)) for c in self._arr]
+        if len(members) == 1:
+            shape = f"{members[0][:3]}|bc{members[0][3]}"
+        else:
+            h = hashlib.sha256(repr(members).encode()).hexdigest()[:16]
+            shape = f"{len(members)}x{self.ncells}|{h}"
+        flags = [("d2q9", self.lattice == D2Q9), ("c7", self.opt.correction), ("eta", eta),
+                 ("eos", eos), ("tape", self.opt.ckpt_every > 0)]
+        lat = "".join(f"{name}|" for name, on in flags if on)
         return f"{dev}|{lat}{'fp32' if self.precision == FP32 else 'fp64'}|{shape}"
 
 

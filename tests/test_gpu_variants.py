@@ -41,3 +41,37 @@ def test_marching_variants_that_cannot_march(make, kw, steps):
     assert res["variant"] not in idle and "march" not in res["name"]
     assert res["ms_per_step"][names[idle[0]]] == math.inf
     sim.close()
+
+
+def test_tuning_cache_tells_handles_apart(tmp_path):
+    """Handles that dispatch to other kernels have other keys, and a stored choice
+    is taken only where its number and name still are a variant."""
+    import paper_1211_3286_amd as rlb
+    box = _modes((64, 48, 40))
+    eta = _modes((64, 48, 40))
+    eta.params.eta_s = 0.1
+    eos = _modes((64, 48, 40))
+    eos.params.eos_gamma = 1.5
+    clamped = _modes((64, 48, 40), bc=(1, 0, 0))
+    tubes = [wl.tube_batch(n_tubes=1, seed=s, lmin=L, lmax=L)[0] for s, L in ((1, 300), (2, 500))]
+    others = [wl.tube_batch(n_tubes=1, seed=s, lmin=L, lmax=L)[0] for s, L in ((1, 350), (2, 450))]
+    sims = [rlb.from_problems(p, precision=FP32, **kw) for p, kw in (
+        (box, {}), (box, {"ckpt_every": 2, "tape_steps": 4}), (eta, {}), (eos, {}), (clamped, {}),
+        (tubes, {}), (others, {}))]
+    keys = [s.tune_key() for s in sims]
+    say(*keys)
+    assert len(set(keys)) == len(keys)
+    again = rlb.from_problems(tubes, precision=FP32)
+    assert again.tune_key() == keys[5]
+    cache = tmp_path / "tune.json"
+    first = sims[0].tune(trial_steps=2, cache=str(cache))
+    assert sims[0].tune(trial_steps=2, cache=str(cache)) == first
+    db = json.loads(cache.read_text())
+    # a choice under this key that the handle does not have: timed anew
+    for variant, name in ((500, first["name"]), (first["variant"], "k_gone<float>")):
+        db[keys[0]] = dict(first, variant=variant, name=name)
+        cache.write_text(json.dumps(db))
+        res = sims[0].tune(trial_steps=2, cache=str(cache))
+        assert res["name"] == sims[0].variants()[res["variant"]] == sims[0].kernel_name
+    for s in sims + [again]:
+        s.close()
