@@ -896,6 +896,11 @@ rlb_status build_segments(rlb_sim* h, int sv) {
   if ((int64_t)segs.size() > h->L.max_segs) return RLB_E_ARG;
   RLB_HIP(hipMemcpyAsync(h->d_segs, segs.data(), sizeof(rlb::Segment) * segs.size(),
                          hipMemcpyHostToDevice, h->stream));
+  // Every flag counts from here: a table of fewer segments has left those beyond it
+  // behind the epoch, where their neighbours would wait for them in vain.
+  RLB_HIP(rlb::launch_begin(nullptr, 0, h->d_flags, (size_t)h->L.max_segs, nullptr, nullptr,
+                            h->stream));
+  h->epoch = 0;
   RLB_HIP(hipStreamSynchronize(h->stream));
   h->nseg = (int)segs.size();
   h->seg_built = sv;

@@ -75,3 +75,31 @@ def test_tuning_cache_tells_handles_apart(tmp_path):
         assert res["name"] == sims[0].variants()[res["variant"]] == sims[0].kernel_name
     for s in sims + [again]:
         s.close()
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32], ids=["fp64", "fp32"])
+def test_segmented_variants_in_any_order(prec):
+    """A table of many segments after one of few: the flags beyond the few had
+    stayed behind, and the launch gave up its waits with RLB_E_DEVICE. The tuner,
+    which goes through the tables, can be called again."""
+    import paper_1211_3286_amd as rlb
+    probs = [_modes((13, 11, 21)), _modes((9, 7, 16), bc=(1, 1, 1))]
+    probs += wl.tube_batch(n_tubes=2, lmin=1500, lmax=2500, seed=5)
+    sim, ref = (rlb.from_problems(probs, precision=prec) for _ in range(2))
+    seg = [v for v, n in enumerate(sim.variants()) if "segments" in n]
+    ref.variant = 0
+    for v in (seg[-1], seg[0], seg[1], seg[0], seg[-1], seg[0]):
+        say("segments", sim.variants()[v])
+        sim.variant = v
+        sim.step(3)
+        ref.step(3)
+        for x, y in zip(sim.populations(), ref.populations()):
+            assert bool((x == y).all())
+    for _ in range(3):
+        sim.tune(trial_steps=2)
+        sim.step(2)
+        ref.step(2)
+    for x, y in zip(sim.populations(), ref.populations()):
+        assert bool((x == y).all())
+    sim.close()
+    ref.close()
