@@ -249,8 +249,9 @@ rlb_status rlb_grad(rlb_handle h, const double* dL_du, const double* dL_deps,
  * this handle dispatches to. A marching variant that cannot launch on the handle's
  * lattice (D3Q19 stored in planes: a tape, or small; D2Q9 of fewer than 64 columns
  * between faces or 8 rows) runs one-step kernels; its name is theirs, ending in
- * "(no march)". rlb_tune times every variant with HIP events on
- * trial steps that read the current state and write only the spare buffer (the
+ * "(no march)". rlb_tune times every variant with HIP events on trial steps,
+ * trial_steps rounded up to whole launches of the variant, that read
+ * the current state and write only the spare buffer (the
  * state is unchanged), selects the fastest, and returns all timings (ms per
  * step, host array of rlb_num_variants doubles, may be NULL; HUGE_VAL for variants
  * the handle cannot run). */

@@ -1130,6 +1130,16 @@ void put_name(const rlb_sim* h, int v, char* buf, size_t buflen) {
                 h->corr ? "+c7" : "", idle ? " (no march)" : "");
 }
 
+// Steps of a variant's launch where it makes a number of its own, else 1.
+int launch_steps(const rlb_sim* h, int v) {
+  if (is_march_variant(h, v)) return march_steps(h, v);
+  if (is_tile_variant(h, v)) return rlb::d2q9_tile_variant(tile_index(v)).h;
+  if (is_tube_variant(h, v))
+    return h->all_tubes ? tube_halo(h, rlb::tube_variant(tube_index(v))) : 1;
+  if (is_strip_variant(h, v)) return strip_halo(h, rlb::d2q9_strip_variant(strip_index(v)));
+  return 1;
+}
+
 // A persistent segment launch whose neighbour wait timed out leaves a sticky
 // error word; it is reported at the next synchronising call.
 rlb_status persistent_error(rlb_sim* h) {
@@ -1542,31 +1552,30 @@ rlb_status rlb_tune(rlb_handle h, int32_t trial_steps, int32_t* best_variant,
   double best_ms = 1e300;
   rlb_status st = RLB_OK;
   for (int v = 0; v < n && st == RLB_OK; ++v) {
+    // whole launches: a part of one would price the variant by its start, or by
+    // another's kernel
+    const int one = launch_steps(h, v);
+    const int steps = (int)std::min<int64_t>((trial_steps + (int64_t)one - 1) / one * one,
+                                             INT32_MAX / one * one);
     float ms = 0.0f;
     bool usable = !is_idle_march(h, v);  // else another variant's kernel, timed already
     for (int rep = 0; rep < 2 && st == RLB_OK && usable; ++rep) {  // rep 0 warms up
       if (hipEventRecord(e0, h->stream) != hipSuccess) st = RLB_E_DEVICE;
       if (h->lattice && is_tile_variant(h, v)) {
         bool flip = false;
-        st = launch_tile_rounds(h, v, trial_steps, 0, state_buf(h), spare_buf(h), 0, 0, &flip);
+        st = launch_tile_rounds(h, v, steps, 0, state_buf(h), spare_buf(h), 0, 0, &flip);
         if (st == RLB_E_UNSUPPORTED) {  // a tiled axis leaves no owned cell
           usable = false;
           st = RLB_OK;
         }
       } else if (h->lattice) {
         const bool march = is_march_variant(h, v);
-        const int per = march ? march_steps(h, v) : 1;
-        for (int i = 0; i < trial_steps && st == RLB_OK; i += per) {
-          if (per > 1 && i + per <= trial_steps)
-            st = launch_march(h, v, state_buf(h), spare_buf(h));
-          else
-            for (int k = i; k < std::min(i + per, trial_steps) && st == RLB_OK; ++k)
-              st = launch_lattice_step(h, march ? march_step(h) : v, false, state_buf(h),
-                                       spare_buf(h));
-        }
+        for (int i = 0; i < steps && st == RLB_OK; i += launch_steps(h, v))
+          st = march ? launch_march(h, v, state_buf(h), spare_buf(h))
+                     : launch_lattice_step(h, v, false, state_buf(h), spare_buf(h));
       } else if (st == RLB_OK) {
         bool flip = false;
-        st = launch_persistent(h, v, trial_steps, 0, state_buf(h), spare_buf(h), 0, 0, &flip);
+        st = launch_persistent(h, v, steps, 0, state_buf(h), spare_buf(h), 0, 0, &flip);
         if (st == RLB_E_UNSUPPORTED) {  // segments do not all fit at once
           usable = false;
           st = RLB_OK;
@@ -1578,7 +1587,7 @@ rlb_status rlb_tune(rlb_handle h, int32_t trial_steps, int32_t* best_variant,
       if (st == RLB_OK && usable && hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
         st = RLB_E_DEVICE;
     }
-    const double per = usable ? (double)ms / trial_steps : HUGE_VAL;
+    const double per = usable ? (double)ms / steps : HUGE_VAL;
     if (ms_per_step) ms_per_step[v] = per;
     if (st == RLB_OK && usable && per < best_ms) {
       best_ms = per;

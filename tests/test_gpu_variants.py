@@ -103,3 +103,32 @@ def test_segmented_variants_in_any_order(prec):
         assert bool((x == y).all())
     sim.close()
     ref.close()
+
+
+@pytest.mark.parametrize("make,prec,variant,steps", [
+    (lambda: _modes((2048, 2048, 1), "d2q9"), FP64, "k_d2q9_march<double>/h4", 80),
+    (lambda: wl.shock_tube(800), FP64, "k_step_tubes<double,128>/h32", 640),
+    (lambda: _modes((4, 800, 1), "d2q9"), FP64, "k_d2q9_strips<double,256>/h8", 320),
+], ids=["march", "tubes", "strips"])
+def test_the_tuner_prices_whole_launches(make, prec, variant, steps):
+    """Five trial steps of a kernel that makes 4, 16 or 32 a launch cost what long
+    runs cost a step: timed as one launch and single steps, or as a part of a
+    round, they read 1.4 times that and more."""
+    import time
+    import torch
+    import paper_1211_3286_amd as rlb
+    sim = rlb.from_problems(make(), precision=prec)
+    ratios = []
+    for _ in range(5):
+        priced = sim.tune(trial_steps=5)["ms_per_step"][variant] * 1e3
+        sim.variant = sim.variants().index(variant)
+        sim.step(steps)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        sim.step(steps)
+        torch.cuda.synchronize()
+        run = (time.perf_counter() - t0) / steps * 1e6
+        say(variant, f"priced {priced:.2f} us, run {run:.2f} us a step")
+        ratios.append(priced / run)
+    assert sorted(ratios)[2] < 1.25
+    sim.close()
