@@ -10,7 +10,7 @@ kernel the tuner picks makes two per launch.
 
 Also reported ("forms"): the same step in FP64, the 1 x 1 x 800 FP64 shock
 tube (2000 steps), the batch of 64 ragged shock tubes (3000 steps, in rounds
-of H steps a launch: launches states how many), the adjoint gradient of a 512
+of H steps a launch: launches states the least and most), the adjoint gradient of a 512
 x 512 run (1000 steps, checkpoints every 50), the 512^3 blast, the D2Q9 MRT
 model of Sec. V (a 4096^2 lattice, the 4 x 800 Cases A-D batch, the correction
 of Eqs. 37-38), and relaxation times set per cell from eta/s. Every form
@@ -175,20 +175,25 @@ def steps_per_pass(kernel: str) -> int:
 
 
 def launch_shape(kernel: str, steps: int) -> dict:
-    """Launches of one rlb_step on the persistent path and steps per launch, at
-    the H of the variant's name (tube rounds may take as few as half of it,
-    strip rounds as many as twice)."""
+    """Launches of one rlb_step on the persistent path and steps per launch. The
+    library cuts rounds to the load of the CUs, tube rounds to no less than half
+    the H of the variant's name and strip rounds to no more than twice it, for
+    members larger than a window: the least and the most of both are given."""
     if "_cells<" in kernel:
         return {"launches": steps, "steps_per_launch": 1}
     g = graph_shape(kernel, steps)
-    return {"launches": g["kernel_nodes"], "steps_per_launch": g["steps_per_node"]}
+    h = g["steps_per_node"]
+    if g["kernel_nodes"] == 1 or "/h" not in kernel:
+        return {"launches": g["kernel_nodes"], "steps_per_launch": h}
+    lo, hi = (-(-h // 2), h) if "tubes" in kernel else (h, 2 * h)
+    return {"launches": [-(-steps // hi), -(-steps // lo)], "steps_per_launch": [lo, hi]}
 
 
 def graph_shape(kernel: str, steps: int) -> dict:
-    """One rlb_step of a persistent-path variant as a chain of launches: the
-    tube and strip rounds are ceil(steps / H) of them (H steps each, from the
-    variant name's /hH); the one-block and segmented kernels do every step in
-    one."""
+    """One rlb_step of a persistent-path variant as a chain of launches of the
+    steps its name tells: the tube and strip rounds are ceil(steps / H) of them
+    (the variant name's /hH); the one-block and segmented kernels do every step
+    in one. (graph_launches: one chain, whether or not a caller captures it.)"""
     m = re.search(r"/h(\d+)", kernel)
     h = int(m.group(1)) if m else None
     return {"graph_launches": 1, "kernel_nodes": -(-steps // h) if h else 1,

@@ -256,3 +256,17 @@ def test_adjoint_trace_reads_the_kernels_of_the_sweep(tmp_path):
     md = bench.adjoint_trace(str(p), "cmd", grid="64x60x1", steps=5)
     assert "| `k_sweep_pair` (both; of the reverse steps above) | 4 | 4.00 | 4.00 |" in md
     assert "| 0 | 5 |" in md
+
+
+def test_launch_shape_claims_no_more_than_the_name_tells():
+    """The library cuts rounds by its own rule on the members and CUs: 64 tubes at
+    h16 take 11 steps a launch on 256 CUs, four 4 x 800 members at h4 take 8."""
+    tubes = bench.launch_shape("k_step_tubes<float,256>/h16", 3000)
+    assert tubes == {"launches": [188, 375], "steps_per_launch": [8, 16]}
+    assert tubes["launches"][0] <= -(-3000 // 11) <= tubes["launches"][1]
+    strips = bench.launch_shape("k_d2q9_strips<double,128>/h4", 400)
+    assert strips == {"launches": [50, 100], "steps_per_launch": [4, 8]}
+    assert bench.launch_shape("k_step_cells<float,64>", 50) == {
+        "launches": 50, "steps_per_launch": 1}
+    assert bench.launch_shape("k_step_members<float,512,1>", 3000) == {
+        "launches": 1, "steps_per_launch": 3000}
