@@ -306,9 +306,24 @@ __device__ __forceinline__ bool float_in_doubt(double x) {
 // populations. One step of 1000 x 800 D2Q9 FP64 (marching) 32 and 26 us; 8 steps of
 // the four Cases of 4 x 800 cells, FP64, 17 and 14; 160^3 FP32 (one-step) 236 and
 // 207.
-template <typename C>
+//
+// PRINTED: the printed form alone, for FP32 kernels with a loop around the
+// collision. There both forms' constants stay in scalar registers across the loop,
+// more than there are (252 v_readlane where the printed form has 70), and the two
+// need more vector registers (131 for 108: 3 waves a SIMD for 4). us a step of the
+// member kernels, both forms and the printed one: D2Q9 4 x 3 cells 3.1 and 2.1, 300
+// of 40^2 29.4 and 17.7, D3Q19 600 of 8^3 28.3 and 24.9; 256 x 1
+// blocks of 4 cells a thread, 40^3 34.0 and 30.2.
+template <typename C, bool PRINTED = false>
 __device__ __forceinline__ Rates local_rates(const Rates& rt, const Ext& v, double N,
                                              const Macro& m) {
+  if constexpr (PRINTED) {
+    const double n_printed = N / (1.0 / sqrt(1.0 - m.u2));  // of rates_printed
+    if (!(v.eta_s > 0.0) || !(n_printed > 0.0) || !(m.P > 0.0)) return rt;
+    Rates r = rt;
+    rates_printed(v, N, m, r);
+    return r;
+  }
   const double n = N * root01(1.0 - m.u2);
   if (!(v.eta_s > 0.0) || !(n > 0.0) || !(m.P > 0.0)) return rt;
   const double x = n * recip(m.P);
@@ -564,8 +579,8 @@ __device__ __forceinline__ void collide_g(C (&g)[19], double Mx, double My, doub
 
 // One collision of both distributions in place on the stored deviations.
 // Returns admissibility; sums receives the FP64 Eq. (10) sums of the incoming
-// populations. EXT: relaxation times of this cell from eta/s (local_rates).
-template <typename C, bool EXT = false>
+// populations. EXT: relaxation times of this cell from eta/s (local_rates, PRINTED).
+template <typename C, bool EXT = false, bool PRINTED = false>
 __device__ __forceinline__ bool collide(C (&f)[19], C (&g)[19], const Rates& rt, const Ref& ref,
                                         Sums& sums, const Ext* ext = nullptr) {
   double N, E, Mx, My, Mz, fs, gs;
@@ -578,7 +593,7 @@ __device__ __forceinline__ bool collide(C (&f)[19], C (&g)[19], const Rates& rt,
   Macro mac;
   if constexpr (EXT) {
     if (!recover_model(N, E, Mx, My, Mz, *ext, mac)) return false;
-    const Rates r = local_rates<C>(rt, *ext, N, mac);
+    const Rates r = local_rates<C, PRINTED>(rt, *ext, N, mac);
     collide_f(f, N, fs, mac, r, ref);
     collide_g(g, Mx, My, Mz, gs, mac, r, ref);
   } else {

@@ -325,7 +325,7 @@ __device__ __forceinline__ Recovered recovered(const C (&f)[9], const C (&g)[9],
   return r;
 }
 
-template <typename C, bool CORR = false, bool EXT = false>
+template <typename C, bool CORR = false, bool EXT = false, bool PRINTED = false>
 __device__ __forceinline__ bool collide_recovered(C (&f)[9], C (&g)[9], const Recovered& r,
                                                   const Rates& rt_member, const Ref& ref,
                                                   Sums& sums, const C7Fields* fm = nullptr,
@@ -338,7 +338,7 @@ __device__ __forceinline__ bool collide_recovered(C (&f)[9], C (&g)[9], const Re
   sums.v[4] = 0.0;
   if (!r.ok) return false;
   Rates rt = rt_member;
-  if constexpr (EXT) rt = local_rates<C>(rt_member, *ext, r.N, r.mac);
+  if constexpr (EXT) rt = local_rates<C, PRINTED>(rt_member, *ext, r.N, r.mac);
   double c7 = 0.0;
   if constexpr (CORR) c7 = d2q9::c7_row(r.mac, *fm, *fp);
   d2q9::collide_f(f, r.N, r.fs, r.mac, rt, ref);
@@ -346,14 +346,14 @@ __device__ __forceinline__ bool collide_recovered(C (&f)[9], C (&g)[9], const Re
   return true;
 }
 
-template <typename C, bool CORR = false, bool EXT = false>
+template <typename C, bool CORR = false, bool EXT = false, bool PRINTED = false>
 __device__ __forceinline__ bool collide(C (&f)[9], C (&g)[9], const Rates& rt_member,
                                         const Ref& ref, Sums& sums,
                                         const C7Fields* fm = nullptr,
                                         const C7Fields* fp = nullptr,
                                         const Ext* ext = nullptr) {
   const Recovered r = recovered<C, EXT>(f, g, ref, ext);
-  return collide_recovered<C, CORR, EXT>(f, g, r, rt_member, ref, sums, fm, fp, ext);
+  return collide_recovered<C, CORR, EXT, PRINTED>(f, g, r, rt_member, ref, sums, fm, fp, ext);
 }
 
 // Equilibrium deviations of a cell from its fields (Eqs. 7, 32, 33), FP64;

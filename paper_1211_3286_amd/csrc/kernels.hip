@@ -65,7 +65,7 @@ __global__ __launch_bounds__(NT) void k_step_members(MemberLaunch a) {
             g[q] = ld(src + (int64_t)(19 + q) * a.cs, off[q]);
           }
           Sums s;
-          const bool ok = collide<T, EXT>(f, g, d.rt, d.ref, s, &d.ext);
+          const bool ok = collide<T, EXT, sizeof(T) == 4>(f, g, d.rt, d.ref, s, &d.ext);
           nbad += ok ? 0 : 1;
 #pragma unroll
           for (int i = 0; i < 5; ++i) acc[i] += s.v[i];

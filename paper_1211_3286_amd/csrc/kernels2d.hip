@@ -58,7 +58,7 @@ __global__ __launch_bounds__(BX* BY) void k_d2q9_lattice(const T* __restrict__ s
       }
       Sums s;
       const bool ok =
-          d2q9::collide<T, CORR, EXT>(f, g, geo.rt, geo.ref, s, &fm, &fp, &geo.ext);
+          d2q9::collide<T, CORR, EXT, sizeof(T) == 4 && (CY > 1)>(f, g, geo.rt, geo.ref, s, &fm, &fp, &geo.ext);
       nbad += ok ? 0 : 1;
       if (DIAG)
 #pragma unroll
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(NT) void k_d2q9_members(MemberLaunch a) {
           }
           Sums s;
           const bool ok =
-              d2q9::collide<T, CORR, EXT>(f, g, d.rt, d.ref, s, &fm, &fp, &d.ext);
+              d2q9::collide<T, CORR, EXT, sizeof(T) == 4>(f, g, d.rt, d.ref, s, &fm, &fp, &d.ext);
           nbad += ok ? 0 : 1;
 #pragma unroll
           for (int i = 0; i < 5; ++i) acc[i] += s.v[i];

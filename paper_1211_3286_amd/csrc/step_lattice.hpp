@@ -146,7 +146,7 @@ __global__ __launch_bounds__(BX* BY) void k_step_lattice(const T* __restrict__ s
           g[a] = get(src + geo.lay.greg, a);
         }
         Sums s;
-        const bool ok = collide<T, EXT>(f, g, geo.rt, geo.ref, s, &geo.ext);
+        const bool ok = collide<T, EXT, sizeof(T) == 4 && (CZ > 1)>(f, g, geo.rt, geo.ref, s, &geo.ext);
         nbad += ok ? 0 : 1;
         if (DIAG)
 #pragma unroll
