@@ -26,6 +26,8 @@ constexpr size_t kAlign = 256;
 constexpr int64_t kLatticeMinCells = 16384;
 // Double-buffered states up to this size are stored with plain stores.
 constexpr size_t kCachedStateBytes = size_t(1) << 30;
+// The last-level cache.
+constexpr uint64_t kCacheBytes = uint64_t(256) << 20;
 // Smallest z-plane and state of a lattice stored in blocks (blocked_layout).
 constexpr int64_t kBlockedMinPlane = 1024;
 constexpr uint64_t kBlockedMinState = uint64_t(128) << 20;
@@ -657,12 +659,15 @@ int default_strip(const rlb_sim* h) {
 // spreads the cells over the chip and streams them all. us a step by member kernel
 // and launches (256 CUs; 11^3 is 3 passes, 13^3 5, 16^3 and 64^2 8, 40^2 4):
 //   D3Q19 FP32: 128 of 11^3 16 and 13, 192 17 and 18, 1024 71 and 119; 256 of 13^3 29
-//     and 34, of 16^3 81 and 66; with eta/s 256 of 11^3 30 and 24;
+//     and 34, of 16^3 81 and 66; eta/s, from where a step no longer streams from the
+//     last-level cache: 512 of 11^3 (198 MiB of state) 47 and 40, 768 (296) 72 and
+//     81, 512 of 13^3 (326) 72 and 84;
 //   FP64: 64 of 11^3 15 and 13, 96 16 and 17, 1024 135 and 193; 128 of 13^3 27 and 32;
 //     256 of 16^3 124 and 136, 384 206 and 191, 512 253 and 265; eta/s the same;
 //   D2Q9: 64 of 40^2 FP32 5.4 and 7.3, FP64 7.9 and 8.7; 256 of 64^2 FP32 21 and 26,
-//     FP64 47 and 55; one of 33 x 32 FP32 4.0 and 4.8; eta/s FP32 256 of 40^2 19
-//     and 14; correction: 128 of 40^2 FP32 11.8 and 13.7, FP64 14 and 18.
+//     FP64 47 and 55; one of 33 x 32 FP32 4.0 and 4.8; eta/s FP32 128 of 40^2 11.4
+//     and 10.4, 256 12 and 14, 512 26 and 24, of 33 x 32 15 and 18; correction: 128
+//     of 40^2 FP32 11.8 and 13.7, FP64 14 and 18, eta/s FP32 256 18 and 19.
 bool members_fill_the_chip(const rlb_sim* h) {
   const auto passes_of = [](int64_t cells) { return (cells + 511) / 512; };
   const int64_t passes = passes_of(h->L.max_member);
@@ -671,7 +676,12 @@ bool members_fill_the_chip(const rlb_sim* h) {
   // members, were they all as large as the largest, per CU
   const double load = (double)total / passes / h->num_cu;
   const bool fp32 = h->precision == RLB_FP32;
-  if (fp32 && h->ext) return h->corr && passes <= 4 && load >= 0.75 && load <= 1.0;
+  if (fp32 && h->ext) {
+    if (!h->d2)
+      return passes <= 5 && 2 * 38 * sizeof(float) * (uint64_t)h->L.ncells > kCacheBytes;
+    return passes <= (h->corr ? 4 : 5) && load >= 0.75 &&
+           load <= (!h->corr && passes <= 3 ? 2.0 : 1.0);
+  }
   if (h->d2 && !h->corr) {
     if (fp32) return passes <= 3 || (passes <= 16 && load >= (passes <= 5 ? 0.25 : 0.5));
     return passes <= 8 && load >= (passes <= 4 ? 0.25 : passes <= 5 ? 0.375 : 0.5);

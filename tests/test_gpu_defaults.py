@@ -85,6 +85,9 @@ MEMBERS, LAUNCHES = "members", "cells"
     (lambda: _plane(64, 64), 256, {FP32: MEMBERS, FP64: MEMBERS}),
     (lambda: _plane(40, 40, 1), 128, {FP32: MEMBERS, FP64: MEMBERS}),
     (lambda: _plane(40, 40, 0, 0.1), 128, {FP32: LAUNCHES, FP64: MEMBERS}),
+    (lambda: _plane(40, 40, 0, 0.1), 256, {FP32: MEMBERS, FP64: MEMBERS}),
+    (lambda: _plane(33, 32, 0, 0.1), 512, {FP32: MEMBERS, FP64: MEMBERS}),
+    (lambda: _box(11, 11, 11, 0.1), 800, {FP32: MEMBERS, FP64: MEMBERS}),
 ])
 def test_batches_that_fill_the_chip_take_the_member_kernel(make, members, want):
     prob = make()
