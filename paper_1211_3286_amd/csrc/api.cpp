@@ -341,17 +341,30 @@ rlb_status launch_lattice_step(rlb_sim* h, int variant, bool diag, const void* s
                                           h->d_partials, h->d_bad, h->stream));
 }
 
+// One-step blocks of a corrected D2Q9 lattice: 64 x 4, which share the neighbours'
+// fields, or 128 x 2 where rows begin off the memory's granules and the state is far
+// out of the caches. us a step, 64 x 4, 128 x 2 and 256 x 1 blocks: 1531 x 1203 FP64
+// 130, 137, 140, FP32 56, 71, 73, 2048^2 FP32 130, 140, 152, 1500 x 4000 211, 240, 235;
+// 1082 x 2685 FP64 222, 206, 210, FP32 125, 124, 123, 1906 x 1500 FP64 224, 202, 205,
+// FP32 125, 121, 118, 2925 x 2045 FP32 259, 240, 240.
+int corrected_blocks(const rlb_sim* h) {
+  const rlb_params& p = h->params[0];
+  return p.nx % 4 != 0 && (int64_t)p.nx * p.ny > 2500000 ? 4 : 3;
+}
+
 // Marching variants (D3Q19: two steps per launch, D2Q9: H); steps that do not
 // fill a launch (the last of a call, diagnostics steps) run a one-step kernel, in
 // blocks as the rows are long. us a step, 128 x 2, 64 x 4 and 256 x 1 blocks: D3Q19
 // 96^3 FP32 44, 47, 44, 160^3 245, 213, 208, 187 x 150 x 131 339, 319, 343, 256^3 880,
 // 874, 885; D2Q9, the last two: 300^2 FP64 6.4 and 8.2, 700 x 500 FP32 11.9 and 10.8,
-// 1000 x 800 22.8 and 20.9, 1531 x 1203 FP64 122 and 117, 2048^2 223 and 226; with
-// the correction 64 x 4 is the better one everywhere.
+// 1000 x 800 22.8 and 20.9, 1531 x 1203 FP64 122 and 117, 219 x 4482 65 and 57, 2048^2
+// 223 and 226, 200^2 4.5 and 5.0; with the correction corrected_blocks.
 int march_step(const rlb_sim* h) {
-  const int nx = h->params[0].nx;
-  if (h->d2) return h->corr || nx <= 384 ? 3 : 2;
-  return nx > 64 && nx <= 128 ? 2 : 1;
+  const rlb_params& p = h->params[0];
+  if (!h->d2) return p.nx > 64 && p.nx <= 128 ? 2 : 1;
+  const auto lanes = [&](int bx) { return (p.nx + bx - 1) / bx * bx; };  // of a row
+  const bool idle = 5 * lanes(256) > 6 * lanes(64) || (int64_t)p.nx * p.ny < 65536;
+  return h->corr ? corrected_blocks(h) : idle ? 3 : 2;
 }
 
 int march_base(const rlb_sim* h) {
@@ -456,7 +469,7 @@ int tile_singles(const rlb_sim* h, int64_t tiles, int left) {
   return left == 1 ? 1 : 0;
 }
 
-int tile_single(const rlb_sim* h) { return h->corr ? 3 : 2; }
+int tile_single(const rlb_sim* h) { return h->corr ? corrected_blocks(h) : 2; }
 
 // D2Q9 tile rounds: ceil(n / H) launches, each advancing up to H steps of the
 // whole lattice; rounds alternate the buffers (pingpong) or always read a and
@@ -515,9 +528,8 @@ rlb_status launch_tile_rounds(rlb_sim* h, int variant, int nsteps, int pingpong,
 //     and 6.0, 550^2 8.7 and 10.1, FP64 3.2 and 4.2, 5.1 and 8.0, 10.9 and 15.7. With
 //     eta/s or the correction, whose halos cost more, only while every window finds
 //     a CU: eta/s 250^2 FP32 4.1 and 5.3, 270 x 260 7.3 and 6.5; correction 150^2
-//     FP64 4.3 and 5.8, 250^2 10.0 and 9.4; else 64 x 4 blocks with the correction,
-//     which share the neighbours' fields (1531 x 1203 FP64 128 and 135, FP32 50 and
-//     70), and 256 x 1. No tiles either where a window is less than half full of rows
+//     FP64 4.3 and 5.8, 250^2 10.0 and 9.4; else corrected_blocks with the
+//     correction, and 256 x 1. No tiles either where a window is less than half full of rows
 //     (100000 x 4 FP32 17.0 and 11.7, x 7 11.5 and 10.5; one row with the correction
 //     100000 x 1 7.4 in 64 x 4 blocks and 6.5), nor in FP32 with more than 5
 //     windows a CU (700 x 500, 1350, 10.1 and 10.4) or, with diagnostics at every
@@ -540,7 +552,7 @@ int default_lattice(const rlb_sim* h) {
       tile_geometry(v, p.nx, p.ny, h->corr, a, grid) &&
       (int64_t)grid.x * grid.y <= per_cu * h->num_cu)
     return rlb::d2q9_num_lattice_variants() + tv;
-  return h->corr && p.ny > 1 ? 3 : 2;
+  return h->corr && p.ny > 1 ? corrected_blocks(h) : 2;
 }
 
 constexpr int kSpinLimit = 1 << 24;  // about a second of polling per wait

@@ -74,7 +74,8 @@ def test_single_steps_of_a_tile_default_cost_a_one_step_kernel():
     ((96, 80, 64), "d3q19", FP32, 2), ((160, 72, 64), "d3q19", FP32, 1),
     ((45, 60, 140), "d3q19", FP64, 1), ((300, 290, 1), "d2q9", FP64, 3),
     ((700, 400, 1), "d2q9", FP64, 2), ((1000, 300, 1), "d2q9", FP32, 2),
-], ids=["d3q19-96", "d3q19-160", "d3q19-45", "d2q9-300", "d2q9-700", "d2q9-1000"])
+    ((219, 800, 1), "d2q9", FP64, 2),
+], ids=["d3q19-96", "d3q19-160", "d3q19-45", "d2q9-300", "d2q9-700", "d2q9-1000", "d2q9-219"])
 def test_steps_between_marching_launches_by_row_length(shape, lattice, prec, blocks):
     """Single and diagnostics steps of a marching handle take the block shape that
     suits the rows: the sums are added in its order."""
@@ -94,3 +95,31 @@ def test_steps_between_marching_launches_by_row_length(shape, lattice, prec, blo
         assert bool((x == y).all())
     sim.close()
     ref.close()
+
+
+@pytest.mark.parametrize("shape,blocks", [((1501, 200), "64,4,1"), ((2000, 1252), "64,4,1"),
+                                          ((1998, 1253), "128,2,1")])
+def test_blocks_of_corrected_lattices_by_rows_and_size(shape, blocks):
+    """One-step default of a corrected lattice in FP32 with eta/s, and the steps
+    between the marching launches of one without, which add the same sums."""
+    import numpy as np
+    import paper_1211_3286_amd as rlb
+    prob = _plane(*shape, corr=1)
+    sim, ref = (rlb.from_problems(prob, precision=FP64, diag_every=1) for _ in range(2))
+    sim.variant = next(i for i, n in enumerate(sim.variants()) if "march" in n)
+    ref.variant = next(i for i, n in enumerate(ref.variants()) if f",{blocks}>+c7" in n)
+    say(shape, sim.kernel_name, ref.kernel_name)
+    for n in (1, 2):
+        sim.step(n)
+        ref.step(n)
+        assert np.array_equal(sim.diagnostics()[0], ref.diagnostics()[0])
+    for x, y in zip(sim.populations(), ref.populations()):
+        assert bool((x == y).all())
+    sim.close()
+    ref.close()
+    prob.n *= 1.7e-7 / 0.0314
+    prob.eps *= 5.1e-7
+    prob.params.eta_s, prob.params.a_e, prob.params.a_eps = 0.1, 1.0, 1.0
+    sim = rlb.from_problems(prob, precision=FP32)
+    assert f",{blocks}>+c7" in sim.kernel_name
+    sim.close()
