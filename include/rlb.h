@@ -302,7 +302,8 @@ const char* rlb_status_string(rlb_status s);
  *     rlb_moments with out_on_device = 1; any may be NULL.
  *   sums: host, 5 doubles or NULL; n_unphysical: host or NULL (as rlb_moments).
  *   hip_stream: hipStream_t (NULL = null stream); the call synchronises it.
- * Returns RLB_E_UNPHYSICAL for inadmissible input cells (nothing computed) or
+ * Returns RLB_E_UNPHYSICAL for inadmissible input cells (no output written; the
+ * steps are enqueued ahead of the answer and run on the scratch array) or
  * cells that became inadmissible (outputs written, as rlb_moments). */
 #define RLB_NOALLOC_SCRATCH_BYTES (64u * 1024u * 1024u)
 rlb_status rlb_run_noalloc(const rlb_params* member, const rlb_options* opt,

@@ -288,8 +288,9 @@ __device__ __forceinline__ void rates_printed(const Ext& v, double N, const Macr
   if (v.a_q > 0.0) r.s_q = 1.0 / (0.5 + v.a_q * (tv - 0.5));
 }
 
-// Whether x is so near to halfway between two floats that 3e-12 of it could
-// change the float it rounds to (1 in 16000 values).
+// Whether x is so near to halfway between two floats that 2^-39 of it (1.8e-12; at
+// the low end of its binade twice that) could change the float it rounds to: 1 in
+// 16000 values.
 __device__ __forceinline__ bool float_in_doubt(double x) {
   constexpr uint32_t kHalf = 1u << 28, kNear = 1u << 14;  // of the 29 bits a float drops
   const uint32_t low = (uint32_t)__double_as_longlong(x) & ((1u << 29) - 1);
@@ -303,17 +304,22 @@ __device__ __forceinline__ bool float_in_doubt(double x) {
 // the mean, by 1.5e-13 (as printed) and 0.8e-13 at most, where 4 - ln lambda
 // cancels. FP32 collisions use the rates rounded to floats: where a rounding
 // hangs on the last bits the printed form decides, so that both give the same
-// populations. One step of 1000 x 800 D2Q9 FP64 (marching) 32 and 26 us; 8 steps of
-// the four Cases of 4 x 800 cells, FP64, 17 and 14; 160^3 FP32 (one-step) 236 and
-// 207.
+// populations. By how much the two can differ: some 28 roundings enter ln lambda
+// between them and 2 ulp of it their logarithms, so L = 4 - ln lambda differs by
+// |dL| <= (28 + 2 |ln lambda|) 2^-53, and a rate 1 / (1/2 + a w), w = c L > 0, by
+// min(|dL| / L, 2 a c |dL|) and a few 2^-53 of itself. float_in_doubt allows for
+// 2^-39 of it at least, which is more unless L < 0.0022 and at once a c > 220. (For w <
+// 0, tau below 1/2, the scheme is unstable and nothing is claimed.) One step of 1000 x
+// 800 D2Q9 FP64 (marching) 32 and 26 us; 8 steps of the four Cases of 4 x 800 cells,
+// FP64, 17 and 14; 160^3 FP32 (one-step) 236 and 207.
 //
 // PRINTED: the printed form alone, for FP32 kernels with a loop around the
 // collision. There both forms' constants stay in scalar registers across the loop,
 // more than there are (252 v_readlane where the printed form has 70), and the two
 // need more vector registers (131 for 108: 3 waves a SIMD for 4). us a step of the
 // member kernels, both forms and the printed one: D2Q9 4 x 3 cells 3.1 and 2.1, 300
-// of 40^2 29.4 and 17.7, D3Q19 600 of 8^3 28.3 and 24.9; 256 x 1
-// blocks of 4 cells a thread, 40^3 34.0 and 30.2.
+// of 40^2 29.4 and 18.4, D3Q19 600 of 8^3 28.3 and 24.4; 256 x 1 blocks of 4 cells a
+// thread with the correction, 1000 x 800 41 and 36.
 template <typename C, bool PRINTED = false>
 __device__ __forceinline__ Rates local_rates(const Rates& rt, const Ext& v, double N,
                                              const Macro& m) {

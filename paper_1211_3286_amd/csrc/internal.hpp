@@ -240,8 +240,6 @@ int num_segment_variants();
 MemberVariant segment_variant(int i);  // (threads per block, cells per thread)
 hipError_t segment_kernel(int precision, int variant, const void** func, dim3* block);
 const char* segment_kernel_name(int precision, int variant);
-hipError_t launch_step_members(int precision, int variant, int n_members, const MemberLaunch& a,
-                               hipStream_t s);
 // The fields of the state; nothing is written while *refused is not 0 (null: always).
 hipError_t launch_export(int precision, const void* state, const StateLayout& l,
                          const MemberDesc* descs, int n_members, int64_t ncells, double* n, double* eps, double* P,
@@ -328,7 +326,7 @@ hipError_t d2q9_launch_population_planes(int precision, const void* state, int64
 int d2q9_num_march_variants(bool corr);
 int d2q9_march_steps(int variant, bool corr);
 bool d2q9_march_fits(const LatticeGeom& g);
-// Share of variant 0's cell slots that are cells of the lattice.
+// Share of a variant's cell slots that are cells of the lattice.
 double d2q9_march_use(int precision, int variant, bool corr, bool ext, const LatticeGeom& g, int cus);
 const char* d2q9_march_kernel_name(int precision, int variant, bool corr);
 hipError_t d2q9_launch_march(int precision, int variant, bool corr, bool ext, const void* src,

@@ -216,7 +216,11 @@ struct TubePlanes {
   }
 };
 
-// The work of a thread on the distributions it has (F: f, G: g).
+// The work of a thread on the distributions it has (F: f, G: g). The f and the g
+// waves of a split block run this function in two instantiations and meet at its
+// barriers, which count waves wherever they stand in the code: every wave must pass
+// as many. So no barrier, and no way out of the loop, may depend on F, G or the
+// lane; block_sum5 counts too, and its shared array is the same one for both.
 template <typename T, int NT, bool EXT, bool F, bool G>
 __device__ __forceinline__ void tube_cell(const TubeRound& a, T (*__restrict__ lds)[NT], int w) {
   using P = TubePlanes<EXT>;
@@ -702,16 +706,6 @@ hipError_t member_kernel(int precision, int v, bool ext, const void** func, dim3
     *func = precision ? mem_func<float, false>(v) : mem_func<double, false>(v);
   *block = dim3(kMem[v].nt, 1, 1);
   return hipSuccess;
-}
-
-hipError_t launch_step_members(int precision, int v, int n_members, const MemberLaunch& a,
-                               hipStream_t s) {
-  const void* f;
-  dim3 block;
-  hipError_t e = member_kernel(precision, v, false, &f, &block);
-  if (e != hipSuccess) return e;
-  void* args[] = {const_cast<MemberLaunch*>(&a)};
-  return hipLaunchKernel(f, dim3(n_members), block, args, 0, s);
 }
 
 hipError_t launch_export(int precision, const void* state, const StateLayout& l,
