@@ -908,7 +908,8 @@ def summarize_trace(csv_path: str, command: str, top: int = 25, min_launches: in
 
 
 def write_traffic(*csvs: str, cells: int = 256 ** 3) -> dict:
-    """HBM bytes per dispatch of every step-kernel variant from pairs of PMC
+    """HBM bytes per dispatch of every step-kernel variant (a marching one makes
+    two steps, at the algorithmic bytes of one pass) from pairs of PMC
     runs (FETCH_SIZE, WRITE_SIZE in KiB; e.g. one pair per precision), each
     counter scaled by what it reads for the 1 GiB plain copy of
     --copy-calibration in the same run."""
@@ -935,12 +936,18 @@ def _traffic_pair(fetch_csv: str, write_csv: str, cells: int) -> dict:
     scale = {c: (1 << 30) / copy[c] for c in copy}
     out = {"_calibration": {"copy_bytes": 1 << 30, "counter_bytes": copy, "scale": scale}}
     for (k, g, c), v in vals.items():
-        # k_step_lattice<T, BX, BY, CZ, DIAG, EXT, NTS>: the launches with fused
-        # diagnostics and the eta/s kernels are not priced
-        m = re.search(r"k_step_lattice<(\w+), (\d+), (\d+), (\d+), (\w+), (\w+), (\w+)>", k)
-        if not m or m.group(5) == "true" or m.group(6) == "true":
+        # k_step_lattice<T, BX, BY, CZ, DIAG, EXT, NTS[, BLOCKS]>: the launches with
+        # fused diagnostics and the eta/s kernels are not priced; k_step_march<T, WX,
+        # WY, NT, EXT, NTS>: two steps a launch
+        m = re.search(r"k_step_lattice<(\w+), (\d+), (\d+), (\d+), (\w+), (\w+), (\w+)(?:, \w+)?>",
+                      k)
+        h = re.search(r"k_step_march<(\w+), (\d+), (\d+), \d+, (\w+), \w+>", k)
+        if m and m.group(5) != "true" and m.group(6) != "true":
+            name = "k_step_lattice<{},{},{},{}>".format(*m.groups()[:4])
+        elif h and h.group(4) != "true":
+            name = "k_step_march<{},{},{}>".format(*h.groups()[:3])
+        else:
             continue
-        name = "k_step_lattice<{},{},{},{}>".format(*m.groups()[:4])
         rec = out.setdefault(name, {"cells": cells, "source_hash": kernel_hash()})
         rec[c.lower() + "_bytes"] = sum(v) / len(v) * scale[c]
     for name, rec in out.items():
@@ -1018,9 +1025,16 @@ def d2q9_kernel_name(kernel: str, grid: int, n: int = 4096):
     n x n periodic lattice, from the mangled-template name in a rocprofv3
     record and its grid (threads): k_d2q9_lattice<T, BX, BY, CY, DIAG, CORR,
     EXT, NTS>, k_d2q9_lattice_c7<T, BX, BY, DIAG, EXT, NTS> (one step a
-    launch) and k_d2q9_tiles<T, TX, TY, NTH, CORR, EXT> (H steps a launch,
-    H recovered from the number of tiles in the grid). None for launches
-    with fused diagnostics, the extended model, or other kernels."""
+    launch), k_d2q9_march<T, H, CORR, EXT> (H steps) and k_d2q9_tiles<T, TX,
+    TY, NTH, CORR, EXT> (H steps, H recovered from the number of tiles in the
+    grid). None for launches with fused diagnostics, the extended model, or
+    other kernels."""
+    m = re.search(r"k_d2q9_march<(\w+), (\d+), (\w+), (\w+)", kernel)
+    if m:
+        typ, H, corr, ext = m.groups()
+        if ext == "true":
+            return None
+        return f"k_d2q9_march<{typ}>/h{H}" + ("+c7" if corr == "true" else ""), int(H)
     m = re.search(r"k_d2q9_tiles<(\w+), (\d+), (\d+), (\d+), (\w+), (\w+)", kernel)
     if m:
         typ, tx, ty, nth, corr, ext = m.groups()

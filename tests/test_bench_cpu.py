@@ -270,3 +270,35 @@ def test_launch_shape_claims_no_more_than_the_name_tells():
         "launches": 50, "steps_per_launch": 1}
     assert bench.launch_shape("k_step_members<float,512,1>", 3000) == {
         "launches": 1, "steps_per_launch": 3000}
+
+
+def test_traffic_of_the_kernels_as_they_are_named_now(tmp_path):
+    """The one-step kernel's names end in a flag for its layout, and marching
+    launches make several steps at the bytes of one pass and some halos."""
+    cells, kib, n = 1000, 1024.0, 64
+    alg = 2 * 38 * 4 * cells
+    k1 = _lat("false, false, true, true")
+    k2 = ("void rlb::(anonymous namespace)::k_step_march<float, 34, 15, 512, false, true>("
+          "float const*)")
+    eta = k2.replace("512, false", "512, true")
+    fetch = [(COPY, "131072", "FETCH_SIZE", (1 << 29) / kib)]
+    write = [(COPY, "131072", "WRITE_SIZE", (1 << 30) / kib)]
+    for k, r in ((k1, 1.0), (k2, 1.1), (eta, 9.0)):
+        fetch.append((k, "1", "FETCH_SIZE", r * alg / 4 / kib))
+        write.append((k, "1", "WRITE_SIZE", r * alg / 2 / kib))
+    d2 = "void rlb::(anonymous namespace)::k_d2q9_march<double, 2, true, false>(double const*)"
+    fetch.append((d2, "512", "FETCH_SIZE", 288.0 * n * n / 4 / kib))
+    write.append((d2, "512", "WRITE_SIZE", 288.0 * n * n / 2 / kib))
+    _write(tmp_path / "f.csv", fetch)
+    _write(tmp_path / "w.csv", write)
+    out = bench.write_traffic(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), cells=cells)
+    names = sorted(k for k in out if not k.startswith("_"))
+    assert names == ["k_step_lattice<float,64,4,1>", "k_step_march<float,34,15>"]
+    assert abs(out["k_step_lattice<float,64,4,1>"]["ratio"] - 1.0) < 1e-12
+    assert abs(out["k_step_march<float,34,15>"]["ratio"] - 1.1) < 1e-12
+    # bench.py looks a variant's record up by its name without the steps
+    assert "k_step_march<float,34,15>/h2".split("/")[0] in out
+    rec = bench.d2q9_traffic(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), n=n)["kernels"]
+    assert list(rec) == ["k_d2q9_march<double>/h2+c7"]
+    rec = rec["k_d2q9_march<double>/h2+c7"]
+    assert rec["steps_per_launch"] == 2 and abs(rec["bytes_per_cell_update"] - 144.0) < 1e-9
