@@ -165,6 +165,17 @@ def _dptr(t) -> int:
     return int(t.data_ptr())
 
 
+def _after_current(stream, device) -> None:
+    """A handle's stream waits for the current one, on which the tensors of the
+    coming call were made: inputs still being written, and outputs in memory
+    whose last user may still run. (Of ``stream`` only cuda_stream is read.)"""
+    import torch
+    cur = torch.cuda.current_stream(device)
+    mine = int(stream.cuda_stream)
+    if mine != int(cur.cuda_stream):
+        torch.cuda.ExternalStream(mine, device=device).wait_stream(cur)
+
+
 class Simulation:
     """One handle of the C ABI: a lattice, or a batch of lattices.
 
@@ -218,12 +229,7 @@ class Simulation:
 
     # -- lifetime --------------------------------------------------------
     def _after_current(self) -> None:
-        """A handle's stream waits for the current one, on which the tensors of
-        the coming call were made: inputs still being written, and outputs in
-        memory whose last user may still run."""
-        cur = self.torch.cuda.current_stream(self.device)
-        if cur != self.stream:
-            self.stream.wait_stream(cur)
+        _after_current(self.stream, self.device)
 
     def close(self) -> None:
         if getattr(self, "h", None) and self.h.value:
@@ -408,10 +414,8 @@ def run_noalloc(params, n0, eps0, u0, nsteps: int, precision: int = FP32, lattic
     arr = cparams([params])
     sums = (ctypes.c_double * 5)()
     bad = ctypes.c_int64(0)
-    cur = torch.cuda.current_stream(dev)
-    st = stream if stream is not None else cur
-    if st != cur:  # the fields and outputs were made on the current stream
-        st.wait_stream(cur)
+    st = stream if stream is not None else torch.cuda.current_stream(dev)
+    _after_current(st, dev)
     code = lib().rlb_run_noalloc(arr, ctypes.byref(opt), *[_dptr(t) for t in fields], int(nsteps),
                                  _dptr(out["n"]), _dptr(out["eps"]), _dptr(out["P"]),
                                  _dptr(out["gamma"]), _dptr(out["u"]), sums, ctypes.byref(bad),

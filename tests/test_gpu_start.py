@@ -62,9 +62,13 @@ def test_a_stream_of_its_own_waits_for_the_current_one():
             v = (v @ w) * 1e-4
         return out.copy_(t + 0.0 * v.flatten()[0].clamp(0, 1))
 
+    class Raw:  # anything with a stream's address
+        def __init__(self, s):
+            self.keep, self.cuda_stream = s, s.cuda_stream
+
     got = []
-    for stream in (None, torch.cuda.Stream()):
-        say("handle on", "the current stream" if stream is None else "another stream")
+    for stream in (None, torch.cuda.Stream(), Raw(torch.cuda.Stream())):
+        say("handle on", "the current stream" if stream is None else type(stream).__name__)
         sim = rlb.Simulation([prob.params], late(n0), late(e0), late(u0), precision=0,
                              ckpt_every=2, tape_steps=4, stream=stream)
         sim.step(4)
@@ -76,5 +80,6 @@ def test_a_stream_of_its_own_waits_for_the_current_one():
         got.append([m["u"], m["eps"], torch.as_tensor(dtau), de0, du0, r["u"], r["eps"]])
         sim.close()
     assert nc == got[0][1].numel()
-    for a, b in zip(*got):
-        assert bool((a == b).all())
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert bool((a == b).all())
