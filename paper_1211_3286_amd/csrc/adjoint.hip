@@ -315,8 +315,10 @@ __global__ __launch_bounds__(256) void k_adj_step(SweepLaunch<T> a) {
                            gridDim.x);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_gstep(SweepLaunch<T> a) {
+// W: at most so many waves of it on a SIMD (by register count; 0: as many as fit).
+template <typename T, int W>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(W ? W : 1, W ? W : 8))) void k_gstep(SweepLaunch<T> a) {
   gstep_block(a.gsrc, a.gdst, a.cs, a.d, blockIdx.x, gridDim.x);
 }
 
@@ -376,6 +378,14 @@ __global__ __launch_bounds__(256) void k_sum_parts(const double* parts, int n, d
 // graph of single kernels 1.6).
 constexpr int64_t kPairBlocks = 256;
 
+// Recomputed steps on the second stream keep to the reverse step's 4 waves a SIMD
+// while a launch has at most this many blocks. FP32 ones would fit 6 and then crowd
+// the reverse steps, which end the chain; FP64 fits 4 by itself. FP32 gradients in
+// us, 6 and 4 waves: 512 x 512 (1024 blocks), 200 steps 4100 and 3950, 1000 steps
+// 19 950 and 18 700; 900 x 700 3050 and 2945; 900 x 900 (3375 blocks) 3929 and 3893;
+// 1024 x 1024 (4096) 3000 and 3110; 1400 x 1000 4355 and 4400.
+constexpr int64_t kBesideBlocks = 3584;
+
 // The second stream and its events, made at the first gradient that wants them
 // and kept with the tape.
 hipError_t side_stream(Tape& t) {
@@ -425,7 +435,10 @@ hipError_t sweep(Tape& t, const GradContext& c, int* cur) {
   bool gathered = false;
   const dim3 block(64, kRows);
   const auto launch_gstep = [&](hipStream_t s) {
-    hipLaunchKernelGGL(k_gstep<T>, dim3(g.nb), block, 0, s, g);
+    if (sizeof(T) == 4 && s != c.stream && g.nb <= kBesideBlocks)
+      hipLaunchKernelGGL((k_gstep<T, 4>), dim3(g.nb), block, 0, s, g);
+    else
+      hipLaunchKernelGGL((k_gstep<T, 0>), dim3(g.nb), block, 0, s, g);
   };
   const auto launch_reverse = [&](bool with_gstep) {  // on the caller's stream
     const dim3 grid(with_gstep ? 2 * ((r.nb + kXcds - 1) / kXcds * kXcds) : r.nb);
