@@ -346,7 +346,7 @@ def bench_blast(torch, rlb, wl, L: int = 512, steps: int = 400, warmup: int = 10
     sim.close()
     del m
     torch.cuda.empty_cache()
-    # the FP64 oracle of 512^3 needs more host memory than the box holds: the
+    # the FP64 oracle of 512^3 needs more host memory than the host holds: the
     # error is stated on the 128^3 analogue (sphere radius 16), 20 steps, in
     # the timed block shape, FP64 (the parity check: admissibility decided on
     # the same inputs) and FP32 (populations can leave the admissible range

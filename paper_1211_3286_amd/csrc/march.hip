@@ -18,7 +18,7 @@
 // read once (x halos hit in L2): 1.07 x 304 B in FP32 (256^3, FETCH_SIZE and
 // WRITE_SIZE: 2.92 and 2.55 GB). What bounds it is memory as far as 2 waves per SIMD
 // keep it busy: 4.5 TB/s (a copy of two streams 5.2 to 6.3) with the VALU issuing in
-// 0.53 to 0.57 of the cycles; 8 % fewer instructions left the time as it was.
+// 0.53 to 0.60 of the cycles; 8 % fewer instructions left the time as it was.
 // Windows: FP32 34 x 15 (OX = 32 cells = one 128-byte line) on 512 threads; two
 // 256-thread blocks of 18 x 14 per CU were slower (0.91 ms a step). FP64 18 x 14
 // on 256 threads (one wave per SIMD, 512 registers; on 512 threads it spills);

@@ -12,10 +12,10 @@
 // It replaces the tiles in LDS (k_d2q9_tiles: 16 % halo cells, index arithmetic
 // per cell, VALU-bound in FP32, two windows a CU in FP64) as the default on
 // large lattices. Bound now: FP32 H = 4 moves 39 B per cell update at 0.195 ms
-// per 4096^2 step, 3.4 TB/s, with the VALU issuing in 0.71 of the cycles of 2 waves
+// per 4096^2 step, 3.4 TB/s, with the VALU issuing in 0.9 of the cycles of 2 waves
 // per SIMD (178 registers); H = 3 and 6 take 0.245 and 0.195 ms, FP64 (76 B, a wave
-// per SIMD, 0.45) H = 3, 4, 6 0.403, 0.299 and 0.293. us a step, best tile and now (H
-// = 4), on one box: 4096^2 FP32 265 and 195, FP64 503 and 299 (217 and 348 on the
+// per SIMD, 0.5) H = 3, 4, 6 0.403, 0.299 and 0.293. us a step, best tile and now (H
+// = 4), one card: 4096^2 FP32 265 and 195, FP64 503 and 299 (217 and 348 on the
 // slowest); 2048^2 FP64 120 and 72; 1531 x 1203 FP32 31 and 26, FP64 52 and 35.
 //
 // With the correction of Eqs. (37)-(38) a stage recovers a row as it arrives and
