@@ -23,9 +23,10 @@ def _modes(shape, lattice="d3q19", corr=0, bc=(0, 0, 0)):
     (lambda: _modes((40, 30, 20)), {}, "k_step_lattice<float,64,4,1>"),
     (lambda: _modes((200, 150, 30)), {"ckpt_every": 4, "tape_steps": 8},
      "k_step_lattice<float,64,4,1>"),
-    (lambda: _modes((3000, 7, 1), "d2q9"), {}, "k_d2q9_lattice<float,256,1,1>"),
+    (lambda: _modes((3000, 7, 1), "d2q9"), {}, "k_d2q9_lattice<float,64,4,1>"),
+    (lambda: _modes((10000, 7, 1), "d2q9"), {}, "k_d2q9_lattice<float,256,1,1>"),
     (lambda: _modes((60, 400, 1), "d2q9", 1, bc=(1, 1, 0)), {}, "k_d2q9_lattice<float,64,4,1>+c7"),
-], ids=["planes", "tape", "few-rows", "few-columns"])
+], ids=["planes", "tape", "few-rows", "few-long-rows", "few-columns"])
 def test_marching_variants_that_cannot_march(make, kw, steps):
     """They bear the name of the kernel that runs, and the tuner neither times nor
     picks them."""
