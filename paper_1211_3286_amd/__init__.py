@@ -414,8 +414,9 @@ def run_noalloc(params, n0, eps0, u0, nsteps: int, precision: int = FP32, lattic
     arr = cparams([params])
     sums = (ctypes.c_double * 5)()
     bad = ctypes.c_int64(0)
+    if stream is not None:
+        _after_current(stream, dev)
     st = stream if stream is not None else torch.cuda.current_stream(dev)
-    _after_current(st, dev)
     code = lib().rlb_run_noalloc(arr, ctypes.byref(opt), *[_dptr(t) for t in fields], int(nsteps),
                                  _dptr(out["n"]), _dptr(out["eps"]), _dptr(out["P"]),
                                  _dptr(out["gamma"]), _dptr(out["u"]), sums, ctypes.byref(bad),
